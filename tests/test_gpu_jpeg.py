@@ -117,6 +117,46 @@ def test_files_whose_rows_are_not_independent(rows, blocks, sub):
                                   what=f"restart rows {rows} blocks {blocks} {sub} scale {scale}")
 
 
+@pytest.mark.parametrize("sub", ["4:2:0", "4:4:4"])
+@pytest.mark.parametrize("side", [64, 256])
+def test_files_without_markers_at_the_edges_of_the_parallel_walk(sub, side):
+    """Files that are one chain of codes are walked in 64 parts at once: fewer blocks than parts
+    (one MCU up), flat images (thousands of blocks of a few bits), blocks longer than a part, white
+    noise at quality 100 (starts that meet the chain late, or never), and a file larger than the
+    memory of the parallel walk (a full-size image of noise, 4:4:4), which takes the serial one."""
+    import io
+
+    from PIL import Image
+    rng = np.random.default_rng(side)
+    jobs = [("flat", 24, 24, 90), ("noise", 3, 5, 100), ("noise", 16, 16, 100), ("noise", 16, 64, 100),
+            ("noise", 40, 23, 75), ("flat", side, side, 90), ("ramp", side, side - 7, 95),
+            ("noise", side, side, 100), ("noise", side - 1, side // 2, 60), ("ramp", side // 2, side, 30)]
+    chunks = []
+    for kind, h, w, quality in jobs:
+        img = np.full((h, w, 3), 77, np.uint8)
+        if kind == "noise":
+            img = rng.integers(0, 256, (h, w, 3), dtype=np.uint8)
+        elif kind == "ramp":
+            img = (np.add.outer(np.arange(h) * 3, np.arange(w) * 2)[..., None]
+                   + np.array([0, 40, 90])).astype(np.uint8)
+        buf = io.BytesIO()
+        Image.fromarray(img).save(buf, format="JPEG", quality=quality, subsampling=sub)
+        chunks.append(np.frombuffer(buf.getvalue(), np.uint8))
+    B = len(chunks)
+    sizes = np.array([c.size for c in chunks], np.int32)
+    offsets = np.zeros(B, np.int64)
+    offsets[1:] = np.cumsum(sizes.astype(np.int64))[:-1]
+    files = np.concatenate(chunks)
+    decoded = _decode_all(files, offsets, sizes)
+    S = 32
+    for scale in ((1.0, 1.0), (0.1, 0.9)):
+        kw = dict(out_size=S, patch=16, num_keep=2, scale=scale, seed=23, batch_index=2)
+        buf, _ = _gpu_jpeg_prep(files, offsets, sizes, max_image_side=side, **kw)
+        assert mae.mae_prep_status(buf.workspace) == 0
+        check_prep_against_oracle(prep_to_numpy(buf), oracle.prep_batch(*decoded, **kw),
+                                  what=f"{sub} side {side} scale {scale}")
+
+
 def test_a_batch_that_mixes_how_its_files_are_organised():
     import io
 
