@@ -355,7 +355,8 @@ int mae_prep_batch(const mae_prep_desc* d, void* visible, uint8_t* mask, int32_t
   // finetuning augmentation: grayscale and solarisation are the resampling kernel's epilogue; the
   // images that drew the blur get their rounded 8-bit crop written to the workspace, and the
   // blur kernel writes their patch rows.  "3 Aug+" needs every image's mean luma after the
-  // brightness step first: one pass that only adds it up, then the pass that writes.
+  // brightness step first: all images' bytes go to the workspace with their luma sums, and a
+  // streaming kernel (the blur kernel's second pass for the blur images) writes the outputs.
   ca.u8_out = ws + wsl.u8_offset;
   ca.aug_mode = d->aug_mode;
   ca.jitter = d->jitter;
@@ -389,12 +390,14 @@ int mae_prep_batch(const mae_prep_desc* d, void* visible, uint8_t* mask, int32_t
   aa.workspace = ws;
   aa.aug_recs = ws + wsl.aug_offset;
   aa.partials = reinterpret_cast<double*>(ws + wsl.partials_offset);
+  aa.luma_partials = ca.luma_partials;
+  aa.luma_slots = ca.G * ca.col_parts;
   aa.visible = visible;
   aa.target = target;
-  hipError_t err = mae::launch_crop_aug(ca, 0, stream);
+  hipError_t err = mae::launch_crop_aug(ca, stream);
   if (err == hipSuccess && d->aug_mode == MAE_AUG_THREE_PLUS) {
     err = mae::launch_aug_blur(aa, true, stream);
-    if (err == hipSuccess) err = mae::launch_crop_aug(ca, 1, stream);
+    if (err == hipSuccess) err = mae::launch_aug_jitter(aa, stream);
   }
   if (err == hipSuccess) err = mae::launch_aug_blur(aa, false, stream);
   return err == hipSuccess ? MAE_OK : MAE_ERR_HIP;

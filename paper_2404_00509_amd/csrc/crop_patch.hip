@@ -42,6 +42,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+typedef u32x3 u32x3_a4 __attribute__((aligned(4)));
 
 // Source taps of output index o when `len` source pixels are resized to S: sample position
 // (o + 1/2) len / S - 1/2 kept as the exact fraction n / (2 S); taps clamped to [0, len).
@@ -627,8 +629,10 @@ __device__ static inline void round_blend3(uint32_t w00, uint32_t w01, uint32_t 
   }
 }
 
-// kPass 0: "3 Aug", or the first pass of "3 Aug+" (kJitter: luma sums only); kPass 1: the second
-// pass of "3 Aug+".  `blur`: this image goes to the blur kernel (bytes only; not called in pass 1).
+// kReduce: "3 Aug+", whose colour jitter needs the whole image first: the bytes go to u8_out with
+// grayscale / solarisation applied (both give whole numbers), their luma after the brightness step
+// is added up, and aug_jitter_kernel does the rest.  `blur`: this image goes to the blur kernel
+// (bytes as they are).
 // kPx: neighbouring pixels of a patch row per lane, 4 when p is a multiple of 4, else 2 (p even):
 // a lane's values are 3 kPx floats = three pieces of kPx floats (16 or 8 bytes).
 template <int kPx>
@@ -642,13 +646,12 @@ struct AugPiece<2> {
   typedef float type __attribute__((ext_vector_type(2)));
 };
 
-template <bool kLds, bool kBf16, bool kJitter, int kPass, int kPx>
+template <bool kLds, bool kBf16, bool kReduce, int kPx>
 __device__ static void produce_aug(const CropArgs& a, const uint32_t* tile, const u32x2* xtab,
                                    const u32x4* ytab, const uint8_t* base, int b, int gy, int gx0,
                                    int npatch, int cw, int my_rank, const AugParams& ap, bool blur,
-                                   float mean, float* strips, double* red64, uint32_t tile_id) {
+                                   float* strips, double* red64, uint32_t tile_id) {
   typedef typename AugPiece<kPx>::type piece_t;
-  constexpr bool kReduce = kJitter && kPass == 0;
   constexpr int kVals = 3 * kPx;  // values per lane and step
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -719,16 +722,33 @@ __device__ static void produce_aug(const CropArgs& a, const uint32_t* tile, cons
       round_blend3(w00, w01, w10, w11, xt.y, cy, ry, dd, inv_dd, v + 3 * j);
     }
 
-    if (blur) {  // the blur kernel's input: the rounded values as bytes
+    if (!blur) {
+#pragma unroll
+      for (int h = 0; h < kPx; ++h) {
+        if (gray) {
+          // (299 R + 587 G + 114 B) / 1000 rounded to nearest: n + 1/2 is at least 0.0005 away from
+          // a multiple of 1000 on either side, far more than the error of the product (n < 2^18)
+          const float n = fmaf(299.0f, v[3 * h],
+                               fmaf(587.0f, v[3 * h + 1], fmaf(114.0f, v[3 * h + 2], 500.5f)));
+          v[3 * h] = v[3 * h + 1] = v[3 * h + 2] = floorf(n * 0.001f);
+        } else {  // solarisation: v >= 128 -> 255 - v, which is the smaller of the two
+#pragma unroll
+          for (int c = 0; c < 3; ++c)  // (the median with zero of two non-negative numbers)
+            v[3 * h + c] = __builtin_amdgcn_fmed3f(v[3 * h + c], 255.0f - v[3 * h + c], 0.0f);
+        }
+      }
+    }
+    if (kReduce || blur) {  // whole numbers 0 .. 255 as bytes, for the kernels that follow
       if (have) {
         // offsets inside one image stay below 2^22: 24-bit multiplies, one 64-bit base
         uint8_t* dst = u8_image + (uint32_t)(__mul24(l0 + gx, D) + 3 * q);
         if constexpr (kPx == 4) {
+          u32x3 w;
 #pragma unroll
           for (int k = 0; k < 3; ++k)
-            reinterpret_cast<uint32_t*>(dst)[k] =
-                (uint32_t)v[4 * k] | ((uint32_t)v[4 * k + 1] << 8) |
-                ((uint32_t)v[4 * k + 2] << 16) | ((uint32_t)v[4 * k + 3] << 24);
+            w[k] = (uint32_t)v[4 * k] | ((uint32_t)v[4 * k + 1] << 8) |
+                   ((uint32_t)v[4 * k + 2] << 16) | ((uint32_t)v[4 * k + 3] << 24);
+          *reinterpret_cast<u32x3_a4*>(dst) = w;
         } else {
 #pragma unroll
           for (int k = 0; k < 3; ++k)
@@ -736,40 +756,18 @@ __device__ static void produce_aug(const CropArgs& a, const uint32_t* tile, cons
                 (uint16_t)((uint32_t)v[2 * k] | ((uint32_t)v[2 * k + 1] << 8));
         }
       }
+      if (blur) continue;
+    }
+    if constexpr (kReduce) {
+#pragma unroll
+      for (int h = 0; h < kPx; ++h) {
+        // equal channels stay equal: their luma is the value itself (the weights add up to one)
+        const float lum = gray ? clamp255(v[3 * h] * ap.brightness)
+                               : jitter_pixel<true>(ap, 0.0f, v[3 * h], v[3 * h + 1], v[3 * h + 2]);
+        lsum += have ? lum : 0.0f;
+      }
       continue;
     }
-
-#pragma unroll
-    for (int h = 0; h < kPx; ++h) {
-      if (gray) {
-        // (299 R + 587 G + 114 B) / 1000 rounded to nearest: n + 1/2 is at least 0.0005 away from
-        // a multiple of 1000 on either side, far more than the error of the product (n < 2^18)
-        const float n =
-            fmaf(299.0f, v[3 * h], fmaf(587.0f, v[3 * h + 1], fmaf(114.0f, v[3 * h + 2], 500.5f)));
-        float g = floorf(n * 0.001f);
-        if (kJitter) {
-          // equal channels stay equal under the jitter: one channel's arithmetic, and the
-          // saturation step leaves it as it is (the luma weights add up to one)
-          g = clamp255(g * ap.brightness);
-          if (kReduce) {
-            lsum += have ? g : 0.0f;
-          } else {
-            g = clamp255(ap.contrast * g + (1.0f - ap.contrast) * mean);
-          }
-        }
-        v[3 * h] = v[3 * h + 1] = v[3 * h + 2] = g;
-        continue;
-      } else {  // solarisation: v >= 128 -> 255 - v, which is the smaller of the two
-#pragma unroll
-        for (int c = 0; c < 3; ++c)  // (the median with zero of two non-negative numbers)
-          v[3 * h + c] = __builtin_amdgcn_fmed3f(v[3 * h + c], 255.0f - v[3 * h + c], 0.0f);
-      }
-      if (kJitter) {
-        const float lum = jitter_pixel<kReduce>(ap, mean, v[3 * h], v[3 * h + 1], v[3 * h + 2]);
-        if (kReduce) lsum += have ? lum : 0.0f;
-      }
-    }
-    if (kReduce) continue;
 
     // normalise, then through the strip: piece k of the strip belongs to group k / 3
     piece_t* mine = reinterpret_cast<piece_t*>(strip + kVals * lane);
@@ -862,8 +860,8 @@ __device__ static void neutral_outputs(const CropArgs& a, int b, int gy, int gx0
 // kLossMode 1, 2: instead of writing the patches, the loss and its gradient against a.pred
 // (1: produce_loss, any patch size; 2: produce_loss_wave, patches of up to 768 values).
 // kLossMode -1: the visible tokens only (no target).
-// kAug: the finetuning augmentation as the epilogue (produce_aug): 1 = "3 Aug", 2 / 3 = first /
-// second pass of "3 Aug+".
+// kAug: the finetuning augmentation as the epilogue (produce_aug): 1 = "3 Aug", 2 = "3 Aug+" up to
+// the colour jitter.
 // kAugPx: pixels per lane of that epilogue (4 when p is a multiple of 4, else 2).
 template <bool kBf16, int kLossMode, int kAug = 0, int kAugPx = 4>
 __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
@@ -904,8 +902,6 @@ __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
   if constexpr (kAug != 0) {
     ap = static_cast<const AugParams*>(a.aug_recs)[b];
     blur = ap.op == kOpBlur;
-    // second pass of "3 Aug+": the blur images' bytes are written already
-    if (kAug == 3 && blur) return;
   }
 
   const int S = a.S, p = a.p;
@@ -1008,22 +1004,13 @@ __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
 
   if constexpr (kAug != 0) {
     __shared__ double red64[kCropMaxThreads / kWave];
-    constexpr bool kJitter = kAug >= 2;
-    constexpr int kPass = kAug == 3 ? 1 : 0;
-    // the wavefronts' strips follow the tables (16-byte aligned)
+    // the wavefronts' strips follow the tables (16-byte aligned; not there for "3 Aug+")
     float* strips = reinterpret_cast<float*>(
         lds + ((a.tile_pixels + 4 + 4 * a.p + 2 * a.part_patches * a.p + 3) & ~3));
-    float mean = 0.0f;
-    if constexpr (kAug == 3) {  // mean luma after the brightness step, from the first pass
-      const int slots = a.G * a.col_parts;
-      double sum = 0.0;
-      for (int g = 0; g < slots; ++g) sum += a.luma_partials[(int64_t)b * slots + g];
-      mean = (float)(sum / ((double)S * (double)S));
-    }
-#define MAE_PRODUCE_AUG(LDS)                                                                      \
-  produce_aug<LDS, kBf16, kJitter, kPass, kAugPx>(a, tile, xtab, ytab, base, b, gy, gx0, npatch,  \
-                                                  rec.cw - xlo, my_rank, ap, blur, mean, strips,  \
-                                                  red64, tile_id)
+#define MAE_PRODUCE_AUG(LDS)                                                                     \
+  produce_aug<LDS, kBf16, kAug == 2, kAugPx>(a, tile, xtab, ytab, base, b, gy, gx0, npatch,      \
+                                             rec.cw - xlo, my_rank, ap, blur, strips, red64,     \
+                                             tile_id)
     if (use_lds) MAE_PRODUCE_AUG(true);
     else MAE_PRODUCE_AUG(false);
 #undef MAE_PRODUCE_AUG
@@ -1232,32 +1219,26 @@ hipError_t launch_crop_loss(const CropArgs& a, hipStream_t stream) {
                             a.ncounts, a.D, stream);
 }
 
-hipError_t launch_crop_aug(const CropArgs& a, int pass, hipStream_t stream) {
+hipError_t launch_crop_aug(const CropArgs& a, hipStream_t stream) {
   dim3 grid((uint32_t)a.B * (uint32_t)a.G * (uint32_t)a.col_parts);
   // the groups of four pixels are dealt to the lanes, so any number of wavefronts will do: at
   // most four (their strips share the LDS with the tile)
   const int waves = ((a.D >> 2) + kWave - 1) / kWave;
   dim3 block(kWave * (waves < 4 ? waves : 4));
-  const size_t lds = ((crop_lds_bytes(a) + 15) & ~(size_t)15) +
-                     (size_t)(block.x / kWave) * kStripFloats * sizeof(float);
-  const int aug = a.aug_mode == 1 ? 1 : (pass == 0 ? 2 : 3);
+  const size_t tables = (crop_lds_bytes(a) + 15) & ~(size_t)15;
+  const size_t strips = (size_t)(block.x / kWave) * kStripFloats * sizeof(float);
   // four pixels per lane when they tile a patch row, else two (even patch sizes)
-#define MAE_AUG_LAUNCH(BF, AUG)                                                          \
+#define MAE_AUG_LAUNCH(BF, AUG, LDS)                                                     \
   do {                                                                                   \
     if ((a.p & 3) == 0)                                                                  \
-      hipLaunchKernelGGL((crop_aug_kernel<BF, AUG, 4>), grid, block, lds, stream, a);    \
+      hipLaunchKernelGGL((crop_aug_kernel<BF, AUG, 4>), grid, block, LDS, stream, a);    \
     else                                                                                 \
-      hipLaunchKernelGGL((crop_aug_kernel<BF, AUG, 2>), grid, block, lds, stream, a);    \
+      hipLaunchKernelGGL((crop_aug_kernel<BF, AUG, 2>), grid, block, LDS, stream, a);    \
   } while (0)
-  if (a.visible_bf16) {
-    if (aug == 1) MAE_AUG_LAUNCH(true, 1);
-    else if (aug == 2) MAE_AUG_LAUNCH(true, 2);
-    else MAE_AUG_LAUNCH(true, 3);
-  } else {
-    if (aug == 1) MAE_AUG_LAUNCH(false, 1);
-    else if (aug == 2) MAE_AUG_LAUNCH(false, 2);
-    else MAE_AUG_LAUNCH(false, 3);
-  }
+  // ("3 Aug+" writes bytes only, whatever the type of `visible`)
+  if (a.aug_mode != 1) MAE_AUG_LAUNCH(false, 2, tables);
+  else if (a.visible_bf16) MAE_AUG_LAUNCH(true, 1, tables + strips);
+  else MAE_AUG_LAUNCH(false, 1, tables + strips);
 #undef MAE_AUG_LAUNCH
   return hipGetLastError();
 }

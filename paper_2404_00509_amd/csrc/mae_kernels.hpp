@@ -47,7 +47,7 @@ struct CropArgs {
   const uint8_t* workspace;
   void* visible;
   float* target;    // nullable
-  uint8_t* u8_out;  // the rounded 8-bit patch rows [B, L, D] of the images that the blur kernel takes
+  uint8_t* u8_out;  // 8-bit patch rows [B, L, D]: the blur images' and, with "3 Aug+", all others'
   // finetuning augmentation as this kernel's epilogue (launch_crop_aug): grayscale and
   // solarisation are applied to the rounded value in registers, blur images go to u8_out
   int32_t aug_mode;       // 1: "3 Aug", 2: "3 Aug+"
@@ -83,10 +83,10 @@ struct CropPlan {
 CropPlan crop_plan(int S, int p, int max_side, int force_parts);
 size_t crop_lds_bytes(const CropArgs& a);
 hipError_t launch_crop_patch(const CropArgs& a, hipStream_t stream);
-// The same with the finetuning augmentation's pointwise operations as the epilogue.  pass 0: the
-// only pass of "3 Aug" / the first pass of "3 Aug+" (luma sums, nothing stored but the 8-bit rows
-// of blur images); pass 1: the second pass of "3 Aug+".
-hipError_t launch_crop_aug(const CropArgs& a, int pass, hipStream_t stream);
+// The same with the finetuning augmentation's pointwise operations as the epilogue: "3 Aug" writes
+// the outputs of the images that did not draw the blur; "3 Aug+" writes all images' bytes and the
+// luma sums (launch_aug_jitter goes on from there).
+hipError_t launch_crop_aug(const CropArgs& a, hipStream_t stream);
 int64_t crop_loss_partials(const CropArgs& a);  // doubles of workspace
 // the loss kernel, then the sum of its partials in a fixed order -> a.loss_out
 hipError_t launch_crop_loss(const CropArgs& a, hipStream_t stream);
@@ -103,11 +103,14 @@ struct AugArgs {
   float nbias[3];
   int32_t blur_parts;         // column parts a row of patches is split into by the blur kernel
   int32_t blur_part_patches;  // patches per part (upper bound)
-  const uint8_t* u8;          // [B, L, D] bytes: the rounded resized crop in patch order
+  const uint8_t* u8;          // [B, L, D] bytes: the rounded resized crop in patch order, with
+                              // grayscale / solarisation applied
   const int32_t* ids_restore;
   const uint8_t* workspace;  // header + CropRec[B] (valid flags)
   const void* aug_recs;      // AugParams[B], written by the parameter kernel
   double* partials;          // [B * G * blur_parts] luma sums of the blur images, mode 2
+  const double* luma_partials;  // [B * luma_slots] of the other images, from the resampling kernel
+  int32_t luma_slots;
   void* visible;
   float* target;  // nullable
 };
@@ -118,6 +121,8 @@ struct AugPlan {
 AugPlan three_aug_plan(int S, int p);
 // The blur images of a batch.  reduce: only their luma sums after the brightness step ("3 Aug+").
 hipError_t launch_aug_blur(const AugArgs& a, bool reduce, hipStream_t stream);
+// "3 Aug+": colour jitter, normalisation and the outputs of the images without the blur.
+hipError_t launch_aug_jitter(const AugArgs& a, hipStream_t stream);
 
 // ---- crop decode of baseline JPEG files ----------------------------------------------------------
 struct JpegRec {

@@ -203,3 +203,26 @@ def test_full_size_batch_every_image(mode):
         gray = px[ops == oracle.OP_GRAY]
         assert (gray - gray[..., :1]).abs().max().item() < 1e-5
         assert px[ops == oracle.OP_SOLARISE].max().item() <= 127 / 255 + 1e-5
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("S,p", [(16, 16), (88, 8), (96, 16), (98, 14)])
+def test_three_aug_plus_without_a_target(S, p, bf16):
+    """Tokens only, as finetuning asks for them: one patch, just under and just over the pixels that
+    a workgroup of the jitter kernel takes, and patches that its steps straddle."""
+    B = 9
+    L = (S // p) ** 2
+    data = synth.make_images("uniform", B, seed=55)
+    kw = dict(out_size=S, patch=p, num_keep=L, seed=12, batch_index=1,
+              aug_mode=mae.MAE_AUG_THREE_PLUS, jitter=0.3)
+    ref = oracle.prep_batch(*data, **kw)
+    dev = [torch.from_numpy(a).cuda() for a in data]
+    desc = mae.make_prep_desc(*dev, out_dtype=mae.MAE_BF16 if bf16 else mae.MAE_F32, **kw)
+    buf = mae.alloc_prep_buffers(desc, want_target=False)
+    buf.visible.fill_(float("nan"))
+    mae.mae_prep_batch(desc, buf.visible, buf.mask, buf.ids_restore, buf.ids_keep, None, buf.crop,
+                       buf.workspace)
+    got = buf.visible.float().cpu().numpy().astype(np.float64)
+    want = ref["visible"].astype(np.float64)
+    # the path's fp32 tolerance, and half a unit in the last place of bf16
+    assert np.all(np.abs(got - want) <= ATOL + (BF16_RTOL if bf16 else RTOL) * np.abs(want))
