@@ -32,7 +32,6 @@
 
 namespace mae {
 
-constexpr int kCropThreads = 256;      // scalar kernel
 constexpr int kCropMaxThreads = 1024;  // resampling kernel: 64 threads per 64 groups of a patch
 constexpr int kStageRows = 7;  // rows per wavefront whose loads are issued together
 constexpr int kCropMaxLds = 64 * 1024;      // dynamic LDS available without opting in to more
@@ -214,6 +213,61 @@ __device__ static void produce_patches(const CropArgs& a, const uint32_t* tile, 
           f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(a.visible) + vo);
           *dst = f32x4{out[0], out[1], out[2], out[3]};
         }
+      }
+    }
+  }
+}
+
+// The same for odd patch sizes, whose patches are no whole number of 16-byte groups: a lane owns one
+// pixel of every patch of the part, and its three values leave with one 12-byte store (4-byte
+// aligned), so a store instruction covers 768 contiguous bytes.  The set-up per position, the staged
+// tile and the absence of global reads in the loop are those of produce_patches; the 225 pixels of
+// p = 15 fill 88 % of four wavefronts.  333 images of 225 pixels, p = 15: 50 us (one pixel per thread
+// with its taps from global memory, worked out for each pixel: 190 us).
+typedef float f32x3 __attribute__((ext_vector_type(3)));
+typedef f32x3 f32x3_a4 __attribute__((aligned(4)));
+template <bool kLds, bool kBf16>
+__device__ static void produce_pixels(const CropArgs& a, const uint32_t* tile, const u32x2* xtab,
+                                      const u32x4* ytab, const uint8_t* base, int b, int gy, int gx0,
+                                      int npatch, int cw, int my_rank) {
+  const int p = a.p, D = a.D, pp = p * p;
+  const bool active = (int)threadIdx.x < pp;
+  const int q = active ? (int)threadIdx.x : 0;
+  const int py = (int)(((float)q + 0.5f) * (1.0f / (float)p));
+  const int px = q - py * p;
+  const u32x4 yt = ytab[py];
+  const float fy = __uint_as_float(yt.z);
+  for (int gx = 0; gx < npatch; ++gx) {
+    const int rank = __builtin_amdgcn_readlane(my_rank, gx);
+    if (!a.target && rank >= a.K) continue;
+    const u32x2 xt = xtab[gx * p + px];
+    const float fx = __uint_as_float(xt.y);
+    uint32_t w00, w01, w10, w11;
+    fetch2<kLds>(tile, base, yt.x, (int)xt.x, cw, w00, w01);
+    fetch2<kLds>(tile, base, yt.y, (int)xt.x, cw, w10, w11);
+    f32x3 out;
+#define MAE_BLEND(C)                                                          \
+{                                                                             \
+  const float a00 = byte_to_float<C>(w00), a01 = byte_to_float<C>(w01);       \
+  const float a10 = byte_to_float<C>(w10), a11 = byte_to_float<C>(w11);       \
+  const float rt = a00 + fx * (a01 - a00);                                    \
+  const float rb = a10 + fx * (a11 - a10);                                    \
+  out[C] = (rt + fy * (rb - rt)) * a.nscale[C] + a.nbias[C];                  \
+}
+    MAE_BLEND(0) MAE_BLEND(1) MAE_BLEND(2)
+#undef MAE_BLEND
+    if (!active) continue;
+    if (a.target)
+      *reinterpret_cast<f32x3_a4*>(a.target + ((int64_t)b * a.L + gy * a.G + gx0 + gx) * D + 3 * q) =
+          out;
+    if (rank < a.K) {
+      const int64_t vo = ((int64_t)b * a.K + rank) * D + 3 * q;
+      if (kBf16) {
+        uint16_t* dst = static_cast<uint16_t*>(a.visible) + vo;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) dst[c] = (uint16_t)bf16_rne(out[c]);
+      } else {
+        *reinterpret_cast<f32x3_a4*>(static_cast<float*>(a.visible) + vo) = out;
       }
     }
   }
@@ -834,7 +888,18 @@ __device__ static void neutral_outputs(const CropArgs& a, int b, int gy, int gx0
   const int D4 = a.D >> 2;
   const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
   const int l0 = gy * a.G + gx0;
-  for (int i = threadIdx.x; i < npatch * D4; i += (int)blockDim.x) {
+  if (a.D & 3) {  // odd patch sizes: value by value
+    for (int i = threadIdx.x; i < npatch * a.D; i += (int)blockDim.x) {
+      const int gx = i / a.D, e = i - gx * a.D;
+      const int l = l0 + gx;
+      if (a.target) a.target[((int64_t)b * a.L + l) * a.D + e] = 0.0f;
+      if (l >= a.K || !a.visible) continue;
+      const int64_t vo = ((int64_t)b * a.K + l) * a.D + e;
+      if (a.visible_bf16) static_cast<uint16_t*>(a.visible)[vo] = 0;
+      else static_cast<float*>(a.visible)[vo] = 0.0f;
+    }
+  }
+  for (int i = threadIdx.x; (a.D & 3) == 0 && i < npatch * D4; i += (int)blockDim.x) {
     const int gx = i / D4, e = 4 * (i - gx * D4);
     const int l = l0 + gx;
     if (a.target) *reinterpret_cast<f32x4*>(a.target + ((int64_t)b * a.L + l) * a.D + e) = zero;
@@ -859,14 +924,14 @@ __device__ static void neutral_outputs(const CropArgs& a, int b, int gy, int gx0
 // Dynamic LDS: [ tile: a.tile_pixels + 4 words | ytab: p x 16 bytes | xtab: a.part_patches p x 8 ].
 // kLossMode 1, 2: instead of writing the patches, the loss and its gradient against a.pred
 // (1: produce_loss, any patch size; 2: produce_loss_wave, patches of up to 768 values).
-// kLossMode -1: the visible tokens only (no target).
+// kLossMode -1: the visible tokens only (no target).  -2: a pixel per lane (odd patch sizes).
 // kAug: the finetuning augmentation as the epilogue (produce_aug): 1 = "3 Aug", 2 = "3 Aug+" up to
 // the colour jitter.
 // kAugPx: pixels per lane of that epilogue (4 when p is a multiple of 4, else 2).
 template <bool kBf16, int kLossMode, int kAug = 0, int kAugPx = 4>
 __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
   constexpr bool kLoss = kLossMode > 0;
-  constexpr bool kKeptOnly = kLossMode < 0;
+  constexpr bool kKeptOnly = kLossMode == -1;
   uint32_t* tile = lds;
   u32x4* ytab = reinterpret_cast<u32x4*>(lds + a.tile_pixels + 4);  // row y0, row y1, weight
   u32x2* xtab = reinterpret_cast<u32x2*>(ytab + a.p);                // x0, weight of x0 + 1
@@ -1036,6 +1101,11 @@ __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
       produce_loss<false>(a, tile, xtab, ytab, base, b, gy, gx0, npatch, rec.cw - xlo, my_rank,
                           red, red64, tile_id);
     }
+  } else if constexpr (kLossMode == -2) {
+    if (use_lds)
+      produce_pixels<true, kBf16>(a, tile, xtab, ytab, base, b, gy, gx0, npatch, rec.cw - xlo, my_rank);
+    else
+      produce_pixels<false, kBf16>(a, tile, xtab, ytab, base, b, gy, gx0, npatch, rec.cw - xlo, my_rank);
   } else if (use_lds) {
     produce_patches<true, kBf16, kKeptOnly>(a, tile, xtab, ytab, base, b, gy, gx0, npatch,
                                                  rec.cw - xlo, my_rank);
@@ -1076,68 +1146,11 @@ __global__ __launch_bounds__(4 * kWave) void crop_loss_wave_kernel(CropArgs a) {
   crop_band<false, 2>(a, lds);
 }
 
-// Patch sizes whose 3 p^2 values per patch are not a multiple of four (odd p): one output pixel
-// per thread, taps straight from global memory.  Correct for every shape, not tuned further.
+// ... for odd patch sizes, with or without a target: 64 threads per 64 pixels of a patch
 template <bool kBf16>
-__global__ __launch_bounds__(kCropThreads) void crop_patch_scalar_kernel(CropArgs a) {
-  // one output pixel (three values) per thread and pass: the taps are worked out once per pixel
-  const int pp = a.p * a.p;
-  const int64_t per_image = (int64_t)a.L * pp;
-  const int64_t total = (int64_t)a.B * per_image;
-  const float inv_den = 1.0f / (float)(2 * a.S);
-  for (int64_t idx = (int64_t)blockIdx.x * kCropThreads + threadIdx.x; idx < total;
-       idx += (int64_t)gridDim.x * kCropThreads) {
-    const int b = (int)(idx / per_image);
-    const int rem = (int)(idx - (int64_t)b * per_image);
-    const CropRec rec = reinterpret_cast<const CropRec*>(a.workspace + kWorkspaceHeader)[b];
-    const int l = rem / pp, q = rem - l * pp;
-    const int64_t to = ((int64_t)b * a.L + l) * a.D + 3 * q;  // the pixel's values in `target`
-    if (!rec.valid) {  // takes no part: zero pixels, nothing masked, identity order
-      const int64_t vo = ((int64_t)b * a.K + l) * a.D + 3 * q;
-      for (int c = 0; c < 3; ++c) {
-        if (a.target) a.target[to + c] = 0.0f;
-        if (l < a.K) {
-          if (kBf16) static_cast<uint16_t*>(a.visible)[vo + c] = 0;
-          else static_cast<float*>(a.visible)[vo + c] = 0.0f;
-        }
-      }
-      if (q == 0) {
-        if (a.mask_out) a.mask_out[(int64_t)b * a.L + l] = 0;
-        if (a.order_out) a.order_out[(int64_t)b * a.L + l] = l;
-        if (a.keep_out && l < a.K) a.keep_out[(int64_t)b * a.K + l] = l;
-        if (a.crop_out && l == 0)
-          for (int i = 0; i < 6; ++i) a.crop_out[(int64_t)b * 6 + i] = 0;
-      }
-      continue;
-    }
-    const int gy = l / a.G, gx = l - gy * a.G;
-    const int py = q / a.p, px = q - py * a.p;
-    const int oy = gy * a.p + py, ox = gx * a.p + px;
-    int x0, x1, y0, y1;
-    float fx, fy;
-    resize_taps(rec.flip ? a.S - 1 - ox : ox, rec.cw, a.S, inv_den, x0, x1, fx);
-    resize_taps(oy, rec.ch, a.S, inv_den, y0, y1, fy);
-    const int W = a.widths[b];
-    const uint8_t* img = a.images + a.offsets[b];
-    const uint8_t* p00 = img + ((int64_t)(rec.top + y0) * W + rec.left + x0) * 3;
-    const uint8_t* p01 = img + ((int64_t)(rec.top + y0) * W + rec.left + x1) * 3;
-    const uint8_t* p10 = img + ((int64_t)(rec.top + y1) * W + rec.left + x0) * 3;
-    const uint8_t* p11 = img + ((int64_t)(rec.top + y1) * W + rec.left + x1) * 3;
-    const int rank = a.ids_restore[(int64_t)b * a.L + l];
-    const int64_t vo = ((int64_t)b * a.K + rank) * a.D + 3 * q;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const float a00 = p00[c], a01 = p01[c], a10 = p10[c], a11 = p11[c];
-      const float rt = a00 + fx * (a01 - a00);
-      const float rb = a10 + fx * (a11 - a10);
-      const float v = (rt + fy * (rb - rt)) * a.nscale[c] + a.nbias[c];
-      if (a.target) a.target[to + c] = v;
-      if (rank < a.K) {
-        if (kBf16) static_cast<uint16_t*>(a.visible)[vo + c] = (uint16_t)bf16_rne(v);
-        else static_cast<float*>(a.visible)[vo + c] = v;
-      }
-    }
-  }
+__global__ __launch_bounds__(kCropMaxThreads) void crop_pixel_kernel(CropArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+  crop_band<kBf16, -2>(a, lds);
 }
 
 // Launch plan of the resampling kernel when no image side exceeds max_side.  A row of patches
@@ -1258,15 +1271,13 @@ hipError_t launch_crop_patch(const CropArgs& a, hipStream_t stream) {
       hipLaunchKernelGGL(crop_patch_kernel<false>, grid, block, lds, stream, a);
     }
   } else {
-    const int64_t total = (int64_t)a.B * a.L * a.p * a.p;  // output pixels
-    int64_t blocks = (total + kCropThreads - 1) / kCropThreads;
-    if (blocks > 256 * 64) blocks = 256 * 64;
-    dim3 grid((uint32_t)blocks), block(kCropThreads);
-    if (a.visible_bf16) {
-      hipLaunchKernelGGL(crop_patch_scalar_kernel<true>, grid, block, 0, stream, a);
-    } else {
-      hipLaunchKernelGGL(crop_patch_scalar_kernel<false>, grid, block, 0, stream, a);
-    }
+    dim3 grid((uint32_t)a.B * (uint32_t)a.G * (uint32_t)a.col_parts);
+    dim3 block(kWave * ((a.p * a.p + kWave - 1) / kWave));
+    const size_t lds = crop_lds_bytes(a);
+    if (a.visible_bf16)
+      hipLaunchKernelGGL(crop_pixel_kernel<true>, grid, block, lds, stream, a);
+    else
+      hipLaunchKernelGGL(crop_pixel_kernel<false>, grid, block, lds, stream, a);
   }
   return hipGetLastError();
 }

@@ -34,19 +34,59 @@ __device__ static inline double wave_sum(double v) {
   return v;
 }
 
+// Rows whose length is no multiple of four values (odd patch sizes) start at any multiple of the
+// value's size; their whole groups are moved with the same wide accesses, less aligned.
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
+// The last n = 1..3 values of such a row, zeros behind them.
 template <bool kBf16>
-__device__ static inline f32x4 load_pred4(const void* pred, int64_t elem) {
-  if (kBf16) {
-    const u32x2 raw = __builtin_nontemporal_load(
-        reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(pred) + elem));
-    return f32x4{bf16_lo(raw.x), bf16_hi(raw.x), bf16_lo(raw.y), bf16_hi(raw.y)};
+__device__ static inline f32x4 load_rest(const void* p, int64_t elem, int n) {
+  f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    if (j >= n) break;
+    v[j] = kBf16 ? __uint_as_float((uint32_t)static_cast<const uint16_t*>(p)[elem + j] << 16)
+                 : static_cast<const float*>(p)[elem + j];
   }
-  return __builtin_nontemporal_load(
-      reinterpret_cast<const f32x4*>(static_cast<const float*>(pred) + elem));
+  return v;
 }
 
-template <bool kBf16>
-__device__ static inline void store_grad4(void* grad, int64_t elem, f32x4 g) {
+template <bool kBf16, bool kRagged = false>
+__device__ static inline f32x4 load_pred4(const void* pred, int64_t elem) {
+  if (kBf16) {
+    const uint16_t* p16 = static_cast<const uint16_t*>(pred) + elem;
+    const u32x2 raw = kRagged
+                          ? u32x2(__builtin_nontemporal_load(reinterpret_cast<const u32x2_a2*>(p16)))
+                          : __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p16));
+    return f32x4{bf16_lo(raw.x), bf16_hi(raw.x), bf16_lo(raw.y), bf16_hi(raw.y)};
+  }
+  const float* p32 = static_cast<const float*>(pred) + elem;
+  return kRagged ? f32x4(__builtin_nontemporal_load(reinterpret_cast<const f32x4_a4*>(p32)))
+                 : __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p32));
+}
+
+// kRagged: the first n values only when n < 4.
+template <bool kBf16, bool kRagged = false>
+__device__ static inline void store_grad4(void* grad, int64_t elem, f32x4 g, int n = 4) {
+  if (kRagged) {
+    if (n >= 4) {
+      if (kBf16)
+        __builtin_nontemporal_store(
+            u32x2_a2{pack_bf16x2(g.x, g.y), pack_bf16x2(g.z, g.w)},
+            reinterpret_cast<u32x2_a2*>(static_cast<uint16_t*>(grad) + elem));
+      else
+        __builtin_nontemporal_store(f32x4_a4(g),
+                                    reinterpret_cast<f32x4_a4*>(static_cast<float*>(grad) + elem));
+      return;
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      if (j >= n) break;
+      if (kBf16) static_cast<uint16_t*>(grad)[elem + j] = (uint16_t)bf16_rne(g[j]);
+      else static_cast<float*>(grad)[elem + j] = g[j];
+    }
+    return;
+  }
   if (kBf16) {
     __builtin_nontemporal_store(u32x2{pack_bf16x2(g.x, g.y), pack_bf16x2(g.z, g.w)},
                                 reinterpret_cast<u32x2*>(static_cast<uint16_t*>(grad) + elem));
@@ -56,14 +96,18 @@ __device__ static inline void store_grad4(void* grad, int64_t elem, f32x4 g) {
 }
 
 // NV = 16-byte groups per lane; D / 4 <= 64 NV.
+// kRagged: D is no multiple of four; the row's last group has D % 4 values, the lane that holds it
+// moves them one by one, and what is behind them stays zero.  333 x 225 rows of 675 values in fp32:
+// 100 us (value by value with three passes over the row: 242 us).
 // kNorm: per-patch normalised target (the recipe's objective); otherwise the target as it is.
 // kRowsPerIter: adjacent rows a wavefront handles per pass.
-template <int NV, int kRowsPerIter, bool kBf16, bool kNorm>
+template <int NV, int kRowsPerIter, bool kBf16, bool kNorm, bool kRagged = false>
 __global__ __launch_bounds__(kLossThreads) void normpix_loss_kernel(LossArgs a) {
   const int lane = threadIdx.x % kWave;
   const int wave_in_grid = blockIdx.x * kLossWaves + threadIdx.x / kWave;
   const int waves = gridDim.x * kLossWaves;
-  const int D = a.D, D4 = a.D >> 2;
+  const int D = a.D, D4 = kRagged ? (a.D + 3) >> 2 : a.D >> 2;  // groups
+  const int whole = a.D >> 2, rest = a.D & 3;                      // (kRagged)
   const float inv_d = 1.0f / (float)D;
   const float inv_dm1 = 1.0f / (float)(D - 1);
   double acc = 0.0;
@@ -87,9 +131,13 @@ __global__ __launch_bounds__(kLossThreads) void normpix_loss_kernel(LossArgs a) 
         t[u][v] = f32x4{0.f, 0.f, 0.f, 0.f};
         q[u][v] = t[u][v];
         if (masked[u] && g < D4) {
-          t[u][v] = __builtin_nontemporal_load(
-              reinterpret_cast<const f32x4*>(a.target + row_elem + 4 * g));
-          q[u][v] = load_pred4<kBf16>(a.pred, row_elem + 4 * g);
+          if (kRagged && g == whole) {
+            t[u][v] = load_rest<false>(a.target, row_elem + 4 * g, rest);
+            q[u][v] = load_rest<kBf16>(a.pred, row_elem + 4 * g, rest);
+          } else {
+            t[u][v] = load_pred4<false, kRagged>(a.target, row_elem + 4 * g);
+            q[u][v] = load_pred4<kBf16, kRagged>(a.pred, row_elem + 4 * g);
+          }
         }
       }
     }
@@ -103,7 +151,9 @@ __global__ __launch_bounds__(kLossThreads) void normpix_loss_kernel(LossArgs a) 
 #pragma unroll
           for (int v = 0; v < NV; ++v) {
             const int g = lane + v * kWave;
-            if (g < D4) store_grad4<kBf16>(a.grad, row_elem + 4 * g, f32x4{0.f, 0.f, 0.f, 0.f});
+            if (g < D4)
+              store_grad4<kBf16, kRagged>(a.grad, row_elem + 4 * g, f32x4{0.f, 0.f, 0.f, 0.f},
+                                          g == whole ? rest : 4);
           }
         }
         continue;
@@ -119,6 +169,10 @@ __global__ __launch_bounds__(kLossThreads) void normpix_loss_kernel(LossArgs a) 
         for (int v = 0; v < NV; ++v) {
           const int g = lane + v * kWave;
           t[u][v] = t[u][v] - mu;
+          if (kRagged && g == whole) {
+#pragma unroll
+            for (int j = 1; j < 4; ++j) t[u][v][j] = j < rest ? t[u][v][j] : 0.f;
+          }
           if (g < D4)
             ss += (t[u][v].x * t[u][v].x + t[u][v].y * t[u][v].y) +
                   (t[u][v].z * t[u][v].z + t[u][v].w * t[u][v].w);
@@ -133,7 +187,8 @@ __global__ __launch_bounds__(kLossThreads) void normpix_loss_kernel(LossArgs a) 
         const f32x4 diff = kNorm ? q[u][v] - t[u][v] * rstd : q[u][v] - t[u][v];
         if (g < D4) {
           sq += (diff.x * diff.x + diff.y * diff.y) + (diff.z * diff.z + diff.w * diff.w);
-          if (a.grad) store_grad4<kBf16>(a.grad, row_elem + 4 * g, diff * gscale);
+          if (a.grad)
+            store_grad4<kBf16, kRagged>(a.grad, row_elem + 4 * g, diff * gscale, g == whole ? rest : 4);
         }
       }
       acc += (double)sq;
@@ -221,56 +276,6 @@ __global__ __launch_bounds__(kLossThreads) void normpix_loss_pair_kernel(LossArg
   if (lane == 0) a.partials[wave_in_grid] = acc;
 }
 
-// Any D (not a multiple of four, or too long for registers): three passes over the row.
-template <bool kBf16, bool kNorm>
-__global__ __launch_bounds__(kLossThreads) void normpix_loss_scalar_kernel(LossArgs a) {
-  const int lane = threadIdx.x % kWave;
-  const int wave_in_grid = blockIdx.x * kLossWaves + threadIdx.x / kWave;
-  const int waves = gridDim.x * kLossWaves;
-  const int D = a.D;
-  double acc = 0.0;
-  const float gscale =
-      a.counts ? (float)(a.gscale_num * inv_count_of(D, sum_counts(a.counts, a.ncounts))) : a.gscale;
-  for (int64_t row = wave_in_grid; row < a.rows; row += waves) {
-    const int64_t row_elem = row * D;
-    const float* t = a.target + row_elem;
-    if (a.mask[row] == 0) {
-      if (a.grad) {
-        for (int e = lane; e < D; e += kWave) {
-          if (kBf16) static_cast<uint16_t*>(a.grad)[row_elem + e] = 0;
-          else static_cast<float*>(a.grad)[row_elem + e] = 0.f;
-        }
-      }
-      continue;
-    }
-    float mu = 0.f, rstd = 1.0f;
-    if (kNorm) {
-      float s = 0.f;
-      for (int e = lane; e < D; e += kWave) s += t[e];
-      mu = wave_sum(s) / (float)D;
-      float ss = 0.f;
-      for (int e = lane; e < D; e += kWave) ss += (t[e] - mu) * (t[e] - mu);
-      const float var = wave_sum(ss) / (float)(D - 1);
-      rstd = 1.0f / sqrtf(var + a.eps);
-    }
-    float sq = 0.f;
-    for (int e = lane; e < D; e += kWave) {
-      float q;
-      if (kBf16) q = __uint_as_float((uint32_t)static_cast<const uint16_t*>(a.pred)[row_elem + e] << 16);
-      else q = static_cast<const float*>(a.pred)[row_elem + e];
-      const float diff = kNorm ? q - (t[e] - mu) * rstd : q - t[e];
-      sq += diff * diff;
-      if (a.grad) {
-        if (kBf16) static_cast<uint16_t*>(a.grad)[row_elem + e] = (uint16_t)bf16_rne(diff * gscale);
-        else static_cast<float*>(a.grad)[row_elem + e] = diff * gscale;
-      }
-    }
-    acc += (double)sq;
-  }
-  acc = wave_sum(acc);
-  if (lane == 0) a.partials[wave_in_grid] = acc;
-}
-
 // Adds the per-wavefront partials in a fixed order: thread i takes partials i, i + 256, ...,
 // then a tree over the 256 threads.
 __global__ __launch_bounds__(kLossThreads) void loss_finish_kernel(const double* partials, int n,
@@ -308,7 +313,7 @@ LossShape loss_shape(int64_t rows, int D, bool pred_bf16) {
   LossShape sh;
   const int nv = ((D >> 2) + kWave - 1) / kWave;
   const int64_t load_bytes = (int64_t)D * (pred_bf16 ? 6 : 8);
-  const bool vec = (D & 3) == 0 && (D >> 2) <= 12 * kWave;
+  const bool vec = (D & 3) == 0;  // others go one row per pass
   sh.rows_per_iter = (vec && nv <= 4 && load_bytes >= 6144) ? 2 : 1;
   // rows as pairs in one run of groups: when that saves a load and a store instruction per pair
   sh.pair_groups = (vec && sh.rows_per_iter == 1) ? pair_groups(D) : 0;
@@ -327,7 +332,7 @@ LossShape loss_shape(int64_t rows, int D, bool pred_bf16) {
 
 template <bool kBf16, bool kNorm>
 static void launch_vec(const LossArgs& a, dim3 grid, dim3 block, hipStream_t stream) {
-  const int nv = ((a.D >> 2) + kWave - 1) / kWave;
+  const int nv = (((a.D + 3) >> 2) + kWave - 1) / kWave;
   const int nvf = a.pair_groups;
   if (nvf != 0) {
 #define MAE_LAUNCH_PAIR(NVF) \
@@ -339,6 +344,19 @@ static void launch_vec(const LossArgs& a, dim3 grid, dim3 block, hipStream_t str
     else if (nvf == 5) MAE_LAUNCH_PAIR(5);
     else MAE_LAUNCH_PAIR(6);
 #undef MAE_LAUNCH_PAIR
+    return;
+  }
+  if (a.D & 3) {
+#define MAE_LAUNCH_RAGGED(NV) \
+  hipLaunchKernelGGL((normpix_loss_kernel<NV, 1, kBf16, kNorm, true>), grid, block, 0, stream, a)
+    if (nv <= 1) MAE_LAUNCH_RAGGED(1);
+    else if (nv <= 2) MAE_LAUNCH_RAGGED(2);
+    else if (nv <= 3) MAE_LAUNCH_RAGGED(3);
+    else if (nv <= 4) MAE_LAUNCH_RAGGED(4);
+    else if (nv <= 6) MAE_LAUNCH_RAGGED(6);
+    else if (nv <= 8) MAE_LAUNCH_RAGGED(8);
+    else MAE_LAUNCH_RAGGED(12);
+#undef MAE_LAUNCH_RAGGED
     return;
   }
 #define MAE_LAUNCH(NV, RPI) \
@@ -358,16 +376,6 @@ static void launch_vec(const LossArgs& a, dim3 grid, dim3 block, hipStream_t str
     else MAE_LAUNCH(12, 1);
   }
 #undef MAE_LAUNCH
-}
-
-template <bool kBf16, bool kNorm>
-static void launch_any(const LossArgs& a, dim3 grid, dim3 block, hipStream_t stream) {
-  const bool vec = (a.D & 3) == 0 && (a.D >> 2) <= 12 * kWave;
-  if (vec) {
-    launch_vec<kBf16, kNorm>(a, grid, block, stream);
-  } else {
-    hipLaunchKernelGGL((normpix_loss_scalar_kernel<kBf16, kNorm>), grid, block, 0, stream, a);
-  }
 }
 
 hipError_t launch_loss_finish(const double* partials, int n, double inv_count, float* loss,
@@ -411,11 +419,11 @@ hipError_t launch_mask_count(const uint8_t* mask, int64_t rows, int32_t* counts,
 hipError_t launch_normpix_loss(const LossArgs& a, hipStream_t stream) {
   dim3 grid(a.num_partials / kLossWaves), block(kLossThreads);
   if (a.pred_bf16) {
-    if (a.norm_pix) launch_any<true, true>(a, grid, block, stream);
-    else launch_any<true, false>(a, grid, block, stream);
+    if (a.norm_pix) launch_vec<true, true>(a, grid, block, stream);
+    else launch_vec<true, false>(a, grid, block, stream);
   } else {
-    if (a.norm_pix) launch_any<false, true>(a, grid, block, stream);
-    else launch_any<false, false>(a, grid, block, stream);
+    if (a.norm_pix) launch_vec<false, true>(a, grid, block, stream);
+    else launch_vec<false, false>(a, grid, block, stream);
   }
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;

@@ -172,6 +172,31 @@ def test_prep_shapes_and_tiny_or_large_images(S, p, K):
         check_prep_against_oracle(prep_to_numpy(big), ref, what=f"S{S}p{p}hint{hint}")
 
 
+@pytest.mark.parametrize("S,p,K", [(16, 1, 64), (27, 3, 20), (72, 9, 64), (62, 31, 3), (225, 15, 45)])
+@pytest.mark.parametrize("want_target", [True, False])
+def test_prep_odd_patch_sizes(S, p, K, want_target):
+    """A pixel per lane: patches of one pixel, of just over one wavefront (81), of 961 pixels; staged,
+    split into column parts and from global memory; with and without a target."""
+    shapes = [(1, 1), (5, 300), (130, 97), (256, 200), (431, 613), (90, 1100)]
+    data = _pack(_random_images(shapes, seed=S + p))
+    kw = dict(out_size=S, patch=p, num_keep=K, seed=9, batch_index=2)
+    ref = oracle.prep_batch(*data, **kw)
+    dev = to_device(*data)
+    for bf16, hint in ((False, 256), (True, 256), (False, 700)):
+        desc = mae.make_prep_desc(*dev, max_image_side=hint,
+                                  out_dtype=mae.MAE_BF16 if bf16 else mae.MAE_F32, **kw)
+        buf = mae.alloc_prep_buffers(desc, want_target=want_target)
+        buf.visible.fill_(float("nan"))
+        if want_target:
+            buf.target.fill_(float("nan"))
+        mae.mae_prep_batch(desc, buf.visible, buf.mask, buf.ids_restore, buf.ids_keep, buf.target,
+                           buf.crop, buf.workspace)
+        assert_close(buf.visible.float().cpu().numpy(), ref["visible"],
+                     rtol=BF16_RTOL if bf16 else RTOL, what=f"visible p{p} hint{hint}")
+        if want_target:
+            assert_close(buf.target.cpu().numpy(), ref["target"], what=f"target p{p} hint{hint}")
+
+
 def test_prep_single_image_and_keep_all():
     data = _pack(_random_images([(77, 91)]))
     for K in (1, 49):
@@ -380,7 +405,11 @@ def _loss_case(B, L, D, seed, mask_mode="random", bf16=False, grad_scale=1.0, ep
 
 @pytest.mark.parametrize("B,L,D", [(1, 1, 12), (3, 5, 768), (2, 49, 588), (5, 7, 256),
                                    (2, 3, 3072), (1, 9, 1024), (2, 4, 1536), (3, 3, 2048),
-                                   (2, 5, 147), (1, 6, 2), (2, 3, 2700), (7, 196, 768)])
+                                   (2, 5, 147), (1, 6, 2), (2, 3, 2700), (7, 196, 768),
+                                   # no multiple of four: one to three values in the last group, the
+                                   # last group alone in its lane's run, every count of groups
+                                   (3, 5, 3), (5, 9, 257), (3, 7, 675), (2, 3, 1023), (2, 3, 1025),
+                                   (2, 3, 1587), (2, 3, 2046), (1, 3, 2883), (2, 2, 3071)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_loss_shapes(B, L, D, bf16):
     _loss_case(B, L, D, seed=B * 1000 + L * 10 + D, bf16=bf16)
