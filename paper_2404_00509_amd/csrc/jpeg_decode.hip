@@ -24,16 +24,20 @@
 //    tables in LDS, decodes code lengths and DC differences only, handles restart markers where
 //    they come, and records the state of the bit reader and the DC predictors at the start of
 //    each of the crop's rows of MCUs.
-//  * jpeg_decode_kernel: one wavefront per group of four images, their tables copied into LDS;
-//    the rows of MCUs that the crops touch are dealt to the lanes, one row per lane.  A lane's
+//  * jpeg_entropy_kernel: one wavefront per group of up to four images, a lane per row of MCUs that
+//    a crop touches (or per piece of such a row where the parallel walk has found the pieces'
+//    states); the coefficients go to the plane buffer as 16-bit values.
+//  * jpeg_decode_kernel (what is left: restart intervals that end inside a row, crops whose
+//    coefficients do not fit the plane buffer): rows dealt to the lanes in the same way.  A lane's
 //    file bytes come through its column of a ring in LDS that is fed at the start of every
 //    block, where all lanes are at the same instruction; the bit buffer takes four bytes at a
 //    time unless one of them is 0xFF.  Per block: DC difference, AC symbols with one table
 //    look-up each (code and value bits out of the same 32-bit peek), de-quantisation on
 //    insertion, fixed-point separable inverse DCT in LDS, eight 8-byte stores into the image's
 //    Y, Cb or Cr plane.
-//  * jpeg_colour_kernel: planes -> interleaved RGB rows of the region (repeated chroma,
-//    fixed-point JFIF colour matrix), which is what the resampling kernel reads.
+//  * jpeg_idct_kernel: coefficients (inverse transform) or planes -> interleaved RGB rows of the
+//    region (repeated chroma, fixed-point JFIF colour matrix), which is what the resampling kernel
+//    reads.
 //
 // The integer arithmetic of the inverse DCT and of the colour conversion is part of the
 // definition of the output (a decoder is only specified up to that): 13-bit cosines, first pass
@@ -487,12 +491,18 @@ __device__ static inline uint32_t ycc_to_rgbx(int y, int cb, int cr) {
 // Images per workgroup of the decode kernel (template parameter kGroup: 4, 2 or 1): their rows of
 // MCUs share the 64 lanes.  A lane gets at most kGroup rows (an image has at most 64).
 
+constexpr int kBlockBytes = 128;  // a block of coefficients in the plane buffer
+constexpr int kLivePlanes = 1, kLiveCoefs = 2, kLivePieces = 3;  // 0: the sample takes no part
+
 // What the wavefront keeps per image of its group.
 struct JpegImage {
   HuffDc dc[2];  // luma, chroma
   HuffAc ac[2];
   uint16_t qz[2][64];  // per zig-zag position: natural position << 8 | quantiser step
-  int my0, mx0, mx1, nrows, region_w, hs, size, scan_off, live;
+  int my0, mx0, mx1, nrows, region_w, hs, size, scan_off;
+  // kLivePlanes: decoded to planes, kLiveCoefs: by jpeg_entropy_kernel to coefficients,
+  // kLivePieces: the same, and the states of pieces of its rows are known
+  int live;
   int restart, mcux;  // restart interval in MCUs (0 = none), MCUs per row of the image
   // bytes of entropy-coded data in the image's slot of the region buffer, byte stuffing removed
   // (see jpeg_unstuff); -1 = not there
@@ -527,7 +537,7 @@ struct JpegLds {
 };
 
 // A file's entropy-coded data without its byte stuffing lies in the image's slot of the region
-// buffer until the colour kernel writes the region there: the bytes at the start of the slot, and
+// buffer until jpeg_idct_kernel writes the region there: the bytes at the start of the slot, and
 // behind them (clean_map_offset) the file position of every 16th of them.  The slot's size does
 // not depend on the file's, so a file may be too large for it; such a file is walked by
 // jpeg_scan_kernel.
@@ -540,6 +550,24 @@ __device__ static inline bool clean_fits(const JpegArgs& a, int size, int scan_o
                                 (int64_t)a.slot_side * a.slot_side * 3;
 }
 constexpr int kCleanStep = kJpegThreads * 16;  // bytes of the file per step
+
+// The walk over a file that is one chain of codes can also tell where each of several pieces of the
+// crop's rows starts, so that a row is several lanes' work: as many pieces as fill a wavefront (four
+// at most), from the crop's first MCU on.  Their states lie at the end of the image's slot of the
+// region buffer until the region is written.
+constexpr int kMaxPieces = 4, kPieceBytes = kJpegThreads * 32;
+__device__ static inline int pieces_per_row(int nrows, int ncols) {
+  return max(1, min(min(kMaxPieces, kJpegThreads / max(nrows, 1)), ncols));
+}
+__device__ static inline RowState* piece_states(const JpegArgs& a, int64_t region_off) {
+  return reinterpret_cast<RowState*>(a.regions + region_off +
+                                     (int64_t)a.slot_side * a.slot_side * 3 - kPieceBytes);
+}
+__device__ static inline bool pieces_fit(const JpegArgs& a, int size, int scan_off, int nrows) {
+  const int64_t raw = (int64_t)size - scan_off;
+  return nrows <= kJpegThreads && clean_map_offset(size, scan_off) + 4 * (raw / 16 + 2) + kPieceBytes <=
+                                      (int64_t)a.slot_side * a.slot_side * 3;
+}
 
 // Entropy-coded data from scan_off to the first marker, byte stuffing removed, into `clean`, with
 // the file position of every 16th byte in `map`; returns how many bytes (whole wavefront).  The
@@ -673,6 +701,18 @@ __device__ static void jpeg_prepare_image(const JpegArgs& a, int b, JpegImage& i
   // rows and columns of MCUs that the crop touches
   const int my0 = cr.top / mcu, my1 = min((cr.top + cr.ch - 1) / mcu, rec.mcuy - 1);
   const int mx0 = cr.left / mcu, mx1 = min((cr.left + cr.cw - 1) / mcu, rec.mcux - 1);
+  // Blocks as 64 coefficients of 16 bits: the slot of the plane buffer (3 bytes per pixel) holds
+  // those of any crop with 4:2:0 sampling and of a crop of up to half the slot with 4:4:4.  A
+  // restart boundary may only fall between rows of MCUs.
+  const int64_t coef_bytes =
+      (int64_t)(my1 - my0 + 1) * (mx1 - mx0 + 1) * (rec.hs * rec.hs + 2) * kBlockBytes;
+  const bool dense = rec.restart % rec.mcux == 0 && !a.whole_image &&
+                     coef_bytes <= (int64_t)a.slot_side * a.slot_side * 3;
+  if (dense) {  // most coefficients are zero: only the others will be written
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4* coef = reinterpret_cast<u32x4*>(a.planes + a.region_offsets[b]);
+    for (int i = lane; i < (int)(coef_bytes / 16); i += kJpegThreads) coef[i] = u32x4{0u, 0u, 0u, 0u};
+  }
   if (lane == 0) {
     im.my0 = my0;
     im.mx0 = mx0;
@@ -685,10 +725,10 @@ __device__ static void jpeg_prepare_image(const JpegArgs& a, int b, JpegImage& i
     im.restart = rec.restart;
     im.mcux = rec.mcux;
     im.clean_bytes = -1;
-    im.live = 1;
+    im.live = dense ? kLiveCoefs : kLivePlanes;
     im.origin = a.offsets[b];
     im.region_off = a.region_offsets[b];
-    // region geometry for the colour kernel and the resampling kernel
+    // region geometry for jpeg_idct_kernel and the resampling kernel
     a.region_widths[b] = (mx1 - mx0 + 1) * mcu;
     a.recs[b].region_h = (my1 - my0 + 1) * mcu;
     crop->top = cr.top - my0 * mcu;
@@ -1140,8 +1180,8 @@ __device__ static __forceinline__ void clean_open(CleanReader& r, int bit) {
 __device__ static inline int clean_bit(const CleanReader& r) { return 32 * r.taken - 32 - r.left; }
 
 // What the wavefront does next: every lane walks its part (again), the zero bits behind data that
-// ends early are looked at, or the rows' starts are walked to.
-enum class SyncStage { kParts, kTail, kRows };
+// ends early are looked at, the rows' starts are walked to, then their pieces'.
+enum class SyncStage { kParts, kTail, kRows, kPieces };
 
 __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
   __shared__ JpegSyncLds s;
@@ -1152,6 +1192,7 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
   const int nblk = im->hs * im->hs, last_phase = nblk + 1, per_mcu = nblk + 2;
   const int my0 = im->my0, nrows = min(im->nrows, a.max_rows);
   const int row_blocks = im->mcux * per_mcu;
+  const int ncols = im->mx1 - im->mx0 + 1, sub = pieces_per_row(nrows, ncols);
   uint32_t ac_limit[2];
   for (int t = 0; t < 2; ++t) {
     const HuffAc& h = im->ac[t];
@@ -1261,9 +1302,18 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
       limit = per_mcu;
       end = kNever;
     } else {
-      const int target = (my0 + row) * row_blocks;
+      if (stage == SyncStage::kRows && __builtin_amdgcn_ballot_w64(row < nrows) == 0) {
+        // (files whose data ends early are decoded row by row)
+        if (im->live != kLiveCoefs || total < (my0 + nrows) * row_blocks || nrows != im->nrows ||
+            !pieces_fit(a, im->size, im->scan_off, nrows))
+          break;
+        stage = SyncStage::kPieces;
+        row = lane / sub;
+      }
+      int target = (my0 + row) * row_blocks;
+      if (stage == SyncStage::kPieces)
+        target += (im->mx0 + (lane - row * sub) * ncols / sub) * per_mcu;
       go = row < nrows && (target < total || target == 0);
-      if (__builtin_amdgcn_ballot_w64(row < nrows) == 0) break;
       from = 0;  // the last part that starts at or before the row's first block
       for (int step = kJpegThreads / 2; step > 0; step >>= 1)
         if (s.first_block[from + step] <= target) from += step;
@@ -1416,8 +1466,9 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
       stage = SyncStage::kRows;
     } else {
       // with no more than a bit buffer's 32 bits left the data has ended for a row after the first
-      const bool first_row = my0 + row == 0;
-      if (asked && (first_row || bits - bit > 32)) {
+      const bool piece = stage == SyncStage::kPieces;
+      const bool first_row = my0 + row == 0 && !piece;
+      if (asked && (first_row || piece || bits - bit > 32)) {
         const uint8_t* file = a.files + im->origin;
         const int32_t* map =
             reinterpret_cast<const int32_t*>(r.clean + clean_map_offset(im->size, im->scan_off));
@@ -1433,7 +1484,12 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
         st.pred[2] = (int16_t)(base2 + sum2);
         st.rst_left = 0;
         st.pad = 0;
-        (reinterpret_cast<RowState*>(a.row_states) + (int64_t)b * a.max_rows)[row] = st;
+        if (piece) piece_states(a, im->region_off)[lane] = st;
+        else (reinterpret_cast<RowState*>(a.row_states) + (int64_t)b * a.max_rows)[row] = st;
+      }
+      if (piece) {
+        if (lane == 0) reinterpret_cast<JpegPrepared*>(a.prepared)[b].im.live = kLivePieces;
+        break;
       }
       row += kJpegThreads;
     }
@@ -1450,6 +1506,12 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_decode_kernel(JpegArgs a) {
   const int lane = threadIdx.x;
   const int b0 = (int)blockIdx.x * kGroup;
   const int nimg = min(kGroup, a.B - b0);
+  bool need = false;
+  if (lane < nimg) {
+    const JpegImage& im = reinterpret_cast<const JpegPrepared*>(a.prepared)[b0 + lane].im;
+    need = im.live == kLivePlanes;
+  }
+  if (__builtin_amdgcn_ballot_w64(need) == 0) return;  // the usual case: all decoded already
   {  // the images' tables, as the table kernel left them
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const u32x4* src = reinterpret_cast<const u32x4*>(a.prepared + (size_t)b0 * sizeof(JpegPrepared));
@@ -1464,7 +1526,9 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_decode_kernel(JpegArgs a) {
   first_task[0] = 0;
 #pragma unroll
   for (int i = 0; i < kGroup; ++i)
-    first_task[i + 1] = first_task[i] + (i < nimg ? min(s.img[i].im.nrows, a.max_rows) : 0);
+    first_task[i + 1] =
+        first_task[i] +
+        (i < nimg && s.img[i].im.live == kLivePlanes ? min(s.img[i].im.nrows, a.max_rows) : 0);
   const int ntasks = first_task[kGroup];
   int16_t* coef = &s.coef[0][lane];  // element k at coef[k * 64]
 #pragma unroll 1
@@ -1560,6 +1624,357 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_decode_kernel(JpegArgs a) {
   }
 }
 
+
+// ---- the crop's coefficients, entropy decoding only ------------------------------------------------
+// A lane per row of MCUs, as above, but the lanes do not wait for the longest block among them: a step
+// is one AC symbol, one table look-up and no branch in the usual case, and its value goes straight to
+// its place (zig-zag order) in the image's coefficients, which the table kernel has cleared.  Every
+// kSteps steps come the things that only some lanes need: the next block's DC coefficient and the
+// file bytes; a lane that ends its block in between waits for that point, three steps on average.
+// There is one wavefront per SIMD at most, so what counts is the number of instructions and LDS round
+// trips per symbol; the inverse transform, which needs neither, is left to jpeg_idct_kernel, where it
+// fills the chip.  Every step stores: a symbol without a value a zero where one is (the last of the
+// coefficients that it skips), and the blocks to the left of the crop go where the row's first block
+// will be, which is cleared once they are behind.
+// The file's bytes lose their stuffing on the way into the ring (SymbolReader): topping up
+// the bit buffer is then a select.  4096 files of 256 pixels with a restart interval per row: 0.80 ms and
+// 0.45 ms for the inverse transform and colours (entropy decoding and transform by the same lanes,
+// block after block, as in jpeg_decode_kernel: 1.42 ms and 0.20 ms for the colours); 1024 files without
+// markers, rows in pieces: 0.22 + 0.12 ms (1.34 + 0.04 ms).
+constexpr int kSteps = 6;    // AC symbols of at most 31 bits between two points that all lanes pass
+constexpr int kRounds = 2;   // such points between two at which file bytes are taken
+constexpr int kAhead = 8 * kRounds;  // dwords in the ring then: kSteps symbols and two more, twice
+constexpr int kDcBits = 8;
+// direct part, then (from entry limit / 64 on) one entry per value of the 16 bits from `limit` on
+constexpr int kCoefAc = kAcEntries;
+constexpr int kCoefTable = 2 * kCoefAc + (2 << kDcBits);
+// An entry: size of the value (bits 0-3) | how far the coefficient index moves (bits 4-9; 63 from any
+// index ends the block) | 32 - bits of code and value (bits 10-15).  kMiss, for a code that is not in
+// the table, uses no bits and parks the lane at the end of a block, where the code is looked up.
+constexpr uint32_t kMiss = (32u << 10) | (63u << 4);
+__device__ static inline uint32_t coef_entry(int len, int rs) {
+  const int size = rs & 15, run = rs >> 4;
+  const int move = size ? run + 1 : (run == 15 ? 16 : 63);
+  return (uint32_t)(((32 - len - size) << 10) | (move << 4) | size);
+}
+
+struct SymbolReader {
+  const uint8_t* chunks;  // as in BitReader
+  int64_t chunks_bytes;
+  uint32_t* ring;  // this lane's column: big-endian dwords without byte stuffing
+  int skew, start, n;
+  int at;          // position (from `chunks`) of the 16 bytes in `next`, or of those to request
+  uint32_t part;   // the low nb bytes wait for a whole dword
+  int nb;
+  bool pend_ff;    // the last byte was 0xFF: its follower says what it is
+  bool ended;      // marker or end of the file: zeros from here on
+  bool pending;
+  u32x4_a8 next;
+  uint32_t hi, lo;  // (hi:lo) >> left are the next 32 bits
+  int left, taken, have;  // 0..31 / dwords that have been in hi, lo / in the ring
+};
+__device__ static __forceinline__ void sym_request(SymbolReader& r) {
+  if (!r.ended) r.next = load_chunk(r.chunks, r.chunks_bytes, r.at);
+  r.pending = true;
+}
+__device__ static __forceinline__ void sym_accept(SymbolReader& r) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t x = r.next[j], inv = ~x;
+    const int p = r.at + 4 * j - r.skew;  // file position
+    const bool ff = ((inv - 0x01010101u) & ~inv & 0x80808080u) != 0u;
+    const bool plain = (int)!ff & (int)!r.pend_ff & (int)(p >= r.start) & (int)(p + 4 <= r.n);
+    if ((int)r.ended | (int)plain) {
+      const uint32_t be = r.ended ? 0u : __builtin_bswap32(x);
+      r.ring[(r.have & (kRingBytes / 4 - 1)) * kJpegThreads] =
+          __builtin_amdgcn_alignbit(r.part, be, 8u * (uint32_t)r.nb);
+      r.part = be;
+      ++r.have;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t b = (x >> (8 * i)) & 0xFFu;
+        const bool here = !r.ended && p + i >= r.start;
+        r.ended = r.ended || (here && (p + i >= r.n || (r.pend_ff && b != 0u)));
+        const bool data = here && !r.ended && (r.pend_ff || b != 0xFFu);
+        const uint32_t v = r.pend_ff ? 0xFFu : b;
+        r.pend_ff = here && !r.ended && !r.pend_ff && b == 0xFFu;
+        r.part = data ? (r.part << 8) | v : r.part;
+        r.nb += data ? 1 : 0;
+        if (r.nb == 4) {
+          r.ring[(r.have & (kRingBytes / 4 - 1)) * kJpegThreads] = r.part;
+          ++r.have;
+          r.nb = 0;
+        }
+      }
+    }
+  }
+  r.at += 16;
+  r.pending = false;
+}
+__device__ static __forceinline__ void sym_feed(SymbolReader& r) {
+  if (r.pending) sym_accept(r);
+#pragma unroll 1
+  while (r.have - r.taken < kAhead) {
+    sym_request(r);
+    sym_accept(r);
+  }
+  // room: at most four dwords come out of 16 bytes, which last for a little more than two rounds
+  if (r.have - r.taken <= kRingBytes / 4 - 4) sym_request(r);
+}
+// Opens the reader in a row's state: its unread bits (up to 64) are the first two dwords.
+__device__ static __forceinline__ void sym_open(SymbolReader& r, const RowState& st) {
+  r.start = st.pos;
+  r.at = (st.pos + r.skew) & ~15;
+  r.part = 0;
+  r.nb = 0;
+  r.pend_ff = r.ended = r.pending = false;
+  r.ring[0] = (uint32_t)(st.acc >> 32);
+  r.ring[kJpegThreads] = (uint32_t)st.acc;
+  r.have = 2;
+#pragma unroll 1
+  while (r.have < 4 + kAhead) {
+    sym_request(r);
+    sym_accept(r);
+  }
+  const int bit = 64 - st.nbits;
+  const int w = bit >> 5;
+  r.left = -bit & 31;
+  r.hi = r.ring[w * kJpegThreads];
+  r.taken = w + (r.left ? 2 : 1);
+  r.lo = r.ring[(r.taken - 1) * kJpegThreads];
+}
+
+// Where the second part of an AC table starts: behind the codes of up to kFastBits bits, or later if
+// what follows is too much for it (codes in between have no entry and are looked up in the ranges).
+__device__ static inline uint32_t long_from(const HuffAc& h) {
+  return min(max(h.range[kFastBits - 1].limit, 65536u - kLongCodes), 65536u);  // (any file's table)
+}
+// The next 32 bits; 32 - `off` of them used.
+__device__ static __forceinline__ uint32_t sym_top(const SymbolReader& r) {
+  return __builtin_amdgcn_alignbit(r.hi, r.lo, (uint32_t)r.left);
+}
+__device__ static __forceinline__ void sym_skip(SymbolReader& r, int off, uint32_t ahead) {
+  const int sum = r.left + off;  // below 32: the dword in `hi` is used up
+  const bool top_up = sum < 32;
+  r.hi = top_up ? r.lo : r.hi;
+  r.lo = top_up ? ahead : r.lo;
+  r.taken += top_up ? 1 : 0;
+  r.left = sum & 31;
+}
+__device__ static __forceinline__ uint32_t sym_ahead(const SymbolReader& r) {
+  return r.ring[(r.taken & (kRingBytes / 4 - 1)) * kJpegThreads];
+}
+// `size` value bits that end `off` bits above the lowest, as the signed value they stand for (T.81
+// F.2.2.1: the lower half of the range is the negative numbers); 0 for none.
+__device__ static __forceinline__ int symbol_value(uint32_t top, int off, int size) {
+  const int v = (int)__builtin_amdgcn_ubfe(top, (uint32_t)off, (uint32_t)size);
+  const int most = (1 << size) - 1;
+  return 2 * v <= most ? v - most : v;
+}
+
+template <int kGroup>
+struct JpegEntropyLds {
+  uint16_t table[kGroup * kCoefTable];  // per image AC luma, AC chroma, DC luma, DC chroma
+  uint32_t ring[kRingBytes / 4][kJpegThreads];
+};
+
+template <int kGroup>
+__global__ __launch_bounds__(kJpegThreads) void jpeg_entropy_kernel(JpegArgs a) {
+  __shared__ JpegEntropyLds<kGroup> s;
+  const int lane = threadIdx.x;
+  const int b0 = (int)blockIdx.x * kGroup;
+  const int nimg = min(kGroup, a.B - b0);
+  const JpegPrepared* prepared = reinterpret_cast<const JpegPrepared*>(a.prepared) + b0;
+  int first_task[kGroup + 1];
+  first_task[0] = 0;
+#pragma unroll
+  for (int i = 0; i < kGroup; ++i) {
+    int rows = 0;
+    if (i < nimg && prepared[i].im.live >= kLiveCoefs) {
+      const JpegImage& im = prepared[i].im;
+      rows = min(im.nrows, a.max_rows);
+      if (im.live == kLivePieces) rows *= pieces_per_row(im.nrows, im.mx1 - im.mx0 + 1);
+    }
+    first_task[i + 1] = first_task[i] + rows;
+    if (rows == 0) continue;
+    for (int t = 0; t < 2; ++t) {
+      const HuffAc& h = prepared[i].im.ac[t];
+      const HuffDc& g = prepared[i].im.dc[t];
+      const uint32_t limit = long_from(h);
+      uint16_t* table = s.table + i * kCoefTable + t * kCoefAc;
+      const int direct = (int)(limit >> (16 - kFastBits));
+#pragma unroll 4
+      for (int j = lane; j < kDirect; j += kJpegThreads) {
+        const int e = h.fast[j];
+        if (j < direct) table[j] = (uint16_t)(e ? coef_entry(e >> 8, e & 255) : kMiss);
+      }
+      for (int j = lane; j < kLongCodes; j += kJpegThreads) {
+        const uint32_t x = limit + (uint32_t)j;
+        uint32_t e = kMiss;
+        if (x <= 0xFFFFu) {
+          int index;
+          const int len = find_code<kFastBits>(h.range, x, index);
+          if (len < 16) e = coef_entry(len + 1, h.symbols[index & 255]);
+        }
+        table[direct + j] = (uint16_t)e;
+      }
+      table = s.table + i * kCoefTable + 2 * kCoefAc + (t << kDcBits);
+      for (int j = lane; j < (1 << kDcBits); j += kJpegThreads) {
+        int index;
+        const int len = find_code<0>(g.range, (uint32_t)j << (16 - kDcBits), index);
+        const int sym = len < kDcBits ? g.symbols[index & 15] : 16;
+        table[j] = (uint16_t)(sym <= 11 ? coef_entry(len + 1, sym) : kMiss);
+      }
+    }
+  }
+  __syncthreads();
+  const int ntasks = first_task[kGroup];
+  const uint32_t slot_bytes = (uint32_t)(a.slot_side * a.slot_side * 3);
+  uint8_t* coefs = a.planes + (int64_t)b0 * slot_bytes;  // (slots follow each other)
+
+#pragma unroll 1
+  for (int task = lane; task < ntasks; task += kJpegThreads) {
+    int slot = 0, slot_first = 0;
+#pragma unroll
+    for (int i = 1; i < kGroup; ++i) {
+      if (task >= first_task[i]) {
+        slot = i;
+        slot_first = first_task[i];
+      }
+    }
+    const JpegImage& im = prepared[slot].im;
+    const int b = b0 + slot;
+    const int nblk = im.hs * im.hs, last_phase = nblk + 1, per_mcu = nblk + 2;
+    const int mx0 = im.mx0, mx1 = im.mx1, ncols = mx1 - mx0 + 1;
+    int row = task - slot_first;  // row of MCUs inside the crop's range
+    int first = 0;                // MCU of the crop that the lane's blocks are stored from
+    int skip = mx0 * per_mcu, total = (mx1 + 1) * per_mcu;  // blocks
+    RowState st = (reinterpret_cast<const RowState*>(a.row_states) + (int64_t)b * a.max_rows)[
+        min(row, a.max_rows - 1)];
+    bool bad = false;
+    if (im.live == kLivePieces) {
+      const int sub = pieces_per_row(im.nrows, ncols);
+      st = piece_states(a, im.region_off)[row];
+      const int piece = row % sub;
+      row /= sub;
+      first = piece * ncols / sub;
+      skip = 0;
+      total = ((piece + 1) * ncols / sub - first) * per_mcu;
+      // (a row whose start is not known flags the sample, also when its pieces' are)
+      bad = (reinterpret_cast<const RowState*>(a.row_states) + (int64_t)b * a.max_rows)[row].pos < 0;
+    }
+    const uint32_t limit_y = long_from(im.ac[0]), limit_c = long_from(im.ac[1]);
+    const int table = slot * kCoefTable;
+    // byte offsets of the row's first block, and of the current one less one coefficient
+    const uint32_t base = (uint32_t)slot * slot_bytes +
+                          (uint32_t)((row * ncols + first) * per_mcu * kBlockBytes);
+    uint32_t out = base - 2;
+    // (a row's restart boundary, if any, lies behind its last MCU: a state that says otherwise is
+    // not one of this file's)
+    bad = bad || st.pos < im.scan_off || st.pos > im.size || st.nbits < 0 || st.nbits > 64 ||
+          (im.restart != 0 && st.rst_left != 0 && (int)st.rst_left <= mx1);
+    bool go = !bad;
+    SymbolReader r;
+    r.skew = (int)(im.origin & 7);
+    r.chunks = a.files + (im.origin - r.skew);
+    r.chunks_bytes = a.files_bytes - (im.origin - r.skew);
+    r.ring = &s.ring[0][lane];
+    r.n = im.size;
+    int pred0 = st.pred[0], pred1 = st.pred[1], pred2 = st.pred[2];
+    int k = 64, phase = -1, done = -1;  // (as behind a block before the first)
+    uint32_t e = 0;                     // the last AC symbol's entry
+    uint32_t limit = 0;
+    int ac = table;
+    bool is_chroma = false;
+    if (go) sym_open(r, st);
+    int round = 0;  // (the same in all lanes that are still at work)
+#pragma unroll 1
+    while (go) {
+      if (__builtin_expect(k >= 64 && e == kMiss, 0)) {
+        int index;
+        const HuffAc& h = im.ac[is_chroma];
+        const uint32_t ahead = sym_ahead(r), top = sym_top(r);
+        const int len = find_code<0>(h.range, top >> 16, index);
+        k -= 63;
+        if (len < 16) {
+          e = coef_entry(len + 1, h.symbols[index & 255]);
+          const int size = (int)(e & 15u), off = (int)(e >> 10);
+          k += (int)((e >> 4) & 63u);
+          *reinterpret_cast<int16_t*>(coefs + (out + 2u * (uint32_t)min(k, 64))) =
+              (int16_t)symbol_value(top, off, size);
+          sym_skip(r, off, ahead);
+        } else {  // no such code
+          bad = true;
+          break;
+        }
+      }
+      // ---- lanes whose block has ended: the next one's DC coefficient ----
+      int dc = 0;
+      const bool opens = k >= 64;
+      if (opens) {
+        bad = bad || ((e & 15u) != 0u && k > 64);  // a run past the end of the block
+        ++done;
+        out += done > skip ? (uint32_t)kBlockBytes : 0u;
+        if (done == skip && skip) {
+          // the blocks to the left of the crop have left their values where the first block goes
+          typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+          for (int i = 0; i < kBlockBytes / 16; ++i)
+            reinterpret_cast<u32x4*>(coefs + base)[i] = u32x4{0u, 0u, 0u, 0u};
+        }
+        phase = phase == last_phase ? 0 : phase + 1;
+        is_chroma = phase >= nblk;
+        limit = is_chroma ? limit_c : limit_y;
+        ac = table + (is_chroma ? kCoefAc : 0);
+        go = done < total && !bad;
+        const uint32_t ahead = sym_ahead(r), top = sym_top(r);
+        uint32_t d = s.table[table + 2 * kCoefAc + (is_chroma ? 1 << kDcBits : 0) +
+                             (int)(top >> (32 - kDcBits))];
+        if (__builtin_expect(d == kMiss, 0)) {
+          int index;
+          const HuffDc& h = im.dc[is_chroma];
+          const int len = find_code<0>(h.range, top >> 16, index);
+          const int sym = len < 16 ? h.symbols[index & 15] : 16;
+          if (sym <= 11) d = coef_entry(len + 1, sym);
+          else if (go) bad = true;
+        }
+        const int size = (int)(d & 15u), off = (int)(d >> 10);
+        const int diff = symbol_value(top, off, size);
+        sym_skip(r, off, ahead);
+        pred0 += is_chroma ? 0 : diff;
+        pred1 += phase == nblk ? diff : 0;
+        pred2 += phase == last_phase ? diff : 0;
+        // (clamped to 16 bits: beyond them the de-quantised value is clamped to the same anyway)
+        dc = min(max(is_chroma ? (phase == nblk ? pred1 : pred2) : pred0, -32767), 32767);
+        k = 1;
+        go = go && !bad;
+      }
+      if (!go) break;
+      if (round == 0) sym_feed(r);
+      round = round + 1 == kRounds ? 0 : round + 1;
+      if (opens) *reinterpret_cast<int16_t*>(coefs + (out + 2u)) = (int16_t)dc;
+      // ---- AC symbols; a lane whose block ends waits for the next round ----
+#pragma unroll
+      for (int i = 0; i < kSteps; ++i) {
+        if (k < 64) {
+          const uint32_t ahead = sym_ahead(r), top = sym_top(r);
+          const uint32_t beyond = __builtin_elementwise_sub_sat(top >> 16, limit);
+          e = s.table[(uint32_t)ac + min(top >> (32 - kFastBits), limit >> (16 - kFastBits)) + beyond];
+          const int size = (int)(e & 15u), off = (int)(e >> 10);
+          k += (int)((e >> 4) & 63u);
+          *reinterpret_cast<int16_t*>(coefs + (out + 2u * (uint32_t)min(k, 64))) =
+              (int16_t)symbol_value(top, off, size);
+          sym_skip(r, off, ahead);
+        }
+      }
+    }
+    if (bad) {
+      reinterpret_cast<CropRec*>(a.workspace + kWorkspaceHeader)[b].valid = 0;
+      if (a.crop_out) a.crop_out[(int64_t)b * 6 + 5] = 0;
+    }
+  }
+}
+
 size_t jpeg_prepared_bytes() { return sizeof(JpegPrepared); }
 size_t jpeg_row_state_bytes() { return sizeof(RowState); }
 
@@ -1569,17 +1984,108 @@ hipError_t launch_jpeg_header(const JpegArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Planes -> interleaved RGB, the region's rows as the resampling kernel reads them.  One workgroup
-// per image and band of rows, four pixels per thread and step; chroma is repeated over hs x hs
-// pixels (T.81 A.1.1 leaves upsampling open; repetition is this library's definition).
-constexpr int kColourThreads = 256;
+// Four pixels of a row of the region: interleaved RGB, 12 bytes at a 4-byte aligned address.
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+typedef u32x3 u32x3_a4 __attribute__((aligned(4)));
+__device__ static inline void store_rgb4(uint8_t* dst, uint32_t yy, uint32_t cb, uint32_t cr) {
+  uint32_t px[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    px[j] = ycc_to_rgbx((int)((yy >> (8 * j)) & 0xFFu), (int)((cb >> (8 * j)) & 0xFFu),
+                        (int)((cr >> (8 * j)) & 0xFFu));
+  *reinterpret_cast<u32x3_a4*>(dst) =
+      u32x3{px[0] | (px[1] << 24), (px[1] >> 8) | (px[2] << 16), (px[2] >> 16) | (px[3] << 8)};
+}
+// Two chroma samples, each over two pixels (T.81 A.1.1 leaves upsampling open; repetition is this
+// library's definition).
+__device__ static inline uint32_t repeat2(uint32_t c) {
+  return (c & 0xFFu) * 0x0101u | (c >> 8) * 0x01010000u;
+}
+
+// Coefficients or planes -> interleaved RGB, the region's rows as the resampling kernel reads them.
+// A workgroup takes 192 blocks of an image at a time, one per lane: 32 MCUs with 4:2:0 sampling (two
+// wavefronts of luma, one of chroma) or 64 with 4:4:4 (a wavefront per component), so that a
+// wavefront has one quantiser table, in scalar registers.  The transform is unrolled over registers
+// (zig-zag order is then free); its even and odd halves are summed apart and give two outputs each,
+// which halves the products (sums of the same integers: nothing changes in the result).  The samples
+// meet in LDS, from where four pixels per lane and step are converted and stored along the rows.
+// Bound by vector instructions, about 2400 per 64 blocks, of which the transform is half.
+// Images that jpeg_decode_kernel has decoded have planes instead of coefficients.
+constexpr int kIdctThreads = 3 * kWave;
+constexpr int kIdctStride = 72;   // bytes per block of samples: 64 and a pad against bank conflicts
+constexpr int kCoefStride = 144;  // the same for its coefficients
 constexpr int kColourBand = 32;
-__global__ __launch_bounds__(kColourThreads) void jpeg_colour_kernel(JpegArgs a, int bands) {
-  const int b = (int)(blockIdx.x / (uint32_t)bands);
-  const int band = (int)(blockIdx.x - (uint32_t)b * (uint32_t)bands);
-  const JpegRec rec = a.recs[b];
-  const int first = band * kColourBand;
-  if (!rec.valid || first >= rec.region_h) return;
+
+constexpr int kZigzagOf[64] = {  // kZigzag for compile-time indices
+    0,  1,  8,  16, 9,  2,  3,  10, 17, 24, 32, 25, 18, 11, 4,  5,  12, 19, 26, 33, 40, 48,
+    41, 34, 27, 20, 13, 6,  7,  14, 21, 28, 35, 42, 49, 56, 57, 50, 43, 36, 29, 22, 15, 23,
+    30, 37, 44, 51, 58, 59, 52, 45, 38, 31, 39, 46, 53, 60, 61, 54, 47, 55, 62, 63};
+
+// Eight outputs of one line of the transform; c = inputs 0|2, 4|6, 1|3, 5|7 as pairs of 16 bits.
+__device__ static inline void idct_line(const s16x2 c[4], int rounding, int out[8]) {
+  constexpr s16x2 kEven[4][2] = {{{5793, 7568}, {5793, 3135}},
+                                 {{5793, 3135}, {-5793, -7568}},
+                                 {{5793, -3135}, {-5793, 7568}},
+                                 {{5793, -7568}, {5793, -3135}}};
+  constexpr s16x2 kOdd[4][2] = {{{8035, 6811}, {4551, 1598}},
+                                {{6811, -1598}, {-8035, -4551}},
+                                {{4551, -8035}, {1598, 6811}},
+                                {{1598, -4551}, {6811, -8035}}};
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    int e = __builtin_amdgcn_sdot2(c[0], kEven[x][0], rounding, false);
+    e = __builtin_amdgcn_sdot2(c[1], kEven[x][1], e, false);
+    int o = __builtin_amdgcn_sdot2(c[2], kOdd[x][0], 0, false);
+    o = __builtin_amdgcn_sdot2(c[3], kOdd[x][1], o, false);
+    out[x] = e + o;
+    out[7 - x] = e - o;
+  }
+}
+
+// A block of coefficients -> its samples, eight rows of eight bytes at `samples`.  qz: quantiser step
+// of zig-zag position `lane` (the wavefront's blocks share the table).
+typedef uint32_t u32x4_c __attribute__((ext_vector_type(4)));
+__device__ static inline void idct_block(const u32x4_c raw[8], int qz, uint8_t* samples) {
+  int c[64];
+#pragma unroll
+  for (int k = 0; k < 64; ++k) {
+    const int v = (int16_t)(raw[k >> 3][(k >> 1) & 3] >> (16 * (k & 1)));
+    c[kZigzagOf[k]] = min(max(__mul24(v, __builtin_amdgcn_readlane(qz, k)), -32767), 32767);
+  }
+  int t[64];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    s16x2 in[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int y = (i & 1) * 4 + (i >> 1);  // rows 0|2, 4|6, 1|3, 5|7
+      in[i] = s16x2{(short)c[y * 8 + u], (short)c[(y + 2) * 8 + u]};
+    }
+    int line[8];
+    idct_line(in, 1 << 10, line);
+#pragma unroll
+    for (int y = 0; y < 8; ++y) t[y * 8 + u] = min(max(line[y] >> 11, -32767), 32767);
+  }
+#pragma unroll
+  for (int y = 0; y < 8; ++y) {
+    s16x2 in[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int u = (i & 1) * 4 + (i >> 1);
+      in[i] = s16x2{(short)t[y * 8 + u], (short)t[y * 8 + u + 2]};
+    }
+    int v[8];
+    idct_line(in, 1 << 16, v);
+#pragma unroll
+    for (int x = 0; x < 8; ++x) v[x] = min(max((v[x] >> 17) + 128, 0), 255);
+    *reinterpret_cast<u32x2*>(samples + 8 * y) =
+        u32x2{(uint32_t)v[0] | ((uint32_t)v[1] << 8) | ((uint32_t)v[2] << 16) | ((uint32_t)v[3] << 24),
+              (uint32_t)v[4] | ((uint32_t)v[5] << 8) | ((uint32_t)v[6] << 16) | ((uint32_t)v[7] << 24)};
+  }
+}
+
+// The planes of one band of rows -> RGB.
+__device__ static void colour_band(const JpegArgs& a, const JpegRec& rec, int b, int first) {
   const int region_w = a.region_widths[b], hs = rec.hs;
   const int chroma_w = region_w / hs;
   const int64_t off = a.region_offsets[b];
@@ -1589,31 +2095,97 @@ __global__ __launch_bounds__(kColourThreads) void jpeg_colour_kernel(JpegArgs a,
   uint8_t* region = a.regions + off;
   const int ng = region_w >> 2;
   const int rows = min(kColourBand, rec.region_h - first);
-  for (int i = (int)threadIdx.x; i < rows * ng; i += kColourThreads) {
+  for (int i = (int)threadIdx.x; i < rows * ng; i += kIdctThreads) {
     const int y = first + i / ng, g = i % ng;
     const uint32_t yy = *reinterpret_cast<const uint32_t*>(plane_y + (int64_t)y * region_w + 4 * g);
     uint32_t cb, cr;  // one byte per pixel
     if (hs == 2) {
       const int64_t o = (int64_t)(y >> 1) * chroma_w + 2 * g;
-      const uint32_t b2 = *reinterpret_cast<const uint16_t*>(plane_cb + o);
-      const uint32_t r2 = *reinterpret_cast<const uint16_t*>(plane_cr + o);
-      cb = (b2 & 0xFFu) * 0x0101u | (b2 >> 8) * 0x01010000u;
-      cr = (r2 & 0xFFu) * 0x0101u | (r2 >> 8) * 0x01010000u;
+      cb = repeat2(*reinterpret_cast<const uint16_t*>(plane_cb + o));
+      cr = repeat2(*reinterpret_cast<const uint16_t*>(plane_cr + o));
     } else {
       const int64_t o = (int64_t)y * chroma_w + 4 * g;
       cb = *reinterpret_cast<const uint32_t*>(plane_cb + o);
       cr = *reinterpret_cast<const uint32_t*>(plane_cr + o);
     }
-    uint32_t px[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      px[j] = ycc_to_rgbx((int)((yy >> (8 * j)) & 0xFFu), (int)((cb >> (8 * j)) & 0xFFu),
-                          (int)((cr >> (8 * j)) & 0xFFu));
     // rows of the region start on 4-byte boundaries (their width is a multiple of 8 pixels)
-    uint32_t* dst = reinterpret_cast<uint32_t*>(region + ((int64_t)y * region_w + 4 * g) * 3);
-    dst[0] = px[0] | (px[1] << 24);
-    dst[1] = (px[1] >> 8) | (px[2] << 16);
-    dst[2] = (px[2] >> 16) | (px[3] << 8);
+    store_rgb4(region + ((int64_t)y * region_w + 4 * g) * 3, yy, cb, cr);
+  }
+}
+
+__global__ __launch_bounds__(kIdctThreads) void jpeg_idct_kernel(JpegArgs a, int parts) {
+  // the step's coefficients, then (all lanes have theirs in registers) its samples
+  __shared__ __attribute__((aligned(16))) uint8_t samples[kIdctThreads * kCoefStride];
+  __shared__ uint32_t place[kWave];  // of an MCU's first pixel in the region
+  const int b = (int)(blockIdx.x / (uint32_t)parts);
+  const int part = (int)(blockIdx.x - (uint32_t)b * (uint32_t)parts);
+  const JpegImage& im = reinterpret_cast<const JpegPrepared*>(a.prepared)[b].im;
+  if (!im.live) return;
+  if (im.live == kLivePlanes) {
+    const JpegRec rec = a.recs[b];
+    for (int first = part * kColourBand; first < rec.region_h; first += parts * kColourBand)
+      colour_band(a, rec, b, first);
+    return;
+  }
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  const int hs = im.hs, per_mcu = hs * hs + 2, mcu = 8 * hs;
+  const int ncols = im.mx1 - im.mx0 + 1, nmcu = ncols * im.nrows;
+  const int region_w = im.region_w;
+  const uint8_t* coef = a.planes + im.region_off;
+  uint8_t* region = a.regions + im.region_off;
+  const int qz = im.qz[hs == 2 ? wave == 2 : wave != 0][lane] & 255;
+  const int group = kWave / hs;  // MCUs per step
+  // this lane's block: MCU inside the group, block of the MCU
+  const int m = hs == 2 ? (wave == 2 ? lane >> 1 : 16 * wave + (lane >> 2)) : lane;
+  const int blk = hs == 2 ? (wave == 2 ? 4 + (lane & 1) : lane & 3) : wave;
+  for (int m0 = part * group; m0 < nmcu; m0 += parts * group) {
+    if ((int)threadIdx.x < group) {
+      const int i = min(m0 + (int)threadIdx.x, nmcu - 1);
+      const int my = i / ncols, mx = i - my * ncols;
+      place[threadIdx.x] = (uint32_t)((my * mcu * region_w + mx * mcu) * 3);
+    }
+    // the step's blocks lie one after the other in memory: 16 bytes per lane and load
+    const u32x4_c* src = reinterpret_cast<const u32x4_c*>(coef + (int64_t)m0 * per_mcu * kBlockBytes);
+    const int pieces = min(group, nmcu - m0) * per_mcu * (kBlockBytes / 16);
+    u32x4_c raw[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      raw[i] = src[min((int)threadIdx.x + i * kIdctThreads, pieces - 1)];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int at = (int)threadIdx.x + i * kIdctThreads;
+      *reinterpret_cast<u32x4_c*>(samples + (at >> 3) * kCoefStride + (at & 7) * 16) = raw[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      raw[i] = *reinterpret_cast<const u32x4_c*>(samples + (m * per_mcu + blk) * kCoefStride + 16 * i);
+    __syncthreads();
+    idct_block(raw, qz, samples + threadIdx.x * kIdctStride);
+    __syncthreads();
+    // 128 pieces of four pixels per row of the group's MCUs
+    for (int i = (int)threadIdx.x; i < 128 * mcu; i += kIdctThreads) {
+      const int y = i >> 7, r = i & 127;
+      const int pm = r >> hs, piece = r & (2 * hs - 1);
+      if (m0 + pm >= nmcu) continue;
+      uint32_t yy, cb, cr;
+      if (hs == 2) {
+        const int luma = 4 * pm + (y >> 3) * 2 + (piece >> 1), chroma = 128 + 2 * pm;
+        yy = *reinterpret_cast<const uint32_t*>(samples + luma * kIdctStride + (y & 7) * 8 +
+                                                4 * (piece & 1));
+        const uint8_t* c = samples + chroma * kIdctStride + (y >> 1) * 8 + 2 * piece;
+        cb = repeat2(*reinterpret_cast<const uint16_t*>(c));
+        cr = repeat2(*reinterpret_cast<const uint16_t*>(c + kIdctStride));
+      } else {
+        const uint8_t* s = samples + pm * kIdctStride + y * 8 + 4 * piece;
+        yy = *reinterpret_cast<const uint32_t*>(s);
+        cb = *reinterpret_cast<const uint32_t*>(s + kWave * kIdctStride);
+        cr = *reinterpret_cast<const uint32_t*>(s + 2 * kWave * kIdctStride);
+      }
+      store_rgb4(region + (place[pm] + (uint32_t)((y * region_w + 4 * piece) * 3)), yy, cb, cr);
+    }
+    __syncthreads();
   }
 }
 
@@ -1651,17 +2223,31 @@ hipError_t launch_jpeg_decode(const JpegArgs& a, hipStream_t stream) {
   // side allowed has slot_side / 16 rows of them when its luma is sampled 2x2
   const int rows = a.slot_side / 16;
   const uint32_t B = (uint32_t)a.B;
-  if (rows <= 16)
+  const int most = rows <= 16 ? 4 : (rows <= 32 ? 2 : 1);
+  // fewer when the batch leaves SIMDs without a wavefront (4 per compute unit): a wavefront with
+  // fewer lanes has fewer of them on a rare path at a time
+  const int group = B <= 1024 ? 1 : (B <= 2048 ? (most < 2 ? most : 2) : most);
+  if (group == 4)
+    hipLaunchKernelGGL(jpeg_entropy_kernel<4>, dim3((B + 3) / 4), block, 0, stream, a);
+  else if (group == 2)
+    hipLaunchKernelGGL(jpeg_entropy_kernel<2>, dim3((B + 1) / 2), block, 0, stream, a);
+  else
+    hipLaunchKernelGGL(jpeg_entropy_kernel<1>, dim3(B), block, 0, stream, a);
+  err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  // files with restart boundaries inside a row of MCUs, and crops whose coefficients do not fit
+  if (most == 4)
     hipLaunchKernelGGL(jpeg_decode_kernel<4>, dim3((B + 3) / 4), block, 0, stream, a);
-  else if (rows <= 32)
+  else if (most == 2)
     hipLaunchKernelGGL(jpeg_decode_kernel<2>, dim3((B + 1) / 2), block, 0, stream, a);
   else
     hipLaunchKernelGGL(jpeg_decode_kernel<1>, dim3(B), block, 0, stream, a);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
-  const int bands = (a.slot_side + kColourBand - 1) / kColourBand;
-  hipLaunchKernelGGL(jpeg_colour_kernel, dim3((uint32_t)a.B * (uint32_t)bands),
-                     dim3(kColourThreads), 0, stream, a, bands);
+  // workgroups per image: a step each for the largest image with 4:2:0 sampling
+  const int parts = (rows * rows + 31) / 32;
+  hipLaunchKernelGGL(jpeg_idct_kernel, dim3(B * (uint32_t)parts), dim3(kIdctThreads), 0, stream, a,
+                     parts);
   return hipGetLastError();
 }
 

@@ -277,6 +277,42 @@ def test_files_the_decoder_does_not_take_are_flagged_and_take_no_part():
         check_neutral_outputs(buf, b)
 
 
+@pytest.mark.parametrize("restart_rows", [0, 1, 2])
+def test_coefficients_and_planes_in_one_batch(restart_rows):
+    """4:4:4 files whose crops are around half the slot: the coefficients of some fit the plane
+    buffer, the others are decoded to planes.  Tables with codes that the direct tables leave out
+    (optimised, quality 100), and crops that start right of the first MCU."""
+    B, S = 13, 64
+    files, offsets, sizes = synth.make_jpegs("gradient", B, seed=68, quality=100, subsampling="4:4:4",
+                                             restart_rows=restart_rows)
+    kw = dict(out_size=S, patch=16, num_keep=4, scale=(0.35, 0.75), seed=24, batch_index=1)
+    ref = oracle.prep_batch(*_decode_all(files, offsets, sizes), **kw)
+    buf, _ = _gpu_jpeg_prep(files, offsets, sizes, **kw)
+    assert mae.mae_prep_status(buf.workspace) == 0
+    check_prep_against_oracle(prep_to_numpy(buf), ref, what=f"restart rows {restart_rows}")
+
+
+def test_files_without_markers_whose_data_ends_early():
+    """Inside the last row (zero bits follow: rows are then not decoded in pieces), or rows before it
+    (the sample is flagged when its crop wants them)."""
+    one, _, lens = synth.make_jpegs("gradient", 1, seed=69, restart_rows=0)
+    cuts = [0, 2, 9, 60, 400, lens[0] // 2]
+    chunks = [one[:lens[0] - c] for c in cuts]
+    sizes = np.array([c.size for c in chunks], np.int32)
+    offsets = np.zeros(len(cuts), np.int64)
+    offsets[1:] = np.cumsum(sizes.astype(np.int64))[:-1]
+    files = np.concatenate(chunks)
+    kw = dict(out_size=96, patch=16, num_keep=9, scale=(1.0, 1.0), ratio=(1.0, 1.0), seed=25)
+    ref = oracle.prep_batch(*_decode_all(files, offsets, sizes), **kw)
+    buf, _ = _gpu_jpeg_prep(files, offsets, sizes, **kw)
+    crop = buf.crop.cpu().numpy()
+    assert list(crop[:, 5]) == [1, 1, 1, 1, 1, 0]
+    keep = list(range(5))
+    sel = {k: (v[keep] if v is not None else None) for k, v in ref.items()}
+    check_prep_against_oracle(prep_to_numpy(buf, rows=keep), sel, what="cut files")
+    check_neutral_outputs(buf, 5)
+
+
 def test_files_of_maximum_side_500():
     """The size of the paper's crop-decode benchmark: 24 to 32 rows of MCUs per image, so the four
     images of a wavefront have more rows than it has lanes."""
