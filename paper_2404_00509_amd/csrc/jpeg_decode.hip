@@ -1079,6 +1079,96 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_scan_kernel(JpegArgs a) {
   }
 }
 
+// ---- symbols by table look-up, for the two kernels that follow -------------------------------------
+// A step is one AC symbol, one look-up and no branch; what only some lanes need comes every kSteps
+// steps: a block's end, the next one's DC coefficient, a code that is not in the table.  A lane that
+// ends its block in between waits for that point, three steps on average; without the waiting every
+// step would carry the instructions for all of it (about 100 instead of 33, 20 without the value).
+constexpr int kLongCodes = 512;  // entries for codes beyond the direct part of a table
+constexpr int kDirect = 1 << kFastBits;
+constexpr int kSteps = 6;    // AC symbols of at most 31 bits between two points that all lanes pass
+constexpr int kRounds = 2;   // such points between two at which file bytes are taken
+constexpr int kAhead = 8 * kRounds;  // dwords in the ring then: kSteps symbols and two more, twice
+constexpr int kDcBits = 8;
+// direct part, then (from entry limit / 64 on) one entry per value of the 16 bits from `limit` on
+constexpr int kCoefAc = kDirect + kLongCodes;
+constexpr int kCoefTable = 2 * kCoefAc + (2 << kDcBits);
+// An entry: size of the value (bits 0-3) | how far the coefficient index moves (bits 4-9; 63 from any
+// index ends the block) | 32 - bits of code and value (bits 10-15).  kMiss, for a code that is not in
+// the table, uses no bits and parks the lane at the end of a block, where the code is looked up.
+constexpr uint32_t kMiss = (32u << 10) | (63u << 4);
+constexpr uint32_t kNoCode = (31u << 10) | (63u << 4);  // one bit, the end of the block
+__device__ static inline uint32_t coef_entry(int len, int rs) {
+  const int size = rs & 15, run = rs >> 4;
+  const int move = size ? run + 1 : (run == 15 ? 16 : 63);
+  return (uint32_t)(((32 - len - size) << 10) | (move << 4) | size);
+}
+
+// Where the second part of an AC table starts: behind the codes of up to kFastBits bits, or later if
+// what follows is too much for it (codes in between have no entry and are looked up in the ranges).
+__device__ static inline uint32_t long_from(const HuffAc& h) {
+  return min(max(h.range[kFastBits - 1].limit, 65536u - kLongCodes), 65536u);  // (any file's table)
+}
+// Bit readers hold the next 32 bits as (hi:lo) >> left; 32 - `off` of them used.
+template <typename Reader>
+__device__ static __forceinline__ uint32_t sym_top(const Reader& r) {
+  return __builtin_amdgcn_alignbit(r.hi, r.lo, (uint32_t)r.left);
+}
+template <typename Reader>
+__device__ static __forceinline__ void sym_skip(Reader& r, int off, uint32_t ahead) {
+  const int sum = r.left + off;  // below 32: the dword in `hi` is used up
+  const bool top_up = sum < 32;
+  r.hi = top_up ? r.lo : r.hi;
+  r.lo = top_up ? ahead : r.lo;
+  r.taken += top_up ? 1 : 0;
+  r.left = sum & 31;
+}
+template <typename Reader>
+__device__ static __forceinline__ uint32_t sym_ahead(const Reader& r) {
+  return r.ring[(r.taken & (kRingBytes / 4 - 1)) * kJpegThreads];
+}
+// `size` value bits that end `off` bits above the lowest, as the signed value they stand for (T.81
+// F.2.2.1: the lower half of the range is the negative numbers); 0 for none.
+__device__ static __forceinline__ int symbol_value(uint32_t top, int off, int size) {
+  const int v = (int)__builtin_amdgcn_ubfe(top, (uint32_t)off, (uint32_t)size);
+  const int most = (1 << size) - 1;
+  return 2 * v <= most ? v - most : v;
+}
+
+// The tables of an image: AC luma, AC chroma, DC luma, DC chroma (whole wavefront).
+__device__ static void coef_tables(const JpegImage& im, uint16_t* tables) {
+  const int lane = threadIdx.x;
+  for (int t = 0; t < 2; ++t) {
+    const HuffAc& h = im.ac[t];
+    const HuffDc& g = im.dc[t];
+    const uint32_t limit = long_from(h);
+    uint16_t* table = tables + t * kCoefAc;
+    const int direct = (int)(limit >> (16 - kFastBits));
+#pragma unroll 4
+    for (int j = lane; j < kDirect; j += kJpegThreads) {
+      const int e = h.fast[j];
+      if (j < direct) table[j] = (uint16_t)(e ? coef_entry(e >> 8, e & 255) : kMiss);
+    }
+    for (int j = lane; j < kLongCodes; j += kJpegThreads) {
+      const uint32_t x = limit + (uint32_t)j;
+      uint32_t e = kMiss;
+      if (x <= 0xFFFFu) {
+        int index;
+        const int len = find_code<kFastBits>(h.range, x, index);
+        if (len < 16) e = coef_entry(len + 1, h.symbols[index & 255]);
+      }
+      table[direct + j] = (uint16_t)e;
+    }
+    table = tables + 2 * kCoefAc + (t << kDcBits);
+    for (int j = lane; j < (1 << kDcBits); j += kJpegThreads) {
+      int index;
+      const int len = find_code<0>(g.range, (uint32_t)j << (16 - kDcBits), index);
+      const int sym = len < kDcBits ? g.symbols[index & 15] : 16;
+      table[j] = (uint16_t)(sym <= 11 ? coef_entry(len + 1, sym) : kMiss);
+    }
+  }
+}
+
 // ---- files that are one chain of codes: where does each of the crop's rows start? ----------------
 // Huffman codes re-synchronise: a decoder set down anywhere in the data soon reads the same blocks
 // as one that came from the start (measured over the synthetic files: after 700 bits at the median,
@@ -1092,17 +1182,11 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_scan_kernel(JpegArgs a) {
 // four in practice).  Prefix sums over the parts' block counts and DC differences then say in
 // which part each row of MCUs starts, and a lane per row walks there from the mark before it.
 //
-// Lanes never wait for each other's blocks: a step is one symbol, DC or AC, with one table look-up
-// and without a branch in the usual case, and the bits come from the data without byte stuffing,
-// so topping up is a select.  1024 files of 256 pixels: 1.0 ms, about 1500 steps of some 100
-// instructions on one wavefront per SIMD, bound by their issue and latency (the walk by one lane
-// per file: 12.7 ms).
-constexpr int kStepsPerFeed = 8;  // symbols of at most 31 bits between two points at which a ring is fed
+// The bits come from the data without byte stuffing, so topping up is a select.  1024 files of 256
+// pixels: 0.65 ms, on one wavefront per SIMD, bound by the steps' issue and latency (with DC and AC
+// symbols and the blocks' ends all in one step of 100 instructions 1.05 ms, by one lane per file
+// 12.7 ms).
 constexpr int kMarks = 3;         // block boundaries remembered inside a part (at each quarter)
-constexpr int kLongCodes = 512;   // entries for codes beyond the direct part of a table
-constexpr int kDirect = 1 << kFastBits;
-constexpr int kAcEntries = kDirect + kLongCodes;
-constexpr int kSyncTable = 2 * kAcEntries + 2 * kDirect;
 
 // A block boundary of a walk and what came before it in the part.
 struct alignas(16) WalkMark {
@@ -1111,20 +1195,11 @@ struct alignas(16) WalkMark {
   uint16_t pad;
 };
 struct JpegSyncLds {
-  // symbol of a code: size of the value (bits 0-3) | how far the coefficient index moves
-  // (bits 4-10, 64 = end of the block) | code length (bits 11-15); 0 = look it up in the ranges.
-  // AC luma, AC chroma, DC luma, DC chroma.
-  uint16_t table[kSyncTable];
+  uint16_t table[kCoefTable];
   uint32_t ring[kRingBytes / 4][kJpegThreads];  // big-endian dwords of the data
   WalkMark mark[kMarks + 1][kJpegThreads];      // [0]: the entry; bit -1 = none
   int first_block[kJpegThreads], dc[3][kJpegThreads];
 };
-__device__ static inline uint16_t ac_entry(int len, int rs) {
-  const int size = rs & 15, run = rs >> 4;
-  const int move = size ? run + 1 : (run == 15 ? 16 : 64);
-  return (uint16_t)((len << 11) | (move << 4) | size);
-}
-
 // Reads the data of one image, a bit position at a time.  (hi:lo) >> left are the next 32 bits.
 struct CleanReader {
   const uint8_t* clean;
@@ -1161,6 +1236,11 @@ __device__ static __forceinline__ void clean_accept(CleanReader& r) {
 }
 __device__ static __forceinline__ void clean_feed(CleanReader& r) {
   if (r.pending) clean_accept(r);
+#pragma unroll 1
+  while (r.have - r.taken < kAhead) {
+    clean_request(r);
+    clean_accept(r);
+  }
   // the 8 dwords to come replace those 32 back, which must have been taken
   if (r.have - r.taken <= kRingBytes / 4 - 8) clean_request(r);
 }
@@ -1169,7 +1249,7 @@ __device__ static __forceinline__ void clean_open(CleanReader& r, int bit) {
   r.left = -bit & 31;
   r.have = w & ~7;
 #pragma unroll 1
-  for (int j = 0; j < 3; ++j) {  // 15 dwords ahead at least: enough for kStepsPerFeed symbols
+  for (int j = 0; j < 3; ++j) {  // (the first feed comes after one DC symbol)
     clean_request(r);
     clean_accept(r);
   }
@@ -1193,36 +1273,8 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
   const int my0 = im->my0, nrows = min(im->nrows, a.max_rows);
   const int row_blocks = im->mcux * per_mcu;
   const int ncols = im->mx1 - im->mx0 + 1, sub = pieces_per_row(nrows, ncols);
-  uint32_t ac_limit[2];
-  for (int t = 0; t < 2; ++t) {
-    const HuffAc& h = im->ac[t];
-    const HuffDc& g = im->dc[t];
-    ac_limit[t] = h.range[kFastBits - 1].limit;
-    uint16_t* table = s.table + t * kAcEntries;
-    for (int i = lane; i < kDirect; i += kJpegThreads) {
-      const int e = h.fast[i];
-      table[i] = e ? ac_entry(e >> 8, e & 255) : (uint16_t)0;
-    }
-    // the codes that follow the direct part, one entry per value of the 16 bits; the last entry
-    // stands for all further ones
-    for (int i = lane; i < kLongCodes; i += kJpegThreads) {
-      const uint32_t x = ac_limit[t] + (uint32_t)i;
-      uint16_t e = 0;
-      if (i < kLongCodes - 1 && x <= 0xFFFFu) {
-        int index;
-        const int len = find_code<kFastBits>(h.range, x, index);
-        if (len < 16) e = ac_entry(len + 1, h.symbols[index & 255]);
-      }
-      table[kDirect + i] = e;
-    }
-    table = s.table + 2 * kAcEntries + t * kDirect;
-    for (int i = lane; i < kDirect; i += kJpegThreads) {
-      int index;
-      const int len = find_code<0>(g.range, (uint32_t)i << (16 - kFastBits), index);
-      const int sym = len < kFastBits ? g.symbols[index & 15] : 16;
-      table[i] = sym <= 11 ? (uint16_t)(((len + 1) << 11) | (1 << 4) | sym) : (uint16_t)0;
-    }
-  }
+  const uint32_t limit_y = long_from(im->ac[0]), limit_c = long_from(im->ac[1]);
+  coef_tables(*im, s.table);
   for (int i = 0; i <= kMarks; ++i) s.mark[i][lane].bit = -1;
   __syncthreads();
 
@@ -1343,63 +1395,29 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
     go = go && bit < end && limit > 0;
     if (go) {
       clean_open(r, bit);
-      int k = 0;
+      int k = 64, ac = 0, round = 0;  // (as behind a block before the first)
+      uint32_t e = 0, ac_limit = 0;
+      bool is_chroma = false;
+      done = -1;
+      phase = phase == 0 ? last_phase : phase - 1;
       while (go) {
-        clean_feed(r);
-#pragma unroll 1
-        for (int i = 0; i < kStepsPerFeed && go; ++i) {
-          const uint32_t ahead = r.ring[(r.taken & (kRingBytes / 4 - 1)) * kJpegThreads];
-          const uint32_t top = __builtin_amdgcn_alignbit(r.hi, r.lo, (uint32_t)r.left);
-          const uint32_t x = top >> 16;
-          const bool is_chroma = phase >= nblk, is_dc = k == 0;
-          uint32_t limit16 = is_chroma ? ac_limit[1] : ac_limit[0];
-          limit16 = is_dc ? 0x10000u : limit16;
-          uint32_t at = is_dc ? 2u * kAcEntries : 0u;
-          at += is_chroma ? (is_dc ? (uint32_t)kDirect : (uint32_t)kAcEntries) : 0u;
-          at += x < limit16 ? x >> (16 - kFastBits)
-                            : (uint32_t)kDirect + min(x - limit16, kLongCodes - 1u);
-          uint32_t e = s.table[at];
-          if (__builtin_expect(e == 0u, 0)) {
-            int index;
-            if (is_dc) {
-              const HuffDc& h = im->dc[is_chroma];
-              const int len = find_code<0>(h.range, x, index);
-              const int sym = len < 16 ? h.symbols[index & 15] : 16;
-              if (sym <= 11) e = (uint32_t)(((len + 1) << 11) | (1 << 4) | sym);
-            } else {
-              const HuffAc& h = im->ac[is_chroma];
-              const int len = find_code<kFastBits>(h.range, x, index);
-              if (len < 16) e = ac_entry(len + 1, h.symbols[index & 255]);
-            }
-            if (!e) {
-              walk_bad = min(walk_bad, done);
-              e = (1u << 11) | (64u << 4);
-            }
-          }
-          const int size = (int)(e & 15u), len = (int)(e >> 11);
-          // DC difference (no value bits: zero)
-          const uint32_t field = (top << len) & ~(0xFFFFFFFFu >> size);
-          int diff = (int)(field >> ((32 - size) & 31));
-          diff += (int)field >= 0 ? 1 - (1 << size) : 0;
-          diff = is_dc ? diff : 0;
-          sum0 += is_chroma ? 0 : diff;
-          sum1 += phase == nblk ? diff : 0;
-          sum2 += phase == last_phase ? diff : 0;
-          k += (int)((e >> 4) & 127u);
-          walk_bad = size != 0 && k > 64 ? min(walk_bad, done) : walk_bad;
-          r.left -= len + size;
-          const bool top_up = r.left < 0;
-          r.hi = top_up ? r.lo : r.hi;
-          r.lo = top_up ? ahead : r.lo;
-          r.taken += top_up ? 1 : 0;
-          r.left &= 31;
-          const bool ends = k >= 64;
-          k = ends ? 0 : k;
-          done += ends ? 1 : 0;
-          phase = ends ? (phase == last_phase ? 0 : phase + 1) : phase;
+        if (__builtin_expect(k >= 64 && e == kMiss, 0)) {
+          int index;
+          const HuffAc& h = im->ac[is_chroma];
+          const uint32_t ahead = sym_ahead(r), top = sym_top(r);
+          const int len = find_code<0>(h.range, top >> 16, index);
+          walk_bad = len < 16 ? walk_bad : min(walk_bad, done);
+          e = len < 16 ? coef_entry(len + 1, h.symbols[index & 255]) : kNoCode;
+          k += (int)((e >> 4) & 63u) - 63;
+          sym_skip(r, (int)(e >> 10), ahead);
+        }
+        if (k >= 64) {
+          if ((e & 15u) != 0u && k > 64) walk_bad = min(walk_bad, done);
+          ++done;
+          phase = phase == last_phase ? 0 : phase + 1;
           const int now = clean_bit(r);
-          go = !ends || (now < end && done < limit);
-          if (ends && now >= mark_at) {
+          go = done == 0 || (now < end && done < limit);
+          if (done > 0 && now >= mark_at) {
             // the first block boundary at or behind one or more of the part's quarters
             WalkMark& m = s.mark[next_mark][lane];
             const WalkMark old = m;
@@ -1439,6 +1457,49 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
               }
               if (next_mark > kMarks) mark_at = kNever;
             }
+          }
+          if (go) {  // the next block's DC difference
+            is_chroma = phase >= nblk;
+            ac_limit = is_chroma ? limit_c : limit_y;
+            ac = is_chroma ? kCoefAc : 0;
+            const uint32_t ahead = sym_ahead(r), top = sym_top(r);
+            uint32_t d =
+                s.table[2 * kCoefAc + (is_chroma ? 1 << kDcBits : 0) + (int)(top >> (32 - kDcBits))];
+            k = 1;
+            e = 0;
+            if (__builtin_expect(d == kMiss, 0)) {
+              int index;
+              const HuffDc& h = im->dc[is_chroma];
+              const int len = find_code<0>(h.range, top >> 16, index);
+              const int sym = len < 16 ? h.symbols[index & 15] : 16;
+              d = kNoCode;
+              if (sym <= 11) {
+                d = coef_entry(len + 1, sym);
+              } else {
+                walk_bad = min(walk_bad, done);
+                k = 64;
+              }
+            }
+            const int size = (int)(d & 15u), off = (int)(d >> 10);
+            const int diff = symbol_value(top, off, size);
+            sym_skip(r, off, ahead);
+            sum0 += is_chroma ? 0 : diff;
+            sum1 += phase == nblk ? diff : 0;
+            sum2 += phase == last_phase ? diff : 0;
+          }
+        }
+        if (!go) break;
+        if (round == 0) clean_feed(r);
+        round = round + 1 == kRounds ? 0 : round + 1;
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) {
+          if (k < 64) {
+            const uint32_t ahead = sym_ahead(r), top = sym_top(r);
+            const uint32_t beyond = __builtin_elementwise_sub_sat(top >> 16, ac_limit);
+            e = s.table[(uint32_t)ac + min(top >> (32 - kFastBits), ac_limit >> (16 - kFastBits)) +
+                        beyond];
+            k += (int)((e >> 4) & 63u);
+            sym_skip(r, (int)(e >> 10), ahead);
           }
         }
       }
@@ -1641,23 +1702,6 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_decode_kernel(JpegArgs a) {
 // 0.45 ms for the inverse transform and colours (entropy decoding and transform by the same lanes,
 // block after block, as in jpeg_decode_kernel: 1.42 ms and 0.20 ms for the colours); 1024 files without
 // markers, rows in pieces: 0.22 + 0.12 ms (1.34 + 0.04 ms).
-constexpr int kSteps = 6;    // AC symbols of at most 31 bits between two points that all lanes pass
-constexpr int kRounds = 2;   // such points between two at which file bytes are taken
-constexpr int kAhead = 8 * kRounds;  // dwords in the ring then: kSteps symbols and two more, twice
-constexpr int kDcBits = 8;
-// direct part, then (from entry limit / 64 on) one entry per value of the 16 bits from `limit` on
-constexpr int kCoefAc = kAcEntries;
-constexpr int kCoefTable = 2 * kCoefAc + (2 << kDcBits);
-// An entry: size of the value (bits 0-3) | how far the coefficient index moves (bits 4-9; 63 from any
-// index ends the block) | 32 - bits of code and value (bits 10-15).  kMiss, for a code that is not in
-// the table, uses no bits and parks the lane at the end of a block, where the code is looked up.
-constexpr uint32_t kMiss = (32u << 10) | (63u << 4);
-__device__ static inline uint32_t coef_entry(int len, int rs) {
-  const int size = rs & 15, run = rs >> 4;
-  const int move = size ? run + 1 : (run == 15 ? 16 : 63);
-  return (uint32_t)(((32 - len - size) << 10) | (move << 4) | size);
-}
-
 struct SymbolReader {
   const uint8_t* chunks;  // as in BitReader
   int64_t chunks_bytes;
@@ -1745,34 +1789,6 @@ __device__ static __forceinline__ void sym_open(SymbolReader& r, const RowState&
   r.lo = r.ring[(r.taken - 1) * kJpegThreads];
 }
 
-// Where the second part of an AC table starts: behind the codes of up to kFastBits bits, or later if
-// what follows is too much for it (codes in between have no entry and are looked up in the ranges).
-__device__ static inline uint32_t long_from(const HuffAc& h) {
-  return min(max(h.range[kFastBits - 1].limit, 65536u - kLongCodes), 65536u);  // (any file's table)
-}
-// The next 32 bits; 32 - `off` of them used.
-__device__ static __forceinline__ uint32_t sym_top(const SymbolReader& r) {
-  return __builtin_amdgcn_alignbit(r.hi, r.lo, (uint32_t)r.left);
-}
-__device__ static __forceinline__ void sym_skip(SymbolReader& r, int off, uint32_t ahead) {
-  const int sum = r.left + off;  // below 32: the dword in `hi` is used up
-  const bool top_up = sum < 32;
-  r.hi = top_up ? r.lo : r.hi;
-  r.lo = top_up ? ahead : r.lo;
-  r.taken += top_up ? 1 : 0;
-  r.left = sum & 31;
-}
-__device__ static __forceinline__ uint32_t sym_ahead(const SymbolReader& r) {
-  return r.ring[(r.taken & (kRingBytes / 4 - 1)) * kJpegThreads];
-}
-// `size` value bits that end `off` bits above the lowest, as the signed value they stand for (T.81
-// F.2.2.1: the lower half of the range is the negative numbers); 0 for none.
-__device__ static __forceinline__ int symbol_value(uint32_t top, int off, int size) {
-  const int v = (int)__builtin_amdgcn_ubfe(top, (uint32_t)off, (uint32_t)size);
-  const int most = (1 << size) - 1;
-  return 2 * v <= most ? v - most : v;
-}
-
 template <int kGroup>
 struct JpegEntropyLds {
   uint16_t table[kGroup * kCoefTable];  // per image AC luma, AC chroma, DC luma, DC chroma
@@ -1798,35 +1814,7 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_entropy_kernel(JpegArgs a) 
     }
     first_task[i + 1] = first_task[i] + rows;
     if (rows == 0) continue;
-    for (int t = 0; t < 2; ++t) {
-      const HuffAc& h = prepared[i].im.ac[t];
-      const HuffDc& g = prepared[i].im.dc[t];
-      const uint32_t limit = long_from(h);
-      uint16_t* table = s.table + i * kCoefTable + t * kCoefAc;
-      const int direct = (int)(limit >> (16 - kFastBits));
-#pragma unroll 4
-      for (int j = lane; j < kDirect; j += kJpegThreads) {
-        const int e = h.fast[j];
-        if (j < direct) table[j] = (uint16_t)(e ? coef_entry(e >> 8, e & 255) : kMiss);
-      }
-      for (int j = lane; j < kLongCodes; j += kJpegThreads) {
-        const uint32_t x = limit + (uint32_t)j;
-        uint32_t e = kMiss;
-        if (x <= 0xFFFFu) {
-          int index;
-          const int len = find_code<kFastBits>(h.range, x, index);
-          if (len < 16) e = coef_entry(len + 1, h.symbols[index & 255]);
-        }
-        table[direct + j] = (uint16_t)e;
-      }
-      table = s.table + i * kCoefTable + 2 * kCoefAc + (t << kDcBits);
-      for (int j = lane; j < (1 << kDcBits); j += kJpegThreads) {
-        int index;
-        const int len = find_code<0>(g.range, (uint32_t)j << (16 - kDcBits), index);
-        const int sym = len < kDcBits ? g.symbols[index & 15] : 16;
-        table[j] = (uint16_t)(sym <= 11 ? coef_entry(len + 1, sym) : kMiss);
-      }
-    }
+    coef_tables(prepared[i].im, s.table + i * kCoefTable);
   }
   __syncthreads();
   const int ntasks = first_task[kGroup];
