@@ -1699,9 +1699,9 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_decode_kernel(JpegArgs a) {
 // will be, which is cleared once they are behind.
 // The file's bytes lose their stuffing on the way into the ring (SymbolReader): topping up
 // the bit buffer is then a select.  4096 files of 256 pixels with a restart interval per row: 0.80 ms and
-// 0.45 ms for the inverse transform and colours (entropy decoding and transform by the same lanes,
+// 0.34 ms for the inverse transform and colours (entropy decoding and transform by the same lanes,
 // block after block, as in jpeg_decode_kernel: 1.42 ms and 0.20 ms for the colours); 1024 files without
-// markers, rows in pieces: 0.22 + 0.12 ms (1.34 + 0.04 ms).
+// markers, rows in pieces: 0.22 + 0.09 ms (1.34 + 0.04 ms).
 struct SymbolReader {
   const uint8_t* chunks;  // as in BitReader
   int64_t chunks_bytes;
@@ -1990,6 +1990,42 @@ __device__ static inline uint32_t repeat2(uint32_t c) {
   return (c & 0xFFu) * 0x0101u | (c >> 8) * 0x01010000u;
 }
 
+// Two 16-bit values saturated to bytes 0 .. 255: bytes 0 and 1 of the result.
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ static inline uint32_t saturate2(uint32_t v) {
+  uint32_t r;
+  asm("v_sat_pk_u8_i16 %0, %1" : "=v"(r) : "v"(v));
+  return r;
+}
+__device__ static inline uint32_t add2(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, a) + __builtin_bit_cast(u16x2, b));
+}
+// What a chroma sample adds to its pixels (ycc_to_rgbx), each twice as 16-bit values.
+struct ChromaTerms {
+  uint32_t r, g, b;
+};
+__device__ static inline ChromaTerms chroma_terms(int cb, int cr) {
+  const int b = cb - 128, r = cr - 128;
+  const int rt = (91881 * r + 32768) >> 16, bt = (116130 * b + 32768) >> 16;
+  const int gt = -((22554 * b + 46802 * r + 32768) >> 16);
+  return {(uint32_t)(rt & 0xFFFF) * 0x10001u, (uint32_t)(gt & 0xFFFF) * 0x10001u,
+          (uint32_t)(bt & 0xFFFF) * 0x10001u};
+}
+// Four pixels of which each two share a chroma sample, two values per instruction.
+__device__ static inline void store_rgb4_pairs(uint8_t* dst, uint32_t yy, const ChromaTerms& c0,
+                                               const ChromaTerms& c1) {
+  const uint32_t y01 = __builtin_amdgcn_perm(0u, yy, 0x0c010c00u);
+  const uint32_t y23 = __builtin_amdgcn_perm(0u, yy, 0x0c030c02u);
+  // bytes R0 R1 G0 G1 / B0 B1, and the same for pixels 2, 3
+  const uint32_t rg01 = saturate2(add2(y01, c0.r)) | saturate2(add2(y01, c0.g)) << 16;
+  const uint32_t rg23 = saturate2(add2(y23, c1.r)) | saturate2(add2(y23, c1.g)) << 16;
+  const uint32_t b01 = saturate2(add2(y01, c0.b)), b23 = saturate2(add2(y23, c1.b));
+  const uint32_t g1b1 = __builtin_amdgcn_perm(b01, rg01, 0x0c0c0503u);
+  const uint32_t r2g2 = __builtin_amdgcn_perm(0u, rg23, 0x02000c0cu);
+  *reinterpret_cast<u32x3_a4*>(dst) = u32x3{__builtin_amdgcn_perm(b01, rg01, 0x01040200u), g1b1 | r2g2,
+                                            __builtin_amdgcn_perm(b23, rg23, 0x05030104u)};
+}
+
 // Coefficients or planes -> interleaved RGB, the region's rows as the resampling kernel reads them.
 // A workgroup takes 192 blocks of an image at a time, one per lane: 32 MCUs with 4:2:0 sampling (two
 // wavefronts of luma, one of chroma) or 64 with 4:4:4 (a wavefront per component), so that a
@@ -1997,7 +2033,8 @@ __device__ static inline uint32_t repeat2(uint32_t c) {
 // (zig-zag order is then free); its even and odd halves are summed apart and give two outputs each,
 // which halves the products (sums of the same integers: nothing changes in the result).  The samples
 // meet in LDS, from where four pixels per lane and step are converted and stored along the rows.
-// Bound by vector instructions, about 2400 per 64 blocks, of which the transform is half.
+// Bound by vector instructions, half of them the transform; the bytes are taken two per instruction where
+// they fit 16 bits (4096 files of 256 pixels: 0.34 ms, with a 32-bit clamp and shift per value 0.45).
 // Images that jpeg_decode_kernel has decoded have planes instead of coefficients.
 constexpr int kIdctThreads = 3 * kWave;
 constexpr int kIdctStride = 72;   // bytes per block of samples: 64 and a pad against bank conflicts
@@ -2062,13 +2099,18 @@ __device__ static inline void idct_block(const u32x4_c raw[8], int qz, uint8_t* 
       const int u = (i & 1) * 4 + (i >> 1);
       in[i] = s16x2{(short)t[y * 8 + u], (short)t[y * 8 + u + 2]};
     }
+    // (v + 2^16 >> 17) + 128, clamped: the high halves two at a time, one more bit, saturated (the sums
+    // stay below 2^31 with the 128 among them)
     int v[8];
-    idct_line(in, 1 << 16, v);
+    idct_line(in, (1 << 16) + (128 << 17), v);
+    uint32_t two[4];
 #pragma unroll
-    for (int x = 0; x < 8; ++x) v[x] = min(max((v[x] >> 17) + 128, 0), 255);
-    *reinterpret_cast<u32x2*>(samples + 8 * y) =
-        u32x2{(uint32_t)v[0] | ((uint32_t)v[1] << 8) | ((uint32_t)v[2] << 16) | ((uint32_t)v[3] << 24),
-              (uint32_t)v[4] | ((uint32_t)v[5] << 8) | ((uint32_t)v[6] << 16) | ((uint32_t)v[7] << 24)};
+    for (int x = 0; x < 4; ++x) {
+      const uint32_t high =
+          __builtin_amdgcn_perm((uint32_t)v[2 * x + 1], (uint32_t)v[2 * x], 0x07060302u);
+      two[x] = saturate2(__builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, high) >> (short)1));
+    }
+    *reinterpret_cast<u32x2*>(samples + 8 * y) = u32x2{two[0] | two[1] << 16, two[2] | two[3] << 16};
   }
 }
 
@@ -2152,26 +2194,30 @@ __global__ __launch_bounds__(kIdctThreads) void jpeg_idct_kernel(JpegArgs a, int
     __syncthreads();
     idct_block(raw, qz, samples + threadIdx.x * kIdctStride);
     __syncthreads();
-    // 128 pieces of four pixels per row of the group's MCUs
-    for (int i = (int)threadIdx.x; i < 128 * mcu; i += kIdctThreads) {
-      const int y = i >> 7, r = i & 127;
+    // 128 pieces of four pixels per row of the group's MCUs; with 4:2:0 a lane takes two rows, which
+    // share their chroma samples
+    for (int i = (int)threadIdx.x; i < 128 * 8; i += kIdctThreads) {
+      const int y = (i >> 7) * hs, r = i & 127;
       const int pm = r >> hs, piece = r & (2 * hs - 1);
       if (m0 + pm >= nmcu) continue;
-      uint32_t yy, cb, cr;
+      uint8_t* dst = region + (place[pm] + (uint32_t)((y * region_w + 4 * piece) * 3));
       if (hs == 2) {
         const int luma = 4 * pm + (y >> 3) * 2 + (piece >> 1), chroma = 128 + 2 * pm;
-        yy = *reinterpret_cast<const uint32_t*>(samples + luma * kIdctStride + (y & 7) * 8 +
-                                                4 * (piece & 1));
+        const uint32_t* yy = reinterpret_cast<const uint32_t*>(samples + luma * kIdctStride +
+                                                               (y & 7) * 8 + 4 * (piece & 1));
         const uint8_t* c = samples + chroma * kIdctStride + (y >> 1) * 8 + 2 * piece;
-        cb = repeat2(*reinterpret_cast<const uint16_t*>(c));
-        cr = repeat2(*reinterpret_cast<const uint16_t*>(c + kIdctStride));
+        const uint32_t cb = *reinterpret_cast<const uint16_t*>(c);
+        const uint32_t cr = *reinterpret_cast<const uint16_t*>(c + kIdctStride);
+        const ChromaTerms c0 = chroma_terms((int)(cb & 0xFFu), (int)(cr & 0xFFu));
+        const ChromaTerms c1 = chroma_terms((int)(cb >> 8), (int)(cr >> 8));
+        store_rgb4_pairs(dst, yy[0], c0, c1);
+        store_rgb4_pairs(dst + 3 * region_w, yy[2], c0, c1);
       } else {
         const uint8_t* s = samples + pm * kIdctStride + y * 8 + 4 * piece;
-        yy = *reinterpret_cast<const uint32_t*>(s);
-        cb = *reinterpret_cast<const uint32_t*>(s + kWave * kIdctStride);
-        cr = *reinterpret_cast<const uint32_t*>(s + 2 * kWave * kIdctStride);
+        store_rgb4(dst, *reinterpret_cast<const uint32_t*>(s),
+                   *reinterpret_cast<const uint32_t*>(s + kWave * kIdctStride),
+                   *reinterpret_cast<const uint32_t*>(s + 2 * kWave * kIdctStride));
       }
-      store_rgb4(region + (place[pm] + (uint32_t)((y * region_w + 4 * piece) * 3)), yy, cb, cr);
     }
     __syncthreads();
   }
