@@ -206,7 +206,7 @@ def mae_stage_of_epoch(epoch: int, lengths) -> int:
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _check(t, name, dtypes=None, numel=None, optional=False):
@@ -222,16 +222,21 @@ def _check(t, name, dtypes=None, numel=None, optional=False):
         raise ValueError(f"{name} must live in device memory")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if dtypes is not None and t.dtype not in (dtypes if isinstance(dtypes, tuple) else (dtypes,)):
+    if dtypes is not None and t.dtype is not dtypes and \
+            not (isinstance(dtypes, tuple) and t.dtype in dtypes):
         raise TypeError(f"{name} has dtype {t.dtype}, expected {dtypes}")
     if numel is not None and t.numel() < numel:
         raise ValueError(f"{name} holds {t.numel()} elements, {numel} are needed")
 
 
 def _stream(stream):
+    # (the current stream's handle alone: a Stream object around it costs more than a launch)
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
+
+
+_Float3 = C.c_float * 3
 
 
 def make_prep_desc(images, offsets, heights, widths, *, out_size, patch, num_keep,
@@ -244,32 +249,31 @@ def make_prep_desc(images, offsets, heights, widths, *, out_size, patch, num_kee
     (int32); heights and widths are then ignored (pass None).  row_index: what mae_jpeg_index
     wrote for these files with the same max_image_side (uint8 tensor), or None."""
     _check(images, "images", torch.uint8)
-    _check(offsets, "offsets", torch.int64)
     if file_sizes is None:
         _check(heights, "heights", torch.int32)
-        _check(widths, "widths", torch.int32, numel=heights.numel())
-        _check(offsets, "offsets", torch.int64, numel=heights.numel())
+        B = heights.numel()
+        _check(widths, "widths", torch.int32, numel=B)
     else:
         _check(file_sizes, "file_sizes", torch.int32)
-        _check(offsets, "offsets", torch.int64, numel=file_sizes.numel())
+        B = file_sizes.numel()
+    _check(offsets, "offsets", torch.int64, numel=B)
     d = MaePrepDesc()
     d.images = images.data_ptr()
-    d.images_bytes = int(images.numel())
+    d.images_bytes = images.numel()
     d.offsets = offsets.data_ptr()
+    d.B = B
     if file_sizes is None:
-        d.B = int(heights.numel())
         d.heights, d.widths = heights.data_ptr(), widths.data_ptr()
         d.input_format = MAE_INPUT_DECODED
     else:
-        d.B = int(file_sizes.numel())
         d.file_sizes = file_sizes.data_ptr()
         d.input_format = MAE_INPUT_JPEG
     d.out_size, d.patch, d.num_keep = out_size, patch, num_keep
     d.scale_lo, d.scale_hi = scale
     d.ratio_lo, d.ratio_hi = ratio
     d.flip_p = flip_p
-    d.mean = (C.c_float * 3)(*mean)
-    d.std = (C.c_float * 3)(*std)
+    d.mean = _Float3(*mean)
+    d.std = _Float3(*std)
     d.seed, d.batch_index, d.sample_base = seed, batch_index, sample_base
     d.noise_bits, d.out_dtype = noise_bits, out_dtype
     d.max_image_side = max_image_side
@@ -341,7 +345,7 @@ def make_loss_desc(pred, target, mask, *, num_masked, eps=1e-6, grad_scale=1.0,
     _check(target, "target", torch.float32, numel=pred.numel(), optional=True)
     _check(mask, "mask", torch.uint8, numel=pred.shape[0] * pred.shape[1])
     d = MaeLossDesc()
-    d.B, d.L, d.D = (int(v) for v in pred.shape)
+    d.B, d.L, d.D = pred.shape
     d.pred, d.target, d.mask = pred.data_ptr(), _ptr(target), mask.data_ptr()
     d.num_masked = int(num_masked)
     d.eps, d.grad_scale = eps, grad_scale
