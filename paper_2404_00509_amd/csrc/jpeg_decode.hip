@@ -505,7 +505,7 @@ struct JpegImage {
   int live;
   int restart, mcux;  // restart interval in MCUs (0 = none), MCUs per row of the image
   // bytes of entropy-coded data in the image's slot of the region buffer, byte stuffing removed
-  // (see jpeg_unstuff); -1 = not there
+  // (see jpeg_unstuff), + kCutShort where the file ends without a marker behind them; -1 = not there
   int clean_bytes;
   int64_t origin, region_off;
 };
@@ -550,6 +550,7 @@ __device__ static inline bool clean_fits(const JpegArgs& a, int size, int scan_o
                                 (int64_t)a.slot_side * a.slot_side * 3;
 }
 constexpr int kCleanStep = kJpegThreads * 16;  // bytes of the file per step
+constexpr int kCutShort = 1 << 30;             // (beyond any number of bytes that fits)
 
 // The walk over a file that is one chain of codes can also tell where each of several pieces of the
 // crop's rows starts, so that a row is several lanes' work: as many pieces as fill a wavefront (four
@@ -570,8 +571,8 @@ __device__ static inline bool pieces_fit(const JpegArgs& a, int size, int scan_o
 }
 
 // Entropy-coded data from scan_off to the first marker, byte stuffing removed, into `clean`, with
-// the file position of every 16th byte in `map`; returns how many bytes (whole wavefront).  The
-// file is read in aligned 16-byte pieces, one per lane, the next step's in flight; a prefix sum
+// the file position of every 16th byte in `map`; returns how many bytes, + kCutShort when the file
+// ends before a marker does it (whole wavefront).  The file is read in aligned 16-byte pieces, one per lane, the next step's in flight; a prefix sum
 // gives each piece its place in the LDS buffer, which leaves in 1-KiB stores.
 __device__ static int jpeg_unstuff(const JpegArgs& a, int64_t origin, int scan_off, int n,
                                    uint8_t* stage, uint8_t* clean, int32_t* map) {
@@ -581,6 +582,7 @@ __device__ static int jpeg_unstuff(const JpegArgs& a, int64_t origin, int scan_o
   const int64_t end = origin + n;
   int done = 0, fill = 0;  // bytes stored / bytes waiting in `stage`
   uint32_t carry = 0;      // last byte of the step before
+  int cut = kCutShort;
   u32x4_a8 cur = load_chunk(a.files, a.files_bytes, first + lane * 16);
   for (int64_t base = first; base < end; base += kCleanStep) {
     const int64_t at = base + lane * 16;
@@ -642,13 +644,16 @@ __device__ static int jpeg_unstuff(const JpegArgs& a, int64_t origin, int scan_o
       fill -= kCleanStep;
       __syncthreads();
     }
-    if (stops) break;
+    if (stops) {
+      cut = 0;
+      break;
+    }
     carry = (uint32_t)__shfl((int)(cur.w >> 24), kJpegThreads - 1);
     cur = next;
   }
   if (lane * 16 < fill)
     reinterpret_cast<u32x4*>(clean + done)[lane] = reinterpret_cast<u32x4*>(stage)[lane];
-  return done + fill;
+  return done + fill + cut;
 }
 
 // Tables, crop geometry and restart-marker positions of image b into slot `im` (whole wavefront).
@@ -1280,7 +1285,8 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
 
   CleanReader r;
   r.clean = a.regions + im->region_off;
-  r.bytes = im->clean_bytes;
+  r.bytes = im->clean_bytes & (kCutShort - 1);
+  const bool cut_short = (im->clean_bytes & kCutShort) != 0;
   r.ring = &s.ring[0][lane];
   const int bits = 8 * r.bytes;  // below 2^30 (clean_fits)
   const int quarter =
@@ -1295,6 +1301,7 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
   int leave = 0, leave_phase = 0, blocks = 0, bad_at = kNever;
   int dc0 = 0, dc1 = 0, dc2 = 0;
   int first_block = 0, total = 0, row = lane, from = 0;
+  int tail0 = 0, tail1 = 0, tail2 = 0;  // DC differences of an MCU of zero bits
   bool bad = false;
   SyncStage stage = SyncStage::kParts;
   int round = 0;
@@ -1347,7 +1354,8 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
       limit = kNever;
       end = part_end;
     } else if (stage == SyncStage::kTail) {
-      // where the data ends early zero bits follow, block after block the same: one MCU tells
+      // where the data ends early zero bits follow, block after block of a component the same: one
+      // MCU tells
       go = lane == kWave - 1 && total < (my0 + nrows) * row_blocks;
       bit = leave;
       phase = leave_phase;
@@ -1524,12 +1532,37 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
       ++round;
     } else if (stage == SyncStage::kTail) {
       bad = bad || (walk_bad != kNever && total + walk_bad < (my0 + nrows) * row_blocks);
+      tail0 = __shfl(sum0, kWave - 1);
+      tail1 = __shfl(sum1, kWave - 1);
+      tail2 = __shfl(sum2, kWave - 1);
       stage = SyncStage::kRows;
     } else {
-      // with no more than a bit buffer's 32 bits left the data has ended for a row after the first
+      // with no more than a bit buffer's 32 bits left a marker has ended the data for a row after the
+      // first
       const bool piece = stage == SyncStage::kPieces;
       const bool first_row = my0 + row == 0 && !piece;
-      if (asked && (first_row || piece || bits - bit > 32)) {
+      RowState* states = reinterpret_cast<RowState*>(a.row_states) + (int64_t)b * a.max_rows;
+      const int last_leave_phase = __shfl(leave_phase, kWave - 1);
+      const int end0 = s.dc[0][kWave - 1] + __shfl(dc0, kWave - 1);
+      const int end1 = s.dc[1][kWave - 1] + __shfl(dc1, kWave - 1);
+      const int end2 = s.dc[2][kWave - 1] + __shfl(dc2, kWave - 1);
+      if (!asked && !piece && row < nrows && cut_short) {
+        // Behind a file that merely stops: the row is zero bits, and so are the blocks between the last
+        // that the data began and this row's first (the rest of an MCU, then whole ones).
+        const int ph = last_leave_phase, rest = ph ? per_mcu - ph : 0;
+        const int whole = ((my0 + row) * row_blocks - total - rest) / per_mcu;
+        RowState st;
+        st.pos = im->size;
+        st.nbits = 0;
+        st.acc = 0;
+        st.pred[0] = (int16_t)(end0 + whole * tail0 + (ph ? max(nblk - ph, 0) * (tail0 / nblk) : 0));
+        st.pred[1] = (int16_t)(end1 + (whole + (ph && ph <= nblk ? 1 : 0)) * tail1);
+        st.pred[2] = (int16_t)(end2 + (whole + (ph ? 1 : 0)) * tail2);
+        st.rst_left = 0;
+        st.pad = 0;
+        states[row] = st;
+      }
+      if (asked && (first_row || piece || cut_short || bits - bit > 32)) {
         const uint8_t* file = a.files + im->origin;
         const int32_t* map =
             reinterpret_cast<const int32_t*>(r.clean + clean_map_offset(im->size, im->scan_off));
@@ -1546,7 +1579,7 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
         st.rst_left = 0;
         st.pad = 0;
         if (piece) piece_states(a, im->region_off)[lane] = st;
-        else (reinterpret_cast<RowState*>(a.row_states) + (int64_t)b * a.max_rows)[row] = st;
+        else states[row] = st;
       }
       if (piece) {
         if (lane == 0) reinterpret_cast<JpegPrepared*>(a.prepared)[b].im.live = kLivePieces;

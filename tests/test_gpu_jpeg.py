@@ -294,7 +294,7 @@ def test_coefficients_and_planes_in_one_batch(restart_rows):
 
 def test_files_without_markers_whose_data_ends_early():
     """Inside the last row (zero bits follow: rows are then not decoded in pieces), or rows before it
-    (the sample is flagged when its crop wants them)."""
+    (no marker ends the data: the rows behind it are zero bits, too)."""
     one, _, lens = synth.make_jpegs("gradient", 1, seed=69, restart_rows=0)
     cuts = [0, 2, 9, 60, 400, lens[0] // 2]
     chunks = [one[:lens[0] - c] for c in cuts]
@@ -306,11 +306,8 @@ def test_files_without_markers_whose_data_ends_early():
     ref = oracle.prep_batch(*_decode_all(files, offsets, sizes), **kw)
     buf, _ = _gpu_jpeg_prep(files, offsets, sizes, **kw)
     crop = buf.crop.cpu().numpy()
-    assert list(crop[:, 5]) == [1, 1, 1, 1, 1, 0]
-    keep = list(range(5))
-    sel = {k: (v[keep] if v is not None else None) for k, v in ref.items()}
-    check_prep_against_oracle(prep_to_numpy(buf, rows=keep), sel, what="cut files")
-    check_neutral_outputs(buf, 5)
+    assert list(crop[:, 5]) == [1, 1, 1, 1, 1, 1]
+    check_prep_against_oracle(prep_to_numpy(buf), ref, what="cut files")
 
 
 def test_files_of_maximum_side_500():
@@ -566,3 +563,38 @@ def test_row_index_with_large_files_augmentation_and_the_loss_without_target():
     assert abs(loss.item() - ref_loss) <= 1e-5 + 1e-5 * abs(ref_loss)
     from helpers import check_grad
     check_grad(grad.cpu().numpy(), ref_grad, 768, M, what="index + loss from images")
+
+
+def _join(chunks):
+    """Files back to back: (bytes, offsets, sizes)."""
+    sizes = np.array([c.size for c in chunks], np.int32)
+    offsets = np.zeros(len(chunks), np.int64)
+    offsets[1:] = np.cumsum(sizes.astype(np.int64))[:-1]
+    return np.concatenate(chunks), offsets, sizes
+
+
+@pytest.mark.parametrize("indexed", [False, True])
+@pytest.mark.parametrize("sub", ["4:2:0", "4:4:4"])
+def test_files_cut_short_with_and_without_an_end_marker(sub, indexed):
+    """A file that simply stops is decoded with zero bits from there on, as the oracle does, wherever
+    it stops; a file whose data a marker ends before the crop's last row is flagged."""
+    one, _, lens = synth.make_jpegs("gradient", 1, seed=69, restart_rows=0, subsampling=sub)
+    n = int(lens[0])
+    cuts = [n // 2, n // 3, 3 * n // 4, 2000, 1]
+    chunks = [one[:n - c] for c in cuts]
+    eoi = np.array([0xFF, 0xD9], np.uint8)
+    chunks += [np.concatenate([one[:n - c], eoi]) for c in cuts[:3]]
+    files, offsets, sizes = _join(chunks)
+    kw = dict(out_size=96, patch=16, num_keep=9, scale=(1.0, 1.0), ratio=(1.0, 1.0), seed=25)
+    ref = oracle.prep_batch(*_decode_all(files, offsets, sizes), **kw)
+    if indexed:
+        index, dev = _row_index(files, offsets, sizes)
+        buf = _prep_with_index(dev, index, **kw)
+    else:
+        buf, _ = _gpu_jpeg_prep(files, offsets, sizes, **kw)
+    assert buf.crop[:, 5].tolist() == [1] * len(cuts) + [0] * 3
+    keep = list(range(len(cuts)))
+    sel = {k: (v[keep] if v is not None else None) for k, v in ref.items()}
+    check_prep_against_oracle(prep_to_numpy(buf, rows=keep), sel, what="cut files")
+    for b in range(len(cuts), len(chunks)):
+        check_neutral_outputs(buf, b)
