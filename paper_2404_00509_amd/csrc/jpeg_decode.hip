@@ -223,6 +223,7 @@ struct BitReader {
   u32x4_a8 next[2];
   uint64_t acc;  // the low nbits bits are the unread ones, oldest on top
   int nbits;
+  int zeros;   // bits put into acc behind the end of the data
   bool ended;  // a marker was reached: zero bits from here on
 };
 
@@ -277,6 +278,7 @@ __device__ static __forceinline__ void open_reader(BitReader& r, int start) {
   r.pending = false;
   r.acc = 0;
   r.nbits = 0;
+  r.zeros = 0;
   if (!r.ended) {
     need_bytes(r, start, 4);
     request_bytes(r);
@@ -357,6 +359,7 @@ __device__ static __forceinline__ void fill(BitReader& r) {
 __device__ static __forceinline__ void fill_bytewise(BitReader& r) {
   while (r.nbits <= 32) {
     uint32_t byte = 0;
+    const int from = r.pos;
     if (!r.ended && r.pos < r.n) {
       byte = file_byte(r, r.pos);
       if (byte == 0xFF) {
@@ -372,7 +375,15 @@ __device__ static __forceinline__ void fill_bytewise(BitReader& r) {
     }
     r.acc = (r.acc << 8) | byte;
     r.nbits += 8;
+    r.zeros += r.pos == from ? 8 : 0;
   }
+}
+// Whether a row of MCUs can start where `left` bits of its data are unread, the last of them in
+// `last`: a marker that ends the data comes behind up to seven one-bits of padding (T.81 F.1.2.3),
+// and no code consists of ones alone, so such a rest holds none.
+__device__ static inline bool row_can_start(int left, uint32_t last) {
+  const uint32_t rest = (1u << (left & 7)) - 1u;
+  return left >= 8 || (left > 0 && (last & rest) != rest);
 }
 // At a restart boundary: what is left of the interval (the padding of its last byte, fill bytes)
 // is dropped, the marker skipped and the reader opened behind it.  Returns false when no restart
@@ -1056,7 +1067,9 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_scan_kernel(JpegArgs a) {
         st.pred[2] = (int16_t)pred[2];
         st.rst_left = (uint16_t)rst_left;
         st.pad = 0;
-        if (r.ended) st.pos = -1;  // the data ended before this row
+        // (the look-ahead meets the end before the row does)
+        if (r.ended && !row_can_start(r.nbits - r.zeros, (uint32_t)(r.acc >> (r.zeros & 63))))
+          st.pos = -1;  // a marker ended the data before this row
         states[row - im.my0] = st;
       }
       rst_left -= interval ? 1 : 0;
@@ -1537,8 +1550,6 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
       tail2 = __shfl(sum2, kWave - 1);
       stage = SyncStage::kRows;
     } else {
-      // with no more than a bit buffer's 32 bits left a marker has ended the data for a row after the
-      // first
       const bool piece = stage == SyncStage::kPieces;
       const bool first_row = my0 + row == 0 && !piece;
       RowState* states = reinterpret_cast<RowState*>(a.row_states) + (int64_t)b * a.max_rows;
@@ -1562,7 +1573,9 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
         st.pad = 0;
         states[row] = st;
       }
-      if (asked && (first_row || piece || cut_short || bits - bit > 32)) {
+      // (bit < bits: the walk counted this block, or it is the file's first)
+      if (asked && (first_row || piece || cut_short ||
+                    row_can_start(bits - bit, (uint32_t)r.clean[max(r.bytes - 1, 0)]))) {
         const uint8_t* file = a.files + im->origin;
         const int32_t* map =
             reinterpret_cast<const int32_t*>(r.clean + clean_map_offset(im->size, im->scan_off));

@@ -573,6 +573,43 @@ def _join(chunks):
     return np.concatenate(chunks), offsets, sizes
 
 
+def _flat(h, w, value, sub, **kw):
+    import io
+
+    from PIL import Image
+    buf = io.BytesIO()
+    Image.fromarray(np.full((h, w, 3), value, np.uint8)).save(buf, format="JPEG", quality=90,
+                                                             subsampling=sub, **kw)
+    return np.frombuffer(buf.getvalue(), np.uint8)
+
+
+@pytest.mark.parametrize("indexed", [False, True])
+@pytest.mark.parametrize("side", [64, 256])
+def test_last_rows_of_a_few_bits(side, indexed):
+    """A flat row of MCUs is as short as 14 bits (one MCU, 4:4:4, the standard's tables) or less
+    (tables fitted to the file): complete files whose last rows hold fewer bits than the decoder's
+    bit buffer, walked in parallel (no markers), serially (an interval of several rows, in which
+    the last row but one of an interval is as short), and through the index."""
+    shapes = [(24, 8, "4:4:4", {}), (16, 8, "4:4:4", dict(optimize=True)),
+              (32, 32, "4:2:0", dict(optimize=True)), (48, 16, "4:2:0", {}),
+              (40, 16, "4:4:4", dict(optimize=True)), (64, 40, "4:2:0", {})]
+    chunks = [_flat(h, w, value, sub, **kw, **rst) for h, w, sub, kw in shapes
+              for value in (0, 77, 255) for rst in ({}, dict(restart_marker_rows=2))]
+    files, offsets, sizes = _join(chunks)
+    decoded = _decode_all(files, offsets, sizes)
+    for lo, scale in ((0.61, (1.0, 1.0)), (0.75, (0.2, 1.0))):
+        kw = dict(out_size=32, patch=16, num_keep=2, scale=scale, ratio=(lo, 1 / lo), seed=31,
+                  batch_index=2)
+        ref = oracle.prep_batch(*decoded, **kw)
+        if indexed:
+            index, dev = _row_index(files, offsets, sizes, max_image_side=side)
+            buf = _prep_with_index(dev, index, max_image_side=side, **kw)
+        else:
+            buf, _ = _gpu_jpeg_prep(files, offsets, sizes, max_image_side=side, **kw)
+        assert mae.mae_prep_status(buf.workspace) == 0
+        check_prep_against_oracle(prep_to_numpy(buf), ref, what=f"short rows, scale {scale}")
+
+
 @pytest.mark.parametrize("indexed", [False, True])
 @pytest.mark.parametrize("sub", ["4:2:0", "4:4:4"])
 def test_files_cut_short_with_and_without_an_end_marker(sub, indexed):
