@@ -1864,7 +1864,8 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_entropy_kernel(JpegArgs a) 
   }
   __syncthreads();
   const int ntasks = first_task[kGroup];
-  const uint32_t slot_bytes = (uint32_t)(a.slot_side * a.slot_side * 3);
+  // (below 2^32: a side of at most 32768, and one image per group where a slot is that large)
+  const uint32_t slot_bytes = (uint32_t)a.slot_side * (uint32_t)a.slot_side * 3u;
   uint8_t* coefs = a.planes + (int64_t)b0 * slot_bytes;  // (slots follow each other)
 
 #pragma unroll 1
@@ -1902,7 +1903,7 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_entropy_kernel(JpegArgs a) 
     const int table = slot * kCoefTable;
     // byte offsets of the row's first block, and of the current one less one coefficient
     const uint32_t base = (uint32_t)slot * slot_bytes +
-                          (uint32_t)((row * ncols + first) * per_mcu * kBlockBytes);
+                          (uint32_t)(row * ncols + first) * (uint32_t)(per_mcu * kBlockBytes);
     uint32_t out = base - 2;
     // (a row's restart boundary, if any, lies behind its last MCU: a state that says otherwise is
     // not one of this file's)
@@ -2219,7 +2220,7 @@ __global__ __launch_bounds__(kIdctThreads) void jpeg_idct_kernel(JpegArgs a, int
     if ((int)threadIdx.x < group) {
       const int i = min(m0 + (int)threadIdx.x, nmcu - 1);
       const int my = i / ncols, mx = i - my * ncols;
-      place[threadIdx.x] = (uint32_t)((my * mcu * region_w + mx * mcu) * 3);
+      place[threadIdx.x] = ((uint32_t)(my * mcu) * (uint32_t)region_w + (uint32_t)(mx * mcu)) * 3u;
     }
     // the step's blocks lie one after the other in memory: 16 bytes per lane and load
     const u32x4_c* src = reinterpret_cast<const u32x4_c*>(coef + (int64_t)m0 * per_mcu * kBlockBytes);

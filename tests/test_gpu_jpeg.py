@@ -228,6 +228,16 @@ def test_image_shapes_at_the_limits():
         check_prep_against_oracle(prep_to_numpy(buf, rows=keep), sel, what=f"limits {scale}")
 
 
+def test_the_largest_side_limit():
+    """Slots of 32768 x 32768 pixels: the offsets inside one do not fit 31 bits."""
+    files, offsets, sizes = synth.make_jpegs("gradient", 2, seed=75, restart_rows=0)
+    kw = dict(out_size=64, patch=16, num_keep=4, seed=32, batch_index=0)
+    ref = oracle.prep_batch(*_decode_all(files, offsets, sizes), **kw)
+    buf, _ = _gpu_jpeg_prep(files, offsets, sizes, max_image_side=32767, **kw)
+    assert mae.mae_prep_status(buf.workspace) == 0
+    check_prep_against_oracle(prep_to_numpy(buf), ref, what="side limit 32767")
+
+
 def test_files_the_decoder_does_not_take_are_flagged_and_take_no_part():
     import io
 
