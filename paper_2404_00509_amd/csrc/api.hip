@@ -156,12 +156,12 @@ struct PrepWorkspace {
 };
 // Launch plan of the resampling kernel: from the side limit of the decoded-region slots for JPEG
 // input, else from the caller's hint.
+int crop_side_of(const mae_prep_desc* d, int slot_side) {
+  if (d->input_format == MAE_INPUT_JPEG) return slot_side;
+  return d->max_image_side > 0 ? d->max_image_side : 256;
+}
 mae::CropPlan crop_plan_of(const mae_prep_desc* d, int slot_side) {
-  return mae::crop_plan(d->out_size, d->patch,
-                        d->input_format == MAE_INPUT_JPEG
-                            ? slot_side
-                            : (d->max_image_side > 0 ? d->max_image_side : 256),
-                        0);
+  return mae::crop_plan(d->out_size, d->patch, crop_side_of(d, slot_side), 0);
 }
 PrepWorkspace prep_workspace(const mae_prep_desc* d) {
   auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
@@ -254,6 +254,7 @@ mae::CropArgs make_crop_args(const mae_prep_desc* d, const PrepShape& sh, const 
   ca.tile_pixels = plan.tile_pixels;
   ca.col_parts = plan.col_parts;
   ca.part_patches = plan.part_patches;
+  ca.max_side = crop_side_of(d, wsl.slot_side);
   for (int c = 0; c < 3; ++c) {
     ca.nscale[c] = (float)(1.0 / (255.0 * (double)d->std[c]));
     ca.nbias[c] = (float)(-(double)d->mean[c] / (double)d->std[c]);

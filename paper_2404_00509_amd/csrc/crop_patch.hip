@@ -32,6 +32,7 @@
 
 namespace mae {
 
+constexpr int kCropThreads = 256;      // crop_patch_scalar_kernel
 constexpr int kCropMaxThreads = 1024;  // resampling kernel: 64 threads per 64 groups of a patch
 constexpr int kStageRows = 7;  // rows per wavefront whose loads are issued together
 constexpr int kCropMaxLds = 64 * 1024;      // dynamic LDS available without opting in to more
@@ -1146,11 +1147,76 @@ __global__ __launch_bounds__(4 * kWave) void crop_loss_wave_kernel(CropArgs a) {
   crop_band<false, 2>(a, lds);
 }
 
-// ... for odd patch sizes, with or without a target: 64 threads per 64 pixels of a patch
+// ... for odd patch sizes (most of them: crop_pixels_staged), with or without a target: 64 threads
+// per 64 pixels of a patch
 template <bool kBf16>
 __global__ __launch_bounds__(kCropMaxThreads) void crop_pixel_kernel(CropArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
   crop_band<kBf16, -2>(a, lds);
+}
+
+// Odd patch sizes where staging does not pay (crop_pixels_staged below): one output pixel per thread,
+// taps straight from global memory, any number of images.
+template <bool kBf16>
+__global__ __launch_bounds__(kCropThreads) void crop_patch_scalar_kernel(CropArgs a) {
+  // one output pixel (three values) per thread and pass: the taps are worked out once per pixel
+  const int pp = a.p * a.p;
+  const int64_t per_image = (int64_t)a.L * pp;
+  const int64_t total = (int64_t)a.B * per_image;
+  const float inv_den = 1.0f / (float)(2 * a.S);
+  for (int64_t idx = (int64_t)blockIdx.x * kCropThreads + threadIdx.x; idx < total;
+       idx += (int64_t)gridDim.x * kCropThreads) {
+    const int b = (int)(idx / per_image);
+    const int rem = (int)(idx - (int64_t)b * per_image);
+    const CropRec rec = reinterpret_cast<const CropRec*>(a.workspace + kWorkspaceHeader)[b];
+    const int l = rem / pp, q = rem - l * pp;
+    const int64_t to = ((int64_t)b * a.L + l) * a.D + 3 * q;  // the pixel's values in `target`
+    if (!rec.valid) {  // takes no part: zero pixels, nothing masked, identity order
+      const int64_t vo = ((int64_t)b * a.K + l) * a.D + 3 * q;
+      for (int c = 0; c < 3; ++c) {
+        if (a.target) a.target[to + c] = 0.0f;
+        if (l < a.K) {
+          if (kBf16) static_cast<uint16_t*>(a.visible)[vo + c] = 0;
+          else static_cast<float*>(a.visible)[vo + c] = 0.0f;
+        }
+      }
+      if (q == 0) {
+        if (a.mask_out) a.mask_out[(int64_t)b * a.L + l] = 0;
+        if (a.order_out) a.order_out[(int64_t)b * a.L + l] = l;
+        if (a.keep_out && l < a.K) a.keep_out[(int64_t)b * a.K + l] = l;
+        if (a.crop_out && l == 0)
+          for (int i = 0; i < 6; ++i) a.crop_out[(int64_t)b * 6 + i] = 0;
+      }
+      continue;
+    }
+    const int gy = l / a.G, gx = l - gy * a.G;
+    const int py = q / a.p, px = q - py * a.p;
+    const int oy = gy * a.p + py, ox = gx * a.p + px;
+    int x0, x1, y0, y1;
+    float fx, fy;
+    resize_taps(rec.flip ? a.S - 1 - ox : ox, rec.cw, a.S, inv_den, x0, x1, fx);
+    resize_taps(oy, rec.ch, a.S, inv_den, y0, y1, fy);
+    const int W = a.widths[b];
+    const uint8_t* img = a.images + a.offsets[b];
+    const uint8_t* p00 = img + ((int64_t)(rec.top + y0) * W + rec.left + x0) * 3;
+    const uint8_t* p01 = img + ((int64_t)(rec.top + y0) * W + rec.left + x1) * 3;
+    const uint8_t* p10 = img + ((int64_t)(rec.top + y1) * W + rec.left + x0) * 3;
+    const uint8_t* p11 = img + ((int64_t)(rec.top + y1) * W + rec.left + x1) * 3;
+    const int rank = a.ids_restore[(int64_t)b * a.L + l];
+    const int64_t vo = ((int64_t)b * a.K + rank) * a.D + 3 * q;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const float a00 = p00[c], a01 = p01[c], a10 = p10[c], a11 = p11[c];
+      const float rt = a00 + fx * (a01 - a00);
+      const float rb = a10 + fx * (a11 - a10);
+      const float v = (rt + fy * (rb - rt)) * a.nscale[c] + a.nbias[c];
+      if (a.target) a.target[to + c] = v;
+      if (rank < a.K) {
+        if (kBf16) static_cast<uint16_t*>(a.visible)[vo + c] = (uint16_t)bf16_rne(v);
+        else static_cast<float*>(a.visible)[vo + c] = v;
+      }
+    }
+  }
 }
 
 // Launch plan of the resampling kernel when no image side exceeds max_side.  A row of patches
@@ -1256,6 +1322,24 @@ hipError_t launch_crop_aug(const CropArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Which kernel resamples for an odd patch size.  Staging reads all pixels of the crop, whatever the
+// output's size, and its workgroup of 64 threads per 64 pixels of a patch is mostly idle for the
+// smallest patches; a thread per output pixel reads four pixels for each from global memory.  So the
+// line lies where the images are several times as large as the output: at a ratio of 3 to 4 that grows
+// with the wavefronts that share the staging, and of 64 / p where the staged rows of a large patch fill
+// the LDS.  Staged / by the thread, tokens and target, side of the images -> output, p: 1356 images
+// 192 -> 80, 5: 67 / 129 us; 762 images 256 -> 80, 5: 63 / 83; 256 -> 55, 5: 57 / 47; 200 images
+// 500 -> 120, 15: 43 / 43; 762 images 256 -> 124, 31: 115 / 133; 1356 images 192 -> 62, 31: 90 / 63;
+// 4096 images 96 -> 48, 3: 111 / 133; 24 -> 24, 3: 43 / 39; 32 -> 16, 1: 104 / 33; and 2048 images
+// 256 -> 25, 5: 186 / 38.
+static bool crop_pixels_staged(const CropArgs& a) {
+  const int waves = (a.p * a.p + kWave - 1) / kWave;
+  // (the runtime takes fewer than 2^32 threads per launch)
+  const uint64_t threads = (uint64_t)a.B * a.G * a.col_parts * waves * kWave;
+  return a.p >= 3 && a.G > 1 && a.S >= (a.p < 5 ? 32 : 20) && 4 * a.max_side <= (12 + waves) * a.S &&
+         a.p * a.max_side <= 64 * a.S && threads < (uint64_t(1) << 32);
+}
+
 hipError_t launch_crop_patch(const CropArgs& a, hipStream_t stream) {
   if ((a.D & 3) == 0) {
     dim3 grid((uint32_t)a.B * (uint32_t)a.G * (uint32_t)a.col_parts);
@@ -1270,6 +1354,15 @@ hipError_t launch_crop_patch(const CropArgs& a, hipStream_t stream) {
     } else {
       hipLaunchKernelGGL(crop_patch_kernel<false>, grid, block, lds, stream, a);
     }
+  } else if (!crop_pixels_staged(a)) {
+    const int64_t total = (int64_t)a.B * a.L * a.p * a.p;  // output pixels
+    int64_t blocks = (total + kCropThreads - 1) / kCropThreads;
+    if (blocks > 256 * 64) blocks = 256 * 64;
+    dim3 grid((uint32_t)blocks), block(kCropThreads);
+    if (a.visible_bf16)
+      hipLaunchKernelGGL(crop_patch_scalar_kernel<true>, grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL(crop_patch_scalar_kernel<false>, grid, block, 0, stream, a);
   } else {
     dim3 grid((uint32_t)a.B * (uint32_t)a.G * (uint32_t)a.col_parts);
     dim3 block(kWave * ((a.p * a.p + kWave - 1) / kWave));

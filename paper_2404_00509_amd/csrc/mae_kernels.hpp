@@ -37,6 +37,7 @@ struct CropArgs {
   int32_t tile_pixels;   // staging tile of the resampling kernel, in 4-byte pixel words
   int32_t col_parts;     // column parts a row of patches is split into
   int32_t part_patches;  // patches per part (upper bound)
+  int32_t max_side;      // the images' side that the plan is for
   float nscale[3];       // 1 / (255 std_c)
   float nbias[3];        // -mean_c / std_c
   const uint8_t* images;

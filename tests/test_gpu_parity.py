@@ -172,17 +172,21 @@ def test_prep_shapes_and_tiny_or_large_images(S, p, K):
         check_prep_against_oracle(prep_to_numpy(big), ref, what=f"S{S}p{p}hint{hint}")
 
 
-@pytest.mark.parametrize("S,p,K", [(16, 1, 64), (27, 3, 20), (72, 9, 64), (62, 31, 3), (225, 15, 45)])
+@pytest.mark.parametrize("S,p,K", [(16, 1, 64), (27, 3, 20), (72, 9, 64), (62, 31, 3), (225, 15, 45),
+                                   # both sides of the line between the two kernels
+                                   (48, 3, 200), (84, 7, 36), (75, 5, 64), (126, 9, 50),
+                                   (124, 31, 4), (93, 31, 3), (19, 19, 1)])
 @pytest.mark.parametrize("want_target", [True, False])
 def test_prep_odd_patch_sizes(S, p, K, want_target):
     """A pixel per lane: patches of one pixel, of just over one wavefront (81), of 961 pixels; staged,
-    split into column parts and from global memory; with and without a target."""
+    split into column parts and from global memory; with and without a target; and a pixel per
+    thread where the images are several times as large as the output."""
     shapes = [(1, 1), (5, 300), (130, 97), (256, 200), (431, 613), (90, 1100)]
     data = _pack(_random_images(shapes, seed=S + p))
     kw = dict(out_size=S, patch=p, num_keep=K, seed=9, batch_index=2)
     ref = oracle.prep_batch(*data, **kw)
     dev = to_device(*data)
-    for bf16, hint in ((False, 256), (True, 256), (False, 700)):
+    for bf16, hint in ((False, 256), (True, 256), (False, 700), (True, 128)):
         desc = mae.make_prep_desc(*dev, max_image_side=hint,
                                   out_dtype=mae.MAE_BF16 if bf16 else mae.MAE_F32, **kw)
         buf = mae.alloc_prep_buffers(desc, want_target=want_target)
@@ -195,6 +199,28 @@ def test_prep_odd_patch_sizes(S, p, K, want_target):
                      rtol=BF16_RTOL if bf16 else RTOL, what=f"visible p{p} hint{hint}")
         if want_target:
             assert_close(buf.target.cpu().numpy(), ref["target"], what=f"target p{p} hint{hint}")
+
+
+def test_prep_odd_patch_with_more_work_items_than_one_launch_takes():
+    """262,160 samples of 16 x 16 patches of 31 x 31 pixels would be 2^32 threads of the staged kernel
+    and more; the samples equal those of small calls."""
+    B, S, p = 262160, 496, 31
+    images, offsets, heights, widths = to_device(*_pack(_random_images([(9, 7)], seed=3)))
+    src = (images, offsets.expand(B).contiguous(), heights.expand(B).contiguous(),
+           widths.expand(B).contiguous())
+    kw = dict(out_size=S, patch=p, num_keep=1, seed=10, out_dtype=mae.MAE_BF16)
+    desc = mae.make_prep_desc(*src, **kw)
+    buf = mae.alloc_prep_buffers(desc, want_target=False)
+    mae.mae_prep_batch(desc, buf.visible, buf.mask, buf.ids_restore, buf.ids_keep, None, buf.crop,
+                       buf.workspace)
+    for b in (0, 1, B // 2, B - 1):
+        one = mae.make_prep_desc(images, offsets, heights, widths, sample_base=b, **kw)
+        small = mae.alloc_prep_buffers(one, want_target=False)
+        mae.mae_prep_batch(one, small.visible, small.mask, small.ids_restore, small.ids_keep, None,
+                           small.crop, small.workspace)
+        assert torch.equal(buf.visible[b], small.visible[0])
+        assert torch.equal(buf.ids_restore[b], small.ids_restore[0])
+        assert torch.equal(buf.crop[b], small.crop[0])
 
 
 def test_prep_single_image_and_keep_all():
