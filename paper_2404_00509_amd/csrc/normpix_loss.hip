@@ -276,6 +276,60 @@ __global__ __launch_bounds__(kLossThreads) void normpix_loss_pair_kernel(LossArg
   if (lane == 0) a.partials[wave_in_grid] = acc;
 }
 
+// Short rows that are no multiple of four values: a value per lane, three passes over the row.  The
+// kernel above gives a lane four values, so that of 27 or 63 only 7 or 16 lanes are at work and the
+// last group's values come one by one.  401,408 rows, with the gradient, this kernel / the one above:
+// 27 values 112 / 155 us, 63 148 / 171 (bf16 115 / 168), 75 222 / 175 (bf16 157 / 171), 97 244 / 175
+// (bf16 204 / 168); 3 values 105 / 96.
+template <bool kBf16, bool kNorm>
+__global__ __launch_bounds__(kLossThreads) void normpix_loss_scalar_kernel(LossArgs a) {
+  const int lane = threadIdx.x % kWave;
+  const int wave_in_grid = blockIdx.x * kLossWaves + threadIdx.x / kWave;
+  const int waves = gridDim.x * kLossWaves;
+  const int D = a.D;
+  double acc = 0.0;
+  const float gscale =
+      a.counts ? (float)(a.gscale_num * inv_count_of(D, sum_counts(a.counts, a.ncounts))) : a.gscale;
+  for (int64_t row = wave_in_grid; row < a.rows; row += waves) {
+    const int64_t row_elem = row * D;
+    const float* t = a.target + row_elem;
+    if (a.mask[row] == 0) {
+      if (a.grad) {
+        for (int e = lane; e < D; e += kWave) {
+          if (kBf16) static_cast<uint16_t*>(a.grad)[row_elem + e] = 0;
+          else static_cast<float*>(a.grad)[row_elem + e] = 0.f;
+        }
+      }
+      continue;
+    }
+    float mu = 0.f, rstd = 1.0f;
+    if (kNorm) {
+      float s = 0.f;
+      for (int e = lane; e < D; e += kWave) s += t[e];
+      mu = wave_sum(s) / (float)D;
+      float ss = 0.f;
+      for (int e = lane; e < D; e += kWave) ss += (t[e] - mu) * (t[e] - mu);
+      const float var = wave_sum(ss) / (float)(D - 1);
+      rstd = 1.0f / sqrtf(var + a.eps);
+    }
+    float sq = 0.f;
+    for (int e = lane; e < D; e += kWave) {
+      float q;
+      if (kBf16) q = __uint_as_float((uint32_t)static_cast<const uint16_t*>(a.pred)[row_elem + e] << 16);
+      else q = static_cast<const float*>(a.pred)[row_elem + e];
+      const float diff = kNorm ? q - (t[e] - mu) * rstd : q - t[e];
+      sq += diff * diff;
+      if (a.grad) {
+        if (kBf16) static_cast<uint16_t*>(a.grad)[row_elem + e] = (uint16_t)bf16_rne(diff * gscale);
+        else static_cast<float*>(a.grad)[row_elem + e] = diff * gscale;
+      }
+    }
+    acc += (double)sq;
+  }
+  acc = wave_sum(acc);
+  if (lane == 0) a.partials[wave_in_grid] = acc;
+}
+
 // Adds the per-wavefront partials in a fixed order: thread i takes partials i, i + 256, ...,
 // then a tree over the 256 threads.
 __global__ __launch_bounds__(kLossThreads) void loss_finish_kernel(const double* partials, int n,
@@ -344,6 +398,10 @@ static void launch_vec(const LossArgs& a, dim3 grid, dim3 block, hipStream_t str
     else if (nvf == 5) MAE_LAUNCH_PAIR(5);
     else MAE_LAUNCH_PAIR(6);
 #undef MAE_LAUNCH_PAIR
+    return;
+  }
+  if ((a.D & 3) && a.D > 4 && a.D < (kBf16 && a.grad ? 96 : 64)) {
+    hipLaunchKernelGGL((normpix_loss_scalar_kernel<kBf16, kNorm>), grid, block, 0, stream, a);
     return;
   }
   if (a.D & 3) {

@@ -434,7 +434,9 @@ def _loss_case(B, L, D, seed, mask_mode="random", bf16=False, grad_scale=1.0, ep
                                    (2, 5, 147), (1, 6, 2), (2, 3, 2700), (7, 196, 768),
                                    # no multiple of four: one to three values in the last group, the
                                    # last group alone in its lane's run, every count of groups
-                                   (3, 5, 3), (5, 9, 257), (3, 7, 675), (2, 3, 1023), (2, 3, 1025),
+                                   # (and the shortest of them, a value per lane)
+                                   (3, 5, 3), (4, 9, 5), (3, 7, 27), (5, 5, 63), (3, 9, 65),
+                                   (3, 9, 95), (3, 9, 97), (5, 9, 257), (3, 7, 675), (2, 3, 1023), (2, 3, 1025),
                                    (2, 3, 1587), (2, 3, 2046), (1, 3, 2883), (2, 2, 3071)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_loss_shapes(B, L, D, bf16):
