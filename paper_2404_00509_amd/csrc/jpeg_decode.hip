@@ -26,9 +26,10 @@
 //    each of the crop's rows of MCUs.
 //  * jpeg_entropy_kernel: one wavefront per group of up to four images, a lane per row of MCUs that
 //    a crop touches (or per piece of such a row where the parallel walk has found the pieces'
-//    states); the coefficients go to the plane buffer as 16-bit values.
-//  * jpeg_decode_kernel (what is left: restart intervals that end inside a row, crops whose
-//    coefficients do not fit the plane buffer): rows dealt to the lanes in the same way.  A lane's
+//    states); the coefficients go to the plane buffer as 16-bit values, those of 4:4:4 crops of more
+//    than half a slot in part to the region buffer.
+//  * jpeg_decode_kernel (what is left: restart intervals that end inside a row, and crops of the whole
+//    slot with 4:4:4 sampling and more than 64 MCUs in a row): rows dealt to the lanes in the same way.  A lane's
 //    file bytes come through its column of a ring in LDS that is fed at the start of every
 //    block, where all lanes are at the same instruction; the bit buffer takes four bytes at a
 //    time unless one of them is 0xFF.  Per block: DC difference, AC symbols with one table
@@ -503,7 +504,8 @@ __device__ static inline uint32_t ycc_to_rgbx(int y, int cb, int cr) {
 // MCUs share the 64 lanes.  A lane gets at most kGroup rows (an image has at most 64).
 
 constexpr int kBlockBytes = 128;  // a block of coefficients in the plane buffer
-constexpr int kLivePlanes = 1, kLiveCoefs = 2, kLivePieces = 3;  // 0: the sample takes no part
+// 0: the sample takes no part
+constexpr int kLivePlanes = 1, kLiveCoefs = 2, kLivePieces = 3, kLiveSpill = 4;
 
 // What the wavefront keeps per image of its group.
 struct JpegImage {
@@ -512,7 +514,8 @@ struct JpegImage {
   uint16_t qz[2][64];  // per zig-zag position: natural position << 8 | quantiser step
   int my0, mx0, mx1, nrows, region_w, hs, size, scan_off;
   // kLivePlanes: decoded to planes, kLiveCoefs: by jpeg_entropy_kernel to coefficients,
-  // kLivePieces: the same, and the states of pieces of its rows are known
+  // kLivePieces: the same, and the states of pieces of its rows are known, kLiveSpill: to
+  // coefficients that its slot of the plane buffer does not hold alone (spilled_rows)
   int live;
   int restart, mcux;  // restart interval in MCUs (0 = none), MCUs per row of the image
   // bytes of entropy-coded data in the image's slot of the region buffer, byte stuffing removed
@@ -667,6 +670,19 @@ __device__ static int jpeg_unstuff(const JpegArgs& a, int64_t origin, int scan_o
   return done + fill + cut;
 }
 
+// Coefficients with 4:4:4 sampling take twice the slot for a crop that fills it.  As many of the crop's
+// last rows of MCUs as the image's slot of the plane buffer holds go there; the first rows, of which
+// this is the number, go to the end of its slot of the region buffer.  One workgroup of
+// jpeg_idct_kernel then takes the rows in order (with such crops by jpeg_decode_kernel to planes, beside
+// others by coefficients, a batch waited for one and the other: 512 files of 256 pixels, 4:4:4, a
+// restart interval per row: 3.94 -> 1.2 ms; 4096 files 5.84 -> 3.8; all of them by planes 3.2 and 4.0): the pixels of rows 0 .. r need (r + 1) half rows of
+// coefficients from the slot's start on, and the rows of coefficients behind r start at or behind
+// that, as all that are there (never more than the slot, whose side is a multiple of two MCUs) end
+// with it.
+__device__ static inline int spilled_rows(int64_t slot_bytes, int64_t row_bytes, int nrows) {
+  return max(0, nrows - (int)(slot_bytes / row_bytes));
+}
+
 // Tables, crop geometry and restart-marker positions of image b into slot `im` (whole wavefront).
 __device__ static void jpeg_prepare_image(const JpegArgs& a, int b, JpegImage& im,
                                           uint8_t* stage) {
@@ -718,16 +734,22 @@ __device__ static void jpeg_prepare_image(const JpegArgs& a, int b, JpegImage& i
   const int my0 = cr.top / mcu, my1 = min((cr.top + cr.ch - 1) / mcu, rec.mcuy - 1);
   const int mx0 = cr.left / mcu, mx1 = min((cr.left + cr.cw - 1) / mcu, rec.mcux - 1);
   // Blocks as 64 coefficients of 16 bits: the slot of the plane buffer (3 bytes per pixel) holds
-  // those of any crop with 4:2:0 sampling and of a crop of up to half the slot with 4:4:4.  A
-  // restart boundary may only fall between rows of MCUs.
-  const int64_t coef_bytes =
-      (int64_t)(my1 - my0 + 1) * (mx1 - mx0 + 1) * (rec.hs * rec.hs + 2) * kBlockBytes;
+  // those of any crop with 4:2:0 sampling and of a crop of up to half the slot with 4:4:4; of a larger
+  // one the slot of the region buffer takes the rest.  A restart boundary may only fall between rows
+  // of MCUs.
+  const int64_t slot_bytes = (int64_t)a.slot_side * a.slot_side * 3;
+  const int nrows = my1 - my0 + 1, ncols = mx1 - mx0 + 1;
+  const int64_t row_bytes = (int64_t)ncols * (rec.hs * rec.hs + 2) * kBlockBytes;
+  const int spilled = spilled_rows(slot_bytes, row_bytes, nrows);
+  // (a row that jpeg_idct_kernel takes in several steps, half of it written before all is read: only
+  // where the spilled rows leave half a row free, which all crops but one of the whole slot do)
   const bool dense = rec.restart % rec.mcux == 0 && !a.whole_image &&
-                     coef_bytes <= (int64_t)a.slot_side * a.slot_side * 3;
+                     (spilled == 0 || ncols <= kWave || spilled * row_bytes + row_bytes / 2 <= slot_bytes);
   if (dense) {  // most coefficients are zero: only the others will be written
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     u32x4* coef = reinterpret_cast<u32x4*>(a.planes + a.region_offsets[b]);
-    for (int i = lane; i < (int)(coef_bytes / 16); i += kJpegThreads) coef[i] = u32x4{0u, 0u, 0u, 0u};
+    const int pieces = (int)((nrows - spilled) * row_bytes / 16);  // (spilled rows: jpeg_entropy_kernel)
+    for (int i = lane; i < pieces; i += kJpegThreads) coef[i] = u32x4{0u, 0u, 0u, 0u};
   }
   if (lane == 0) {
     im.my0 = my0;
@@ -741,7 +763,7 @@ __device__ static void jpeg_prepare_image(const JpegArgs& a, int b, JpegImage& i
     im.restart = rec.restart;
     im.mcux = rec.mcux;
     im.clean_bytes = -1;
-    im.live = dense ? kLiveCoefs : kLivePlanes;
+    im.live = !dense ? kLivePlanes : (spilled ? kLiveSpill : kLiveCoefs);
     im.origin = a.offsets[b];
     im.region_off = a.region_offsets[b];
     // region geometry for jpeg_idct_kernel and the resampling kernel
@@ -1299,7 +1321,6 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
   CleanReader r;
   r.clean = a.regions + im->region_off;
   r.bytes = im->clean_bytes & (kCutShort - 1);
-  const bool cut_short = (im->clean_bytes & kCutShort) != 0;
   r.ring = &s.ring[0][lane];
   const int bits = 8 * r.bytes;  // below 2^30 (clean_fits)
   const int quarter =
@@ -1314,7 +1335,6 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
   int leave = 0, leave_phase = 0, blocks = 0, bad_at = kNever;
   int dc0 = 0, dc1 = 0, dc2 = 0;
   int first_block = 0, total = 0, row = lane, from = 0;
-  int tail0 = 0, tail1 = 0, tail2 = 0;  // DC differences of an MCU of zero bits
   bool bad = false;
   SyncStage stage = SyncStage::kParts;
   int round = 0;
@@ -1545,36 +1565,37 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
       ++round;
     } else if (stage == SyncStage::kTail) {
       bad = bad || (walk_bad != kNever && total + walk_bad < (my0 + nrows) * row_blocks);
-      tail0 = __shfl(sum0, kWave - 1);
-      tail1 = __shfl(sum1, kWave - 1);
-      tail2 = __shfl(sum2, kWave - 1);
+      if (im->clean_bytes & kCutShort) {
+        // Behind a file that merely stops a row is zero bits, and so are the blocks between the last
+        // that the data began and the row's first (the rest of an MCU, then whole ones).
+        const int ph = __shfl(leave_phase, kWave - 1), rest = ph ? per_mcu - ph : 0;
+        const int mcu0 = __shfl(sum0, kWave - 1), mcu1 = __shfl(sum1, kWave - 1),
+                  mcu2 = __shfl(sum2, kWave - 1);
+        const int end0 = s.dc[0][kWave - 1] + __shfl(dc0, kWave - 1),
+                  end1 = s.dc[1][kWave - 1] + __shfl(dc1, kWave - 1),
+                  end2 = s.dc[2][kWave - 1] + __shfl(dc2, kWave - 1);
+        for (int i = lane; i < nrows; i += kJpegThreads) {
+          const int target = (my0 + i) * row_blocks;
+          if (target < total || target == 0) continue;
+          const int whole = (target - total - rest) / per_mcu;
+          RowState st;
+          st.pos = im->size;
+          st.nbits = 0;
+          st.acc = 0;
+          st.pred[0] = (int16_t)(end0 + whole * mcu0 + (ph ? max(nblk - ph, 0) * (mcu0 / nblk) : 0));
+          st.pred[1] = (int16_t)(end1 + (whole + (ph && ph <= nblk ? 1 : 0)) * mcu1);
+          st.pred[2] = (int16_t)(end2 + (whole + (ph ? 1 : 0)) * mcu2);
+          st.rst_left = 0;
+          st.pad = 0;
+          (reinterpret_cast<RowState*>(a.row_states) + (int64_t)b * a.max_rows)[i] = st;
+        }
+      }
       stage = SyncStage::kRows;
     } else {
       const bool piece = stage == SyncStage::kPieces;
       const bool first_row = my0 + row == 0 && !piece;
-      RowState* states = reinterpret_cast<RowState*>(a.row_states) + (int64_t)b * a.max_rows;
-      const int last_leave_phase = __shfl(leave_phase, kWave - 1);
-      const int end0 = s.dc[0][kWave - 1] + __shfl(dc0, kWave - 1);
-      const int end1 = s.dc[1][kWave - 1] + __shfl(dc1, kWave - 1);
-      const int end2 = s.dc[2][kWave - 1] + __shfl(dc2, kWave - 1);
-      if (!asked && !piece && row < nrows && cut_short) {
-        // Behind a file that merely stops: the row is zero bits, and so are the blocks between the last
-        // that the data began and this row's first (the rest of an MCU, then whole ones).
-        const int ph = last_leave_phase, rest = ph ? per_mcu - ph : 0;
-        const int whole = ((my0 + row) * row_blocks - total - rest) / per_mcu;
-        RowState st;
-        st.pos = im->size;
-        st.nbits = 0;
-        st.acc = 0;
-        st.pred[0] = (int16_t)(end0 + whole * tail0 + (ph ? max(nblk - ph, 0) * (tail0 / nblk) : 0));
-        st.pred[1] = (int16_t)(end1 + (whole + (ph && ph <= nblk ? 1 : 0)) * tail1);
-        st.pred[2] = (int16_t)(end2 + (whole + (ph ? 1 : 0)) * tail2);
-        st.rst_left = 0;
-        st.pad = 0;
-        states[row] = st;
-      }
       // (bit < bits: the walk counted this block, or it is the file's first)
-      if (asked && (first_row || piece || cut_short ||
+      if (asked && (first_row || piece || (im->clean_bytes & kCutShort) ||
                     row_can_start(bits - bit, (uint32_t)r.clean[max(r.bytes - 1, 0)]))) {
         const uint8_t* file = a.files + im->origin;
         const int32_t* map =
@@ -1592,7 +1613,7 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
         st.rst_left = 0;
         st.pad = 0;
         if (piece) piece_states(a, im->region_off)[lane] = st;
-        else states[row] = st;
+        else (reinterpret_cast<RowState*>(a.row_states) + (int64_t)b * a.max_rows)[row] = st;
       }
       if (piece) {
         if (lane == 0) reinterpret_cast<JpegPrepared*>(a.prepared)[b].im.live = kLivePieces;
@@ -1745,9 +1766,9 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_decode_kernel(JpegArgs a) {
 // will be, which is cleared once they are behind.
 // The file's bytes lose their stuffing on the way into the ring (SymbolReader): topping up
 // the bit buffer is then a select.  4096 files of 256 pixels with a restart interval per row: 0.80 ms and
-// 0.34 ms for the inverse transform and colours (entropy decoding and transform by the same lanes,
+// 0.25 ms for the inverse transform and colours (entropy decoding and transform by the same lanes,
 // block after block, as in jpeg_decode_kernel: 1.42 ms and 0.20 ms for the colours); 1024 files without
-// markers, rows in pieces: 0.22 + 0.09 ms (1.34 + 0.04 ms).
+// markers, rows in pieces: 0.22 + 0.07 ms (1.34 + 0.04 ms).
 struct SymbolReader {
   const uint8_t* chunks;  // as in BitReader
   int64_t chunks_bytes;
@@ -1845,9 +1866,15 @@ template <int kGroup>
 __global__ __launch_bounds__(kJpegThreads) void jpeg_entropy_kernel(JpegArgs a) {
   __shared__ JpegEntropyLds<kGroup> s;
   const int lane = threadIdx.x;
-  const int b0 = (int)blockIdx.x * kGroup;
+  // the first half of the workgroups stores to the plane buffer, the second the spilled rows
+  const uint32_t half = gridDim.x / 2;
+  const bool spill = blockIdx.x >= half;
+  const int b0 = (int)(blockIdx.x - (spill ? half : 0u)) * kGroup;
   const int nimg = min(kGroup, a.B - b0);
   const JpegPrepared* prepared = reinterpret_cast<const JpegPrepared*>(a.prepared) + b0;
+  // (below 2^32: a side of at most 32768, and one image per group where a slot is that large)
+  const uint32_t slot_bytes = (uint32_t)a.slot_side * (uint32_t)a.slot_side * 3u;
+  uint8_t* coefs = (spill ? a.regions : a.planes) + (int64_t)b0 * slot_bytes;  // (slots follow each other)
   int first_task[kGroup + 1];
   first_task[0] = 0;
 #pragma unroll
@@ -1855,8 +1882,21 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_entropy_kernel(JpegArgs a) 
     int rows = 0;
     if (i < nimg && prepared[i].im.live >= kLiveCoefs) {
       const JpegImage& im = prepared[i].im;
-      rows = min(im.nrows, a.max_rows);
-      if (im.live == kLivePieces) rows *= pieces_per_row(im.nrows, im.mx1 - im.mx0 + 1);
+      const int ncols = im.mx1 - im.mx0 + 1;
+      rows = spill ? 0 : min(im.nrows, a.max_rows);
+      if (im.live == kLivePieces) rows *= pieces_per_row(im.nrows, ncols);
+      if (im.live == kLiveSpill) {
+        const uint32_t row_bytes = (uint32_t)ncols * (uint32_t)((im.hs * im.hs + 2) * kBlockBytes);
+        const int spilled = spilled_rows(slot_bytes, row_bytes, im.nrows);
+        rows = spill ? spilled : rows - spilled;
+        if (spill) {  // (not earlier: the walk's copy of the file's data was there)
+          typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+          const uint32_t bytes = (uint32_t)spilled * row_bytes;
+          u32x4* coef = reinterpret_cast<u32x4*>(coefs + (uint32_t)(i + 1) * slot_bytes - bytes);
+          for (uint32_t j = (uint32_t)lane; j < bytes / 16; j += kJpegThreads)
+            coef[j] = u32x4{0u, 0u, 0u, 0u};
+        }
+      }
     }
     first_task[i + 1] = first_task[i] + rows;
     if (rows == 0) continue;
@@ -1864,9 +1904,6 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_entropy_kernel(JpegArgs a) 
   }
   __syncthreads();
   const int ntasks = first_task[kGroup];
-  // (below 2^32: a side of at most 32768, and one image per group where a slot is that large)
-  const uint32_t slot_bytes = (uint32_t)a.slot_side * (uint32_t)a.slot_side * 3u;
-  uint8_t* coefs = a.planes + (int64_t)b0 * slot_bytes;  // (slots follow each other)
 
 #pragma unroll 1
   for (int task = lane; task < ntasks; task += kJpegThreads) {
@@ -1883,6 +1920,13 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_entropy_kernel(JpegArgs a) 
     const int nblk = im.hs * im.hs, last_phase = nblk + 1, per_mcu = nblk + 2;
     const int mx0 = im.mx0, mx1 = im.mx1, ncols = mx1 - mx0 + 1;
     int row = task - slot_first;  // row of MCUs inside the crop's range
+    uint32_t origin = (uint32_t)slot * slot_bytes;  // where row 0 would be
+    if (im.live == kLiveSpill) {
+      const uint32_t row_bytes = (uint32_t)(ncols * per_mcu * kBlockBytes);
+      const int spilled = spilled_rows(slot_bytes, row_bytes, im.nrows);
+      row += spill ? 0 : spilled;
+      origin += (spill ? slot_bytes : 0u) - (uint32_t)spilled * row_bytes;
+    }
     int first = 0;                // MCU of the crop that the lane's blocks are stored from
     int skip = mx0 * per_mcu, total = (mx1 + 1) * per_mcu;  // blocks
     RowState st = (reinterpret_cast<const RowState*>(a.row_states) + (int64_t)b * a.max_rows)[
@@ -1902,7 +1946,7 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_entropy_kernel(JpegArgs a) 
     const uint32_t limit_y = long_from(im.ac[0]), limit_c = long_from(im.ac[1]);
     const int table = slot * kCoefTable;
     // byte offsets of the row's first block, and of the current one less one coefficient
-    const uint32_t base = (uint32_t)slot * slot_bytes +
+    const uint32_t base = origin +
                           (uint32_t)(row * ncols + first) * (uint32_t)(per_mcu * kBlockBytes);
     uint32_t out = base - 2;
     // (a row's restart boundary, if any, lies behind its last MCU: a state that says otherwise is
@@ -2081,8 +2125,11 @@ __device__ static inline void store_rgb4_pairs(uint8_t* dst, uint32_t yy, const 
 // which halves the products (sums of the same integers: nothing changes in the result).  The samples
 // meet in LDS, from where four pixels per lane and step are converted and stored along the rows.
 // Bound by vector instructions, half of them the transform; the bytes are taken two per instruction where
-// they fit 16 bits (4096 files of 256 pixels: 0.34 ms, with a 32-bit clamp and shift per value 0.45).
-// Images that jpeg_decode_kernel has decoded have planes instead of coefficients.
+// they fit 16 bits (4096 files of 256 pixels: 0.25 ms; 0.34 with an image's parts next to each other in
+// the grid, where the parts with nothing to do left some compute units more work than others, and
+// 0.45 with a 32-bit clamp and shift per value besides).
+// Images that jpeg_decode_kernel has decoded have planes instead of coefficients; images with spilled
+// rows are one workgroup's work.
 constexpr int kIdctThreads = 3 * kWave;
 constexpr int kIdctStride = 72;   // bytes per block of samples: 64 and a pad against bank conflicts
 constexpr int kCoefStride = 144;  // the same for its coefficients
@@ -2194,8 +2241,9 @@ __global__ __launch_bounds__(kIdctThreads) void jpeg_idct_kernel(JpegArgs a, int
   // the step's coefficients, then (all lanes have theirs in registers) its samples
   __shared__ __attribute__((aligned(16))) uint8_t samples[kIdctThreads * kCoefStride];
   __shared__ uint32_t place[kWave];  // of an MCU's first pixel in the region
-  const int b = (int)(blockIdx.x / (uint32_t)parts);
-  const int part = (int)(blockIdx.x - (uint32_t)b * (uint32_t)parts);
+  // all images' first parts first: the longest work, where an image is one workgroup's
+  const int part = (int)(blockIdx.x / (uint32_t)a.B);
+  const int b = (int)(blockIdx.x - (uint32_t)part * (uint32_t)a.B);
   const JpegImage& im = reinterpret_cast<const JpegPrepared*>(a.prepared)[b].im;
   if (!im.live) return;
   if (im.live == kLivePlanes) {
@@ -2211,24 +2259,41 @@ __global__ __launch_bounds__(kIdctThreads) void jpeg_idct_kernel(JpegArgs a, int
   const int region_w = im.region_w;
   const uint8_t* coef = a.planes + im.region_off;
   uint8_t* region = a.regions + im.region_off;
+  const bool spill = im.live == kLiveSpill;
+  if (spill && part != 0) return;  // (its rows in order: spilled_rows)
+  const int64_t slot_bytes = (int64_t)a.slot_side * a.slot_side * 3;
+  const int64_t row_bytes = (int64_t)ncols * per_mcu * kBlockBytes;
+  const int64_t spilled_bytes = spill ? spilled_rows(slot_bytes, row_bytes, im.nrows) * row_bytes : 0;
   const int qz = im.qz[hs == 2 ? wave == 2 : wave != 0][lane] & 255;
   const int group = kWave / hs;  // MCUs per step
   // this lane's block: MCU inside the group, block of the MCU
   const int m = hs == 2 ? (wave == 2 ? lane >> 1 : 16 * wave + (lane >> 2)) : lane;
   const int blk = hs == 2 ? (wave == 2 ? 4 + (lane & 1) : lane & 3) : wave;
-  for (int m0 = part * group; m0 < nmcu; m0 += parts * group) {
+  // MCUs of a step: any, or whole rows, or parts of one row that is longer
+  const int row_steps = (ncols + group - 1) / group, step_mcus = spill ? max(group / ncols, 1) * ncols : group;
+  const int nsteps = spill && row_steps > 1 ? im.nrows * row_steps : (nmcu + step_mcus - 1) / step_mcus;
+  for (int step = spill ? 0 : part; step < nsteps; step += spill ? 1 : parts) {
+    int m0 = step * step_mcus, end = min(nmcu, m0 + step_mcus);
+    if (spill && row_steps > 1) {
+      const int row = step / row_steps;
+      m0 = row * ncols + (step - row * row_steps) * group;
+      end = (row + 1) * ncols;
+    }
     if ((int)threadIdx.x < group) {
-      const int i = min(m0 + (int)threadIdx.x, nmcu - 1);
+      const int i = min(m0 + (int)threadIdx.x, end - 1);
       const int my = i / ncols, mx = i - my * ncols;
       place[threadIdx.x] = ((uint32_t)(my * mcu) * (uint32_t)region_w + (uint32_t)(mx * mcu)) * 3u;
     }
     // the step's blocks lie one after the other in memory: 16 bytes per lane and load
-    const u32x4_c* src = reinterpret_cast<const u32x4_c*>(coef + (int64_t)m0 * per_mcu * kBlockBytes);
-    const int pieces = min(group, nmcu - m0) * per_mcu * (kBlockBytes / 16);
+    const int64_t first = (int64_t)m0 * per_mcu * kBlockBytes;
+    const int pieces = min(group, end - m0) * per_mcu * (kBlockBytes / 16);
     u32x4_c raw[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      raw[i] = src[min((int)threadIdx.x + i * kIdctThreads, pieces - 1)];
+    for (int i = 0; i < 8; ++i) {
+      const int64_t at = first + 16 * min((int)threadIdx.x + i * kIdctThreads, pieces - 1);
+      const uint8_t* src = (at < spilled_bytes ? region + slot_bytes : coef) - spilled_bytes;
+      raw[i] = *reinterpret_cast<const u32x4_c*>(src + at);
+    }
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int at = (int)threadIdx.x + i * kIdctThreads;
@@ -2246,7 +2311,7 @@ __global__ __launch_bounds__(kIdctThreads) void jpeg_idct_kernel(JpegArgs a, int
     for (int i = (int)threadIdx.x; i < 128 * 8; i += kIdctThreads) {
       const int y = (i >> 7) * hs, r = i & 127;
       const int pm = r >> hs, piece = r & (2 * hs - 1);
-      if (m0 + pm >= nmcu) continue;
+      if (m0 + pm >= end) continue;
       uint8_t* dst = region + (place[pm] + (uint32_t)((y * region_w + 4 * piece) * 3));
       if (hs == 2) {
         const int luma = 4 * pm + (y >> 3) * 2 + (piece >> 1), chroma = 128 + 2 * pm;
@@ -2309,11 +2374,11 @@ hipError_t launch_jpeg_decode(const JpegArgs& a, hipStream_t stream) {
   // fewer lanes has fewer of them on a rare path at a time
   const int group = B <= 1024 ? 1 : (B <= 2048 ? (most < 2 ? most : 2) : most);
   if (group == 4)
-    hipLaunchKernelGGL(jpeg_entropy_kernel<4>, dim3((B + 3) / 4), block, 0, stream, a);
+    hipLaunchKernelGGL(jpeg_entropy_kernel<4>, dim3(2 * ((B + 3) / 4)), block, 0, stream, a);
   else if (group == 2)
-    hipLaunchKernelGGL(jpeg_entropy_kernel<2>, dim3((B + 1) / 2), block, 0, stream, a);
+    hipLaunchKernelGGL(jpeg_entropy_kernel<2>, dim3(2 * ((B + 1) / 2)), block, 0, stream, a);
   else
-    hipLaunchKernelGGL(jpeg_entropy_kernel<1>, dim3(B), block, 0, stream, a);
+    hipLaunchKernelGGL(jpeg_entropy_kernel<1>, dim3(2 * B), block, 0, stream, a);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   // files with restart boundaries inside a row of MCUs, and crops whose coefficients do not fit

@@ -288,9 +288,9 @@ def test_files_the_decoder_does_not_take_are_flagged_and_take_no_part():
 
 
 @pytest.mark.parametrize("restart_rows", [0, 1, 2])
-def test_coefficients_and_planes_in_one_batch(restart_rows):
+def test_coefficients_around_the_size_of_the_plane_slot(restart_rows):
     """4:4:4 files whose crops are around half the slot: the coefficients of some fit the plane
-    buffer, the others are decoded to planes.  Tables with codes that the direct tables leave out
+    buffer, of the others the first rows go to the region buffer.  Tables with codes that the direct tables leave out
     (optimised, quality 100), and crops that start right of the first MCU."""
     B, S = 13, 64
     files, offsets, sizes = synth.make_jpegs("gradient", B, seed=68, quality=100, subsampling="4:4:4",
@@ -300,6 +300,36 @@ def test_coefficients_and_planes_in_one_batch(restart_rows):
     buf, _ = _gpu_jpeg_prep(files, offsets, sizes, **kw)
     assert mae.mae_prep_status(buf.workspace) == 0
     check_prep_against_oracle(prep_to_numpy(buf), ref, what=f"restart rows {restart_rows}")
+
+
+@pytest.mark.parametrize("restart_rows", [0, 1])
+@pytest.mark.parametrize("side,shapes", [
+    (64, [(64, 64), (57, 64), (64, 49), (33, 64), (40, 60), (64, 8)]),
+    (256, [(256, 256), (250, 256), (256, 130), (129, 256), (180, 200), (256, 64)]),
+    # rows of more than 64 MCUs are transformed in several steps; the whole slot goes by planes
+    (576, [(576, 576), (568, 576), (576, 565), (300, 576), (576, 520)])])
+def test_coefficients_of_up_to_twice_the_plane_slot(side, shapes, restart_rows):
+    """Whole 4:4:4 images, from the whole slot down to crops that the plane buffer holds alone."""
+    import io
+
+    from PIL import Image
+    rng = np.random.default_rng(side)
+    chunks = []
+    for h, w in shapes:
+        buf = io.BytesIO()
+        kw = dict(restart_marker_rows=1) if restart_rows else {}
+        Image.fromarray(synth._one_image("gradient", h, w, rng)).save(
+            buf, format="JPEG", quality=90, subsampling="4:4:4", **kw)
+        chunks.append(np.frombuffer(buf.getvalue(), np.uint8))
+    files, offsets, sizes = _join(chunks)
+    decoded = _decode_all(files, offsets, sizes)
+    for scale, ratio in (((1.0, 1.0), (0.61, 1.6)), ((0.4, 0.9), (0.75, 4 / 3))):
+        kw = dict(out_size=96, patch=16, num_keep=9, scale=scale, ratio=ratio, seed=33,
+                  batch_index=3)
+        ref = oracle.prep_batch(*decoded, **kw)
+        buf, _ = _gpu_jpeg_prep(files, offsets, sizes, max_image_side=side, **kw)
+        assert mae.mae_prep_status(buf.workspace) == 0
+        check_prep_against_oracle(prep_to_numpy(buf), ref, what=f"side {side} scale {scale}")
 
 
 def test_files_without_markers_whose_data_ends_early():
