@@ -1336,6 +1336,10 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
   int dc0 = 0, dc1 = 0, dc2 = 0;
   int first_block = 0, total = 0, row = lane, from = 0;
   bool bad = false;
+  // (as row_can_start; a file that merely stops has none)
+  const int padding = (im->clean_bytes & kCutShort)
+                          ? 0
+                          : min(__builtin_ctz(~(uint32_t)r.clean[max(r.bytes - 1, 0)]), 7);
   SyncStage stage = SyncStage::kParts;
   int round = 0;
   for (;;) {
@@ -1565,7 +1569,7 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
       ++round;
     } else if (stage == SyncStage::kTail) {
       bad = bad || (walk_bad != kNever && total + walk_bad < (my0 + nrows) * row_blocks);
-      if (im->clean_bytes & kCutShort) {
+      if (__builtin_expect((im->clean_bytes & kCutShort) != 0, 0)) {
         // Behind a file that merely stops a row is zero bits, and so are the blocks between the last
         // that the data began and the row's first (the rest of an MCU, then whole ones).
         const int ph = __shfl(leave_phase, kWave - 1), rest = ph ? per_mcu - ph : 0;
@@ -1595,8 +1599,7 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
       const bool piece = stage == SyncStage::kPieces;
       const bool first_row = my0 + row == 0 && !piece;
       // (bit < bits: the walk counted this block, or it is the file's first)
-      if (asked && (first_row || piece || (im->clean_bytes & kCutShort) ||
-                    row_can_start(bits - bit, (uint32_t)r.clean[max(r.bytes - 1, 0)]))) {
+      if (asked && (first_row || piece || bits - bit > padding)) {
         const uint8_t* file = a.files + im->origin;
         const int32_t* map =
             reinterpret_cast<const int32_t*>(r.clean + clean_map_offset(im->size, im->scan_off));
