@@ -43,7 +43,7 @@ def _gpu_jpeg_prep(files, offsets, sizes, bf16=False, **kw):
 @pytest.mark.parametrize("sub", ["4:2:0", "4:4:4"])
 @pytest.mark.parametrize("kind,S", [("gradient", 112), ("uniform", 64)])
 def test_crop_decode_matches_full_decode(sub, kind, S):
-    B = 16 if sub == "4:2:0" else 13      # 13: the last group of images is not full
+    B = 16 if sub == "4:2:0" else 13
     files, offsets, sizes = synth.make_jpegs(kind, B, seed=60, subsampling=sub)
     L = (S // 16) ** 2
     kw = dict(out_size=S, patch=16, num_keep=oracle.num_keep(L, 0.75), seed=13, batch_index=1)
@@ -351,8 +351,7 @@ def test_files_without_markers_whose_data_ends_early():
 
 
 def test_files_of_maximum_side_500():
-    """The size of the paper's crop-decode benchmark: 24 to 32 rows of MCUs per image, so the four
-    images of a wavefront have more rows than it has lanes."""
+    """The size of the paper's crop-decode benchmark: 24 to 32 rows of MCUs per image."""
     B, S = 6, 224
     files, offsets, sizes = synth.make_jpegs("gradient500", B, seed=67)
     L = (S // 16) ** 2
@@ -361,6 +360,49 @@ def test_files_of_maximum_side_500():
     buf, _ = _gpu_jpeg_prep(files, offsets, sizes, max_image_side=512, **kw)
     assert mae.mae_prep_status(buf.workspace) == 0
     check_prep_against_oracle(prep_to_numpy(buf), ref, what="side 500")
+
+
+@pytest.mark.parametrize("B,side", [(1025, 256), (2051, 256), (1027, 512)])
+def test_batches_whose_wavefronts_share_images(B, side):
+    """The entropy kernel takes one, two or four images per wavefront by the batch's size (two at most
+    beyond 256 pixels): batches just over the lines, with the last group partly filled, whose groups
+    mix files in every organisation (rows, chains whose rows are taken in pieces, 4:4:4 crops that
+    spill, up to 128 rows per group, intervals that end inside rows) with files that are refused."""
+    import io
+
+    from PIL import Image
+    kind = "gradient" if side == 256 else "gradient500"
+    n = 22                                   # no multiple of four: every group is another mixture
+    imgs = synth.make_images(kind, n, seed=76)
+    variants = [dict(restart_marker_rows=1), dict(), dict(subsampling="4:4:4", restart_marker_rows=1),
+                dict(subsampling="4:4:4"), dict(progressive=True), dict(restart_marker_blocks=5),
+                dict(subsampling="4:4:4", restart_marker_rows=1, narrow=True), dict(optimize=True)]
+    chunks, refused = [], []
+    for i in range(n):
+        args = dict(format="JPEG", quality=85, subsampling="4:2:0")
+        args.update(variants[i % len(variants)])
+        view = synth.image_view(*imgs, i)
+        if args.pop("narrow", False):
+            view = np.ascontiguousarray(view[:, :100])
+        refused.append("progressive" in args)
+        buf = io.BytesIO()
+        Image.fromarray(view).save(buf, **args)
+        chunks.append(np.frombuffer(buf.getvalue(), np.uint8))
+    files, first, lens = _join(chunks)
+    pick = np.arange(B) % n
+    # (the oracle gets the first file's image in place of a refused one)
+    stand_in = np.where(refused, 0, np.arange(n))
+    images, offs, hs, ws = _decode_all(files, first[stand_in], lens[stand_in])
+    ref = dict(out_size=32, patch=16, num_keep=2, scale=(0.2, 1.0), seed=34, batch_index=4)
+    buf, _ = _gpu_jpeg_prep(files, first[pick], lens[pick], max_image_side=side, **ref)
+    ref = oracle.prep_batch(images, offs[pick], hs[pick], ws[pick], **ref)
+    bad = np.array(refused)[pick]
+    np.testing.assert_array_equal(buf.crop[:, 5].cpu().numpy(), np.where(bad, 0, 1))
+    keep = np.nonzero(~bad)[0]
+    sel = {k: (v[keep] if v is not None else None) for k, v in ref.items()}
+    check_prep_against_oracle(prep_to_numpy(buf, rows=keep), sel, what=f"{B} files, side {side}")
+    for b in np.nonzero(bad)[0][[0, -1]]:
+        check_neutral_outputs(buf, int(b))
 
 
 def test_jpeg_input_on_a_side_stream_and_in_a_captured_graph():
@@ -565,9 +607,8 @@ def test_row_index_of_files_the_decoder_does_not_take():
 
 
 def test_row_index_with_large_files_augmentation_and_the_loss_without_target():
-    """The index under the other modes of the call: files of maximum side 500 (two images per
-    wavefront in the decode kernel, 64 index rows per file), the finetuning augmentation, and the
-    loss that reads the decoded regions again."""
+    """The index under the other modes of the call: files of maximum side 500 (64 index rows per
+    file), the finetuning augmentation, and the loss that reads the decoded regions again."""
     B, S = 6, 128
     files, offsets, sizes = synth.make_jpegs("gradient500", B, seed=73, restart_rows=0)
     decoded = _decode_all(files, offsets, sizes)
