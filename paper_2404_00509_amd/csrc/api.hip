@@ -360,9 +360,6 @@ int mae_prep_batch(const mae_prep_desc* d, void* visible, uint8_t* mask, int32_t
   // streaming kernel (the blur kernel's second pass for the blur images) writes the outputs.
   ca.u8_out = ws + wsl.u8_offset;
   ca.aug_mode = d->aug_mode;
-  ca.jitter = d->jitter;
-  ca.sample_base = d->sample_base;
-  ca.key1 = pa.key1;
   ca.luma_partials = reinterpret_cast<double*>(ws + wsl.crop_partials_offset);
   ca.aug_recs = ws + wsl.aug_offset;
   mae::AugArgs aa;
@@ -376,9 +373,6 @@ int mae_prep_batch(const mae_prep_desc* d, void* visible, uint8_t* mask, int32_t
   aa.D = ca.D;
   aa.visible_bf16 = ca.visible_bf16;
   aa.mode = d->aug_mode;
-  aa.jitter = d->jitter;
-  aa.sample_base = d->sample_base;
-  aa.key1 = pa.key1;
   const mae::AugPlan aplan = mae::three_aug_plan(d->out_size, d->patch);
   aa.blur_parts = aplan.parts;
   aa.blur_part_patches = aplan.part_patches;

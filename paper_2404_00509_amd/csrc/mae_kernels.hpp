@@ -52,9 +52,6 @@ struct CropArgs {
   // finetuning augmentation as this kernel's epilogue (launch_crop_aug): grayscale and
   // solarisation are applied to the rounded value in registers, blur images go to u8_out
   int32_t aug_mode;       // 1: "3 Aug", 2: "3 Aug+"
-  float jitter;
-  uint32_t sample_base;
-  uint64_t key1;
   double* luma_partials;  // "3 Aug+": [B * G * col_parts] sums of luma after the brightness step
   const void* aug_recs;   // AugParams[B], written by the parameter kernel
   // the loss as the kernel's epilogue (launch_crop_loss): nothing above from `visible` on is used
@@ -97,9 +94,6 @@ struct AugArgs {
   int32_t B, S, p, G, L, K, D;
   int32_t visible_bf16;
   int32_t mode;  // 1: one of grayscale / solarise / blur; 2: the same followed by colour jitter
-  float jitter;  // strength of the colour jitter (factors uniform on 1 +- jitter)
-  uint32_t sample_base;
-  uint64_t key1;
   float nscale[3];
   float nbias[3];
   int32_t blur_parts;         // column parts a row of patches is split into by the blur kernel
