@@ -360,7 +360,6 @@ __device__ static __forceinline__ void fill(BitReader& r) {
 __device__ static __forceinline__ void fill_bytewise(BitReader& r) {
   while (r.nbits <= 32) {
     uint32_t byte = 0;
-    const int from = r.pos;
     if (!r.ended && r.pos < r.n) {
       byte = file_byte(r, r.pos);
       if (byte == 0xFF) {
@@ -369,14 +368,16 @@ __device__ static __forceinline__ void fill_bytewise(BitReader& r) {
         } else {
           r.ended = true;
           byte = 0;
+          r.zeros += 8;
         }
       } else {
         r.pos += 1;
       }
+    } else {
+      r.zeros += 8;
     }
     r.acc = (r.acc << 8) | byte;
     r.nbits += 8;
-    r.zeros += r.pos == from ? 8 : 0;
   }
 }
 // Whether a row of MCUs can start where `left` bits of its data are unread, the last of them in
