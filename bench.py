@@ -9,8 +9,8 @@ gradient), on synthetic images already resident in HBM.  Prints ONE JSON line.
 `value` is measured on the headline workload (c4).  The other workloads with a loss (c3, c5) are
 timed the same way and reported under "configs".  The first consumer of the path's output,
 mae_patch_embed, the finetuning-mode input pipeline ("3 Aug", "3 Aug+"), the input pipeline on
-JPEG files ("crop decode"), the stages of a progressive schedule and a patch size that takes the
-element-wise kernel are timed by themselves after the steps and reported under "patch_embed",
+JPEG files ("crop decode"), the stages of a progressive schedule and an odd patch size (a kernel of
+its own) are timed by themselves after the steps and reported under "patch_embed",
 "finetune_prep", "jpeg_prep*", "stages" and "odd_patch_prep"; they are not part of the step or of
 `value`.
 
@@ -383,11 +383,11 @@ def time_finetune(args, mae, torch, w):
         # the method's bytes: the crop read once, tokens, mask and ids written.  What the
         # implementation moves on top of that is reported beside it, not counted: the 8-bit
         # resized crop of the images that drew the blur (a third of them), written once and read
-        # once per pass of the blur kernel, and for "3 Aug+" the second read of the crops.
+        # once per pass of the blur kernel (two with "3 Aug+"), and for "3 Aug+" that of the others,
+        # written once and read once by the jitter kernel.
         nbytes = crop_bytes + wl.B * (L * wl.D * 4 + L * 5 + L * 4)
         u8_third = wl.B * res * res * 3 // 3
-        extra = u8_third * (3 if mode == mae.MAE_AUG_THREE_PLUS else 2) \
-            + (crop_bytes * 2 // 3 if mode == mae.MAE_AUG_THREE_PLUS else 0)
+        extra = u8_third * (3 + 2 * 2 if mode == mae.MAE_AUG_THREE_PLUS else 2)
         key = "three" if mode == mae.MAE_AUG_THREE else "three_plus"
         gbps = nbytes / (st["avg_ms"] * 1e-3) / 1e9
         rows.append(dict(st, augmentation=name, out_size=res,
@@ -402,8 +402,8 @@ def time_finetune(args, mae, torch, w):
 
 def time_odd_patch(args, mae, torch, w):
     """mae_prep_batch with a patch size whose rows are not whole 16-byte groups (3 p p % 4 != 0):
-    the same images to 225 px in patches of 15 (D = 675), keep a quarter.  These shapes take the
-    element-wise kernel instead of the staged one; this is what that costs."""
+    the same images to 225 px in patches of 15 (D = 675), keep a quarter.  Such a patch goes a pixel
+    per lane through the staged kernel's odd variant; this is what that costs."""
     wl, dev = w.wl, w.dev
     S, p = 225, 15
     L = (S // p) ** 2

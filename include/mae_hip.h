@@ -97,12 +97,15 @@ typedef enum { MAE_AUG_SIMPLE = 0, MAE_AUG_THREE = 1, MAE_AUG_THREE_PLUS = 2 } m
  * to 16 (in this mode the hint is a limit; 0 = 256).  A file with one restart interval per row
  * of MCUs (a choice of the dataset writer that costs 0.2 % in size) has independent rows, and
  * those outside the crop are never touched; in any other file the entropy-coded data has to be
- * walked through from its start down to the crop's last row to find where the rows begin (symbol
- * lengths only, one lane per file: several times the cost of the decoding itself), unless the
- * caller passes the file's row index (mae_jpeg_index, jpeg_row_index below), which is computed
- * once per file and makes every file decode like one with independent rows.  Any other file makes
- * its sample invalid
- * (valid = 0 in crop_out, counted by mae_prep_status).  A decoder is specified by the standard
+ * walked through from its start to find where the crop's rows begin (symbol lengths only).  A file
+ * without restart markers is walked in 64 places at once, which costs about as much as the decoding
+ * itself; one whose intervals are no rows of MCUs, or whose data is too large for the image's slot
+ * of the workspace, is walked by one lane, which costs several times as much.  No file is walked
+ * when the caller passes the file's row index (mae_jpeg_index, jpeg_row_index below), which is computed
+ * once per file and makes every file decode like one with independent rows.  Zero bits follow the
+ * end of a row's data, or of a file that simply stops; a file whose data a marker ends before a row
+ * of the crop begins, and any other file, makes its sample invalid (valid = 0 in crop_out, counted
+ * by mae_prep_status).  A decoder is specified by the standard
  * only up to the accuracy of the inverse DCT, the chroma interpolation and the colour arithmetic;
  * here: 13-bit fixed-point separable inverse DCT (first pass kept with 3 fractional bits, inputs
  * of both passes clamped to +-32767), each chroma sample repeated over the pixels it covers,

@@ -20,8 +20,9 @@
 //    out of the two pixel words.  Nothing inside the loop reads global memory, so the stores of
 //    one patch never have to complete before the next patch is computed.
 //  * Variants of the last phase on the same staged tile: the finetuning augmentation as the
-//    epilogue (produce_aug: values rounded to bytes in integers, grayscale / solarisation, colour
-//    jitter; only the images that drew the blur leave as bytes for the blur kernel); the kept
+//    epilogue (produce_aug: values rounded to bytes in integers, grayscale / solarisation; the images
+//    that drew the blur, and all of them when the colour jitter follows, leave as bytes for the
+//    kernels of three_aug.hip); the kept
 //    patches only (no target wanted); and the loss itself
 //    (produce_loss_wave, produce_loss): the masked patches' values stay in registers, are
 //    normalised per patch and compared with the prediction, so that no float target is ever
@@ -617,7 +618,8 @@ __device__ static void produce_loss_wave(const CropArgs& a, const uint32_t* tile
 // The per-image operation acts on the resized crop rounded to bytes.  Grayscale and solarisation
 // are pointwise, so they are applied to the rounded values while these are still in registers and
 // the result goes straight to `target` / `visible`; the images that drew the blur only get their
-// rounded bytes written (patch order) for the blur kernel.
+// rounded bytes written (patch order) for the blur kernel.  With "3 Aug+" all images leave as bytes
+// (kReduce below), the operation applied to those without the blur.
 //
 // Grayscale and the jitter's saturation step need whole pixels, so here a lane takes four
 // neighbouring pixels of a patch row (12 values) instead of four values -- two pixels when the

@@ -1,9 +1,11 @@
-// Gaussian blur of the finetuning augmentation "3 Aug" / "3 Aug+" (Sec. 3 finetuning recipe,
-// Sec. 4.4 "Data Augmentation", Sec. 5.2 Table 7).  Per image one of grayscale / solarisation /
+// Gaussian blur and colour jitter of the finetuning augmentation "3 Aug" / "3 Aug+" (Sec. 3 finetuning
+// recipe, Sec. 4.4 "Data Augmentation", Sec. 5.2 Table 7).  Per image one of grayscale / solarisation /
 // Gaussian blur is drawn; the first two are pointwise and run as the epilogue of the resampling
 // kernel, which leaves the rounded 8-bit resized crop of the blur images in patch order
-// ([B, L, D] bytes, the layout of `target`).  This kernel blurs them, applies the colour jitter
-// of "3 Aug+", normalises and writes `target` / `visible`.
+// ([B, L, D] bytes, the layout of `target`), and with "3 Aug+" also those of the others, after their
+// operation.  aug_blur_kernel blurs the former, applies the colour jitter of "3 Aug+", normalises and
+// writes `target` / `visible`; aug_jitter_kernel, at the end of the file, does the same for the
+// others without the blur.
 //
 // aug_blur_kernel: one workgroup per image, row of patches and column part of whole patches; it
 // leaves at once when its image drew another operation.
