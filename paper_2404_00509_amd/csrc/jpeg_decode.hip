@@ -28,14 +28,14 @@
 //    a crop touches (or per piece of such a row where the parallel walk has found the pieces'
 //    states); the coefficients go to the plane buffer as 16-bit values, those of 4:4:4 crops of more
 //    than half a slot in part to the region buffer.
-//  * jpeg_decode_kernel (what is left: restart intervals that end inside a row, and crops of the whole
-//    slot with 4:4:4 sampling and more than 64 MCUs in a row): rows dealt to the lanes in the same way.  A lane's
-//    file bytes come through its column of a ring in LDS that is fed at the start of every
-//    block, where all lanes are at the same instruction; the bit buffer takes four bytes at a
-//    time unless one of them is 0xFF.  Per block: DC difference, AC symbols with one table
-//    look-up each (code and value bits out of the same 32-bit peek), de-quantisation on
-//    insertion, fixed-point separable inverse DCT in LDS, eight 8-byte stores into the image's
-//    Y, Cb or Cr plane.
+//  * jpeg_decode_kernel (what is left: restart intervals that end inside a row, and crops of the
+//    whole slot with 4:4:4 sampling and more than 64 MCUs in a row): rows dealt to the lanes in the
+//    same way.  A lane's file bytes come through its column of a ring in LDS that is fed at the
+//    start of every block, where all lanes are at the same instruction; the bit buffer takes four
+//    bytes at a time unless one of them is 0xFF.  Per block: DC difference, AC symbols with one
+//    table look-up each (code and value bits out of the same 32-bit peek), de-quantisation on
+//    insertion, fixed-point separable inverse DCT in LDS, eight 8-byte stores into the image's Y,
+//    Cb or Cr plane.
 //  * jpeg_idct_kernel: coefficients (inverse transform) or planes -> interleaved RGB rows of the
 //    region (repeated chroma, fixed-point JFIF colour matrix), which is what the resampling kernel
 //    reads.
@@ -587,8 +587,9 @@ __device__ static inline bool pieces_fit(const JpegArgs& a, int size, int scan_o
 
 // Entropy-coded data from scan_off to the first marker, byte stuffing removed, into `clean`, with
 // the file position of every 16th byte in `map`; returns how many bytes, + kCutShort when the file
-// ends before a marker does it (whole wavefront).  The file is read in aligned 16-byte pieces, one per lane, the next step's in flight; a prefix sum
-// gives each piece its place in the LDS buffer, which leaves in 1-KiB stores.
+// ends before a marker does it (whole wavefront).  The file is read in aligned 16-byte pieces, one
+// per lane, the next step's in flight; a prefix sum gives each piece its place in the LDS buffer,
+// which leaves in 1-KiB stores.
 __device__ static int jpeg_unstuff(const JpegArgs& a, int64_t origin, int scan_off, int n,
                                    uint8_t* stage, uint8_t* clean, int32_t* map) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -671,15 +672,15 @@ __device__ static int jpeg_unstuff(const JpegArgs& a, int64_t origin, int scan_o
   return done + fill + cut;
 }
 
-// Coefficients with 4:4:4 sampling take twice the slot for a crop that fills it.  As many of the crop's
-// last rows of MCUs as the image's slot of the plane buffer holds go there; the first rows, of which
-// this is the number, go to the end of its slot of the region buffer.  One workgroup of
-// jpeg_idct_kernel then takes the rows in order (with such crops by jpeg_decode_kernel to planes, beside
-// others by coefficients, a batch waited for one and the other: 512 files of 256 pixels, 4:4:4, a
-// restart interval per row: 3.94 -> 1.2 ms; 4096 files 5.84 -> 3.8; all of them by planes 3.2 and 4.0): the pixels of rows 0 .. r need (r + 1) half rows of
-// coefficients from the slot's start on, and the rows of coefficients behind r start at or behind
-// that, as all that are there (never more than the slot, whose side is a multiple of two MCUs) end
-// with it.
+// Coefficients with 4:4:4 sampling take twice the slot for a crop that fills it.  As many of the
+// crop's last rows of MCUs as the image's slot of the plane buffer holds go there; the first rows,
+// of which this is the number, go to the end of its slot of the region buffer.  One workgroup of
+// jpeg_idct_kernel then takes the rows in order (with such crops by jpeg_decode_kernel to planes,
+// beside others by coefficients, a batch waited for one and the other: 512 files of 256 pixels,
+// 4:4:4, a restart interval per row: 3.94 -> 1.10 ms; 4096 files 5.85 -> 3.77; all of them by
+// planes 3.19 and 3.98): the pixels of rows 0 .. r need (r + 1) half rows of coefficients from the
+// slot's start on, and the rows of coefficients behind r start at or behind that, as all that are
+// there (never more than the slot, whose side is a multiple of two MCUs) end with it.
 __device__ static inline int spilled_rows(int64_t slot_bytes, int64_t row_bytes, int nrows) {
   return max(0, nrows - (int)(slot_bytes / row_bytes));
 }
@@ -1211,18 +1212,19 @@ __device__ static void coef_tables(const JpegImage& im, uint16_t* tables) {
 }
 
 // ---- files that are one chain of codes: where does each of the crop's rows start? ----------------
-// Huffman codes re-synchronise (Ferguson and Rabinowitz, "Self-synchronizing Huffman codes", 1984; used
-// to decode JPEG files in parallel by Klein and Wiseman, 2003): a decoder set down anywhere in the data soon reads the same blocks
-// as one that came from the start (measured over the synthetic files: after 700 bits at the median,
-// 4000 at the 99th percentile; white noise 2000 / 15000).  The wavefront cuts the data into 64
-// equal parts, a lane each.  Every lane walks its part from a guessed block boundary and notes the
-// one (bit position and block of the MCU) at which it leaves the part, which is where the next
-// lane should have entered.  A lane whose entry turns out to be another walks again, but only
-// until it meets its earlier walk at one of the marks in its part.  The first lane's entry is
-// known, so after i rounds the first i lanes are right, whatever the guesses were: when no entry
-// changes any more the result is that of the walk from the start (64 rounds at most, three or
-// four in practice).  Prefix sums over the parts' block counts and DC differences then say in
-// which part each row of MCUs starts, and a lane per row walks there from the mark before it.
+// Huffman codes re-synchronise (Ferguson and Rabinowitz, "Self-synchronizing Huffman codes", 1984;
+// used to decode JPEG files in parallel by Klein and Wiseman, 2003): a decoder set down anywhere in
+// the data soon reads the same blocks as one that came from the start (measured over the synthetic
+// files: after 700 bits at the median, 4000 at the 99th percentile; white noise 2000 / 15000).  The
+// wavefront cuts the data into 64 equal parts, a lane each.  Every lane walks its part from a
+// guessed block boundary and notes the one (bit position and block of the MCU) at which it leaves
+// the part, which is where the next lane should have entered.  A lane whose entry turns out to be
+// another walks again, but only until it meets its earlier walk at one of the marks in its part.
+// The first lane's entry is known, so after i rounds the first i lanes are right, whatever the
+// guesses were: when no entry changes any more the result is that of the walk from the start (64
+// rounds at most, three or four in practice).  Prefix sums over the parts' block counts and DC
+// differences then say in which part each row of MCUs starts, and a lane per row walks there from
+// the mark before it.
 //
 // The bits come from the data without byte stuffing, so topping up is a select.  1024 files of 256
 // pixels: 0.65 ms, on one wavefront per SIMD, bound by the steps' issue and latency (with DC and AC
@@ -1764,15 +1766,15 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_decode_kernel(JpegArgs a) {
 // its place (zig-zag order) in the image's coefficients, which the table kernel has cleared.  Every
 // kSteps steps come the things that only some lanes need: the next block's DC coefficient and the
 // file bytes; a lane that ends its block in between waits for that point, three steps on average.
-// There is one wavefront per SIMD at most, so what counts is the number of instructions and LDS round
-// trips per symbol; the inverse transform, which needs neither, is left to jpeg_idct_kernel, where it
-// fills the chip.  Every step stores: a symbol without a value a zero where one is (the last of the
-// coefficients that it skips), and the blocks to the left of the crop go where the row's first block
-// will be, which is cleared once they are behind.
-// The file's bytes lose their stuffing on the way into the ring (SymbolReader): topping up
-// the bit buffer is then a select.  4096 files of 256 pixels with a restart interval per row: 0.80 ms and
-// 0.25 ms for the inverse transform and colours (entropy decoding and transform by the same lanes,
-// block after block, as in jpeg_decode_kernel: 1.42 ms and 0.20 ms for the colours); 1024 files without
+// There is one wavefront per SIMD at most, so what counts is the number of instructions and LDS
+// round trips per symbol; the inverse transform, which needs neither, is left to jpeg_idct_kernel,
+// where it fills the chip.  Every step stores: a symbol without a value a zero where one is (the
+// last of the coefficients that it skips), and the blocks to the left of the crop go where the
+// row's first block will be, which is cleared once they are behind. The file's bytes lose their
+// stuffing on the way into the ring (SymbolReader): topping up the bit buffer is then a select.
+// 4096 files of 256 pixels with a restart interval per row: 0.80 to 0.84 ms and 0.25 ms for the
+// inverse transform and colours (entropy decoding and transform by the same lanes, block after
+// block, as in jpeg_decode_kernel: 1.42 ms and 0.20 ms for the colours); 1024 files without
 // markers, rows in pieces: 0.22 + 0.07 ms (1.34 + 0.04 ms).
 struct SymbolReader {
   const uint8_t* chunks;  // as in BitReader

@@ -16,11 +16,12 @@
 
 namespace mae {
 
-// exp(x) as the degree-13 Taylor polynomial in Horner form; |x| <= 1/2.  The divisions by 13 .. 1 are
-// rounded like a division instruction's, at a tenth of its length: the product with the rounded
-// reciprocal of k is within one unit in the last place of the quotient (for k <= 13 the reciprocal is
-// at most 2^-54 of its value off, which is less than half a unit, and the product's rounding at most
-// another half), and one correction by the exact remainder rounds it correctly (Markstein's theorem).  This chain was the longest of the kernel.
+// exp(x) as the degree-13 Taylor polynomial in Horner form; |x| <= 1/2.  The divisions by 13 .. 1
+// are rounded like a division instruction's, at a tenth of its length: the product with the rounded
+// reciprocal of k is within one unit in the last place of the quotient (for k <= 13 the reciprocal
+// is at most 2^-54 of its value off, which is less than half a unit, and the product's rounding at
+// most another half), and one correction by the exact remainder rounds it correctly (Markstein's
+// theorem).  This chain was the longest of the kernel.
 __device__ static double exp_poly(double x) {
   double e = 1.0;
 #pragma unroll
