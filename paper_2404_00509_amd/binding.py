@@ -229,10 +229,16 @@ def _check(t, name, dtypes=None, numel=None, optional=False):
         raise ValueError(f"{name} holds {t.numel()} elements, {numel} are needed")
 
 
+# The current stream's handle alone: a Stream object around it costs more than a launch.  Not public
+# in torch, so it may be missing.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
-    # (the current stream's handle alone: a Stream object around it costs more than a launch)
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
 
