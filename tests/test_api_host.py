@@ -408,3 +408,16 @@ def test_binding_rejects_host_tensors_before_any_call():
         mae.make_loss_desc(pred, pred, torch.zeros(1, 4, dtype=torch.uint8), num_masked=1)
     with pytest.raises(ValueError, match="device memory"):
         mae.make_embed_desc(pred.to(torch.bfloat16), None, pred[0].to(torch.bfloat16))
+
+
+def test_current_stream_without_the_direct_call(monkeypatch):
+    """Where torch lacks the direct call, the handle comes from the public Stream object."""
+    class Stream:
+        cuda_stream = 1234
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    monkeypatch.setattr(binding.torch.cuda, "current_stream", lambda: Stream)
+    assert binding._stream(None) == 1234
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 10 + device)
+    monkeypatch.setattr(binding.torch.cuda, "current_device", lambda: 3)
+    assert binding._stream(None) == 13
+    assert binding._stream(Stream) == 1234
