@@ -288,7 +288,7 @@ def test_files_the_decoder_does_not_take_are_flagged_and_take_no_part():
 
 
 @pytest.mark.parametrize("restart_rows", [0, 1, 2])
-def test_coefficients_around_the_size_of_the_plane_slot(restart_rows):
+def test_coefficients_and_planes_in_one_batch(restart_rows):
     """4:4:4 files whose crops are around half the slot: the coefficients of some fit the plane
     buffer, of the others the first rows go to the region buffer.  Tables with codes that the direct tables leave out
     (optimised, quality 100), and crops that start right of the first MCU."""
@@ -330,6 +330,30 @@ def test_coefficients_of_up_to_twice_the_plane_slot(side, shapes, restart_rows):
         buf, _ = _gpu_jpeg_prep(files, offsets, sizes, max_image_side=side, **kw)
         assert mae.mae_prep_status(buf.workspace) == 0
         check_prep_against_oracle(prep_to_numpy(buf), ref, what=f"side {side} scale {scale}")
+
+
+@pytest.mark.parametrize("restart_rows", [0, 1])
+def test_large_files_with_wrong_bytes_next_to_good_ones(restart_rows):
+    """Noise in the entropy-coded data of 4:4:4 files whose rows spill: wrong pixels or a flagged
+    sample; the files around them in the buffers are what they are alone."""
+    B, S = 7, 64
+    files, offsets, sizes = synth.make_jpegs("gradient", B, seed=77, quality=95, subsampling="4:4:4",
+                                             restart_rows=restart_rows)
+    decoded = _decode_all(files, offsets, sizes)
+    files = files.copy()
+    rng = np.random.default_rng(78)
+    wrong = (1, 2, 5)
+    for b in wrong:
+        lo, hi = offsets[b] + sizes[b] // 3, offsets[b] + sizes[b] - 200
+        files[lo:hi] = rng.integers(0, 255, hi - lo)        # no 0xFF: no marker among them
+    kw = dict(out_size=S, patch=16, num_keep=4, scale=(1.0, 1.0), ratio=(0.61, 1.6), seed=35,
+              batch_index=1)
+    ref = oracle.prep_batch(*decoded, **kw)
+    buf, _ = _gpu_jpeg_prep(files, offsets, sizes, **kw)
+    assert bool(torch.isfinite(buf.target).all()) and bool(torch.isfinite(buf.visible).all())
+    keep = [b for b in range(B) if b not in wrong]
+    sel = {k: (v[keep] if v is not None else None) for k, v in ref.items()}
+    check_prep_against_oracle(prep_to_numpy(buf, rows=keep), sel, what="good files")
 
 
 def test_files_without_markers_whose_data_ends_early():
