@@ -126,15 +126,15 @@ __device__ inline uint32_t xcd_remap(uint32_t wg, uint32_t n) {
   return xcd < r ? xcd * (q + 1) + pos : r * (q + 1) + (xcd - r) * q + pos;
 }
 
-// ---- float -> bfloat16, round to nearest even (finite inputs) ----------------------------------
-__device__ inline uint32_t bf16_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return u >> 16;
-}
+// ---- float -> bfloat16, round to nearest even -----------------------------------------------------
+// One instruction for two values (v_cvt_pk_bf16_f32); rounded by integer arithmetic a pair takes seven,
+// which kernels that write bf16 and are bound by vector instructions paid for.
+typedef float bf16_in2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16_out2 __attribute__((ext_vector_type(2)));
 __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
-  return bf16_rne(lo) | (bf16_rne(hi) << 16);
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((bf16_in2{lo, hi}), bf16_out2));
 }
+__device__ inline uint32_t bf16_rne(float f) { return pack_bf16x2(f, 0.0f) & 0xFFFFu; }
 __device__ inline float bf16_lo(uint32_t v) { return __uint_as_float(v << 16); }
 __device__ inline float bf16_hi(uint32_t v) { return __uint_as_float(v & 0xFFFF0000u); }
 
