@@ -101,6 +101,28 @@ def test_embed_matches_the_oracle(M, D, E, L, bf16_out):
     _check(tokens, ref, S, D, bf16_out, f"M{M} D{D} E{E} L{L}")
 
 
+# The launch takes 256 x 256 tiles from 512 of them on, 128 x 128 from 128 of those on, else 64 x 64:
+# the sizes on either side of both lines, ragged in both directions, rows of every kind of last slice
+# (whole, half a chunk alone, one to four sub-steps with and without a half chunk) and fewer slices
+# than stages.
+@pytest.mark.parametrize("D", [4, 16, 20, 40, 52, 64, 128, 140, 192, 200])
+@pytest.mark.parametrize("M,E", [(4090, 8190), (4093, 8188), (3838, 8190), (1020, 2041), (1020, 1916)])
+def test_embed_tile_sizes_and_last_slices(M, E, D):
+    L = 49
+    vis, w, bias, pos, ids = _inputs(17 + D, M, D, E, L)
+    rows = np.unique(np.concatenate([np.arange(0, 40), np.arange(M - 40, M), np.arange(250, 262),
+                                     np.random.default_rng(D).integers(0, M, 60)]))
+    ref, S = _reference(vis[rows], w, bias, pos, ids[rows])
+    padded = torch.from_numpy(np.concatenate([[0], bias]).astype(np.float32)).cuda()
+    for bf16_out in (True, False):
+        tokens, (dv, dw, _, dp, di, _) = _gpu(vis, w, bias, pos, ids, bf16_out)
+        _check(tokens[torch.from_numpy(rows).cuda()], ref, S, D, bf16_out, f"M{M} D{D} E{E}")
+        again = torch.full_like(tokens, float("nan"))  # a bias that starts on no 16-byte boundary
+        mae.mae_patch_embed(mae.make_embed_desc(dv, di, dw, padded[1:], dp, out_dtype=mae.MAE_BF16
+                                                if bf16_out else mae.MAE_F32), again)
+        assert torch.equal(again, tokens)
+
+
 @pytest.mark.parametrize("with_bias,with_pos", [(False, False), (True, False), (False, True)])
 def test_embed_optional_terms(with_bias, with_pos):
     M, D, E, L = 300, 588, 200, 256
