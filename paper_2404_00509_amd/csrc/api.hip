@@ -188,7 +188,7 @@ PrepWorkspace prep_workspace(const mae_prep_desc* d) {
       // resampling kernel
       const size_t rows = (size_t)d->B * (d->out_size / d->patch);
       w.crop_partials_offset =
-          w.total + rows * mae::three_aug_plan(d->out_size, d->patch).parts * sizeof(double);
+          w.total + (size_t)d->B * mae::blur_luma_slots(d->out_size, d->patch) * sizeof(double);
       w.total = w.crop_partials_offset +
                 rows * (size_t)crop_plan_of(d, w.slot_side).col_parts * sizeof(double);
     }
@@ -376,6 +376,7 @@ int mae_prep_batch(const mae_prep_desc* d, void* visible, uint8_t* mask, int32_t
   const mae::AugPlan aplan = mae::three_aug_plan(d->out_size, d->patch);
   aa.blur_parts = aplan.parts;
   aa.blur_part_patches = aplan.part_patches;
+  aa.band_parts = mae::blur_band_parts(d->out_size, d->patch);
   for (int c = 0; c < 3; ++c) {
     aa.nscale[c] = ca.nscale[c];
     aa.nbias[c] = ca.nbias[c];

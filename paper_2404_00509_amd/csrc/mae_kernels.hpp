@@ -111,12 +111,15 @@ struct AugArgs {
   int32_t luma_slots;
   void* visible;
   float* target;  // nullable
+  int32_t band_parts;  // luma sums per 16 rows (blur on the matrix cores): column parts
 };
 struct AugPlan {
   int parts, part_patches;
   size_t lds_bytes;
 };
 AugPlan three_aug_plan(int S, int p);
+int blur_luma_slots(int S, int p);  // per image: luma sums that launch_aug_blur leaves
+int blur_band_parts(int S, int p);
 // The blur images of a batch.  reduce: only their luma sums after the brightness step ("3 Aug+").
 hipError_t launch_aug_blur(const AugArgs& a, bool reduce, hipStream_t stream);
 // "3 Aug+": colour jitter, normalisation and the outputs of the images without the blur.

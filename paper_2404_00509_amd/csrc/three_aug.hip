@@ -7,8 +7,9 @@
 // writes `target` / `visible`; aug_jitter_kernel, at the end of the file, does the same for the
 // others without the blur.
 //
-// aug_blur_kernel: one workgroup per image, row of patches and column part of whole patches; it
-// leaves at once when its image drew another operation.
+// aug_blur_band_kernel, for patches of 16 and 32 pixels: on the matrix cores (see there).
+// aug_blur_kernel, for other even patch sizes: one workgroup per image, row of patches and column part of
+// whole patches; it leaves at once when its image drew another operation.
 //  * Staging.  The bytes of the part's rows and of R more rows above and below, over the part's
 //    patches and the neighbouring patch on either side, are copied into LDS in image order (all
 //    loads of a thread issued before the first is stored).  Rows beyond the image repeat its
@@ -24,7 +25,9 @@
 // the parameter kernel (one record per image) and sit in scalar registers.
 // The contrast step needs the mean luma of the whole image after the brightness step: with jitter
 // on, a first launch of the same kernel (kReduce) only accumulates that sum per part in double
-// precision, and the second launch adds the partial sums of its image in fixed order.
+// precision, and the second launch adds the partial sums of its image in fixed order.  Where the
+// brightness factor is at most 1 nothing is clamped and the blur is linear: the sum is then one over the
+// bytes (band_luma_sum).
 #include "aug_device.hpp"
 #include "mae_device.hpp"
 #include "mae_kernels.hpp"
@@ -37,6 +40,7 @@ constexpr int kMaxRadius = 6;  // ceil(3 * 2.0)
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef u32x2 u32x2_a4 __attribute__((aligned(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef u32x3 u32x3_a4 __attribute__((aligned(4)));
@@ -358,6 +362,285 @@ __global__ __launch_bounds__(kAugThreads) void aug_blur_kernel(AugArgs a) {
     blur_part<6, kReduce, kBf16, kPx>(a, ap, b, gy, part, gx0, npatch, vbuf, scratch, red);
 }
 
+// ---- Gaussian blur on the matrix cores ----------------------------------------------------------------
+// Patches whose side is a multiple of 16 (16 and 32).  Both passes are products with a band matrix of
+// taps (v_mfma_f32_16x16x32_bf16), so the vector ALUs, which bound the kernel above at 26 multiply-adds
+// per value, are left with the operands' conversion and the epilogue.  Nothing is lost by the 16-bit
+// operands: a byte is exact in bf16, a tap is the sum of three bf16 values of 8 bits each, and so is,
+// to its last bit or half of it, a value between the passes.  All products of the parts that reach 2^-24
+// of the result are taken, the smallest first, and added in fp32.
+// (The fp32 form of the instruction, v_mfma_f32_16x16x4f32, needs no parts but runs no faster than the
+// vector ALUs and not beside them: 355 us for the outputs and 267 for all sums of the launch below.)
+//
+// A wavefront takes 16 rows of an image, or a part of them, and walks along x in steps of 16 pixels;
+// nothing is shared, so there is no barrier and no LDS.
+//  * Vertical: V[x, y] = sum over 32 rows r of X[x, r] T[r, y], a channel at a time, for the 16 pixels from
+//    16 j - 8 on.  The rows come straight from memory: lane (x, g) loads the dwords that end with its
+//    pixel's three bytes of rows 8 g .. 8 g + 7 (rows and columns beyond the image: the border's), the
+//    next tile's while this one is multiplied.
+//  * Horizontal: O[y, x] = sum over x' of V[y, x'] T[x', x] with the two tiles that hold the 16 pixels
+//    and eight more on either side.  The instruction leaves V with x' = 4 g + e in register e of lane
+//    group g and takes eight consecutive indices of the sum from a lane group: the registers of the two
+//    tiles as they are, with the taps in the same order.
+// The 16 rows go through the columns of V in the order 0, 4, 8, 12, 1, ..: a lane then ends with pixel x of
+// rows g, 4 + g, 8 + g, 12 + g, and a store instruction covers four whole rows of the tile.
+// 4096 images of 224 pixels ("3 Aug+", a third of them blurred): 322 us for the outputs and 125 for the luma
+// sums (518 and 358 us by the kernel above); 1024 images of 160 pixels, "3 Aug": 37 us (65).  Bound by the
+// vector instructions of the epilogue and of the splits, and by the stores (0.8 GB).
+typedef uint32_t u32_a1 __attribute__((aligned(1)));
+typedef float f32x3 __attribute__((ext_vector_type(3)));
+typedef f32x3 f32x3_a4 __attribute__((aligned(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+constexpr int kBandRows = 16;
+
+// Pairs of values as three pairs of bf16 that add up to them.
+__device__ static inline void split3(float x, float y, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+  hi = pack_bf16x2(x, y);
+  x -= bf16_lo(hi);
+  y -= bf16_hi(hi);
+  mid = pack_bf16x2(x, y);
+  lo = pack_bf16x2(x - bf16_lo(mid), y - bf16_hi(mid));
+}
+__device__ static inline f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// A wavefront's rows of an image's bytes (patch order): the lane's pixel 16 j + shift + lane % 16 of kRows
+// rows, row i of which is first + stride i, as dwords whose upper three bytes are its channels.
+template <int kRows>
+struct BandPixels {
+  const uint8_t* img;
+  uint32_t row[kRows];
+  int psh, p, D, S, shift;
+  __device__ inline void open(const AugArgs& a, int b, int first, int stride, int shift_) {
+    p = a.p;
+    psh = __builtin_ctz(p);  // (16 or 32)
+    D = a.D;
+    S = a.S;
+    shift = shift_ + (int)(threadIdx.x & 15);
+    img = a.u8 + (int64_t)b * a.L * D - 1;  // (the workspace begins further in front)
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+      const int y = min(max(first + stride * i, 0), S - 1);
+      row[i] = (uint32_t)((y >> psh) * a.G * D + (y & (p - 1)) * 3 * p);
+    }
+  }
+  __device__ inline void load(int j, uint32_t* px) const {
+    const int x = min(max(16 * j + shift, 0), S - 1);
+    const uint32_t column = (uint32_t)((x >> psh) * D + (x & (p - 1)) * 3);
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) px[i] = *reinterpret_cast<const u32_a1*>(img + (row[i] + column));
+  }
+};
+__device__ static inline float channel_of(uint32_t px, int c) {
+  return (float)((px >> (8 * c + 8)) & 0xFFu);
+}
+
+__device__ static inline void store_luma_sum(const AugArgs& a, int b, int slot, float lsum) {
+  double sum = (double)lsum;  // lanes by butterfly
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+  if (threadIdx.x % kWave == 0)
+    a.partials[(int64_t)b * (a.S / kBandRows) * a.band_parts + slot] = sum;
+}
+
+// The luma sum after the brightness step where nothing is clamped by it (a factor of at most 1): the blur
+// is linear, so the sum over the blurred image is one over the bytes, weighted with what every pixel
+// contributes: the sum of the taps in x and in y, of which those beyond the border fall to its pixel.
+__device__ static void band_luma_sum(const AugArgs& a, const AugParams& ap, int b, int y0, int tile0,
+                                     int tile1, int slot) {
+  const int lane = threadIdx.x % kWave, g = lane >> 4;
+  const float taps = static_cast<const AugParams*>(a.aug_recs)[b].tap[lane & 7];
+  float half = 0.0f, near = 0.0f, edge = 0.0f;  // taps 0 .. 6; 1 .. lane; sum of (d + 1) tap[d]
+#pragma unroll
+  for (int d = 0; d <= kMaxRadius; ++d) {
+    const float t = __shfl(taps, d, kWave);
+    half += t;
+    near += d >= 1 && d <= lane ? t : 0.0f;
+    edge += (float)(d + 1) * t;
+  }
+  // lane q: the weight of a pixel q pixels off the nearest border (6: or more)
+  const float weights = lane == 0 ? edge : half + near;
+  const auto weight = [&](int at) { return __shfl(weights, min(min(at, a.S - 1 - at), kMaxRadius), kWave); };
+  BandPixels<4> rows;
+  rows.open(a, b, y0 + g, 4, 0);
+  float wy[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) wy[e] = weight(y0 + 4 * e + g);
+  float lsum = 0.0f;
+  uint32_t px[4], next[4];
+  rows.load(tile0, px);
+  for (int j = tile0; j < tile1; ++j) {
+    rows.load(min(j + 1, tile1 - 1), next);
+    const float wx = weight(16 * j + (lane & 15));
+    float sum = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sum += wy[e] * luma(channel_of(px[e], 0), channel_of(px[e], 1), channel_of(px[e], 2));
+      px[e] = next[e];
+    }
+    lsum += wx * sum;
+  }
+  store_luma_sum(a, b, slot, lsum * ap.brightness);
+}
+
+template <bool kReduce, bool kBf16>
+__device__ static void blur_band(const AugArgs& a, const AugParams& ap, int b, int y0, int tile0,
+                                 int tile1, int slot) {
+  const int lane = threadIdx.x % kWave, lx = lane & 15, g = lane >> 4;
+  const int S = a.S, p = a.p, D = a.D;
+  const int psh = __builtin_ctz(p);
+  BandPixels<8> rows;
+  rows.open(a, b, y0 - 8 + 8 * g, 1, -8);
+  uint32_t px[8];
+  rows.load(tile0, px);
+
+  const float taps = static_cast<const AugParams*>(a.aug_recs)[b].tap[lane & 7];
+  const auto tap = [&](int d) { return __shfl(taps, min(abs(d), 7), kWave); };  // ([7] is zero)
+  u32x4 tv[3], th[3];  // parts of the vertical and the horizontal taps
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int dy = 2 * i + 8 * g - 8 - (4 * (lx & 3) + (lx >> 2));
+    const int dx = (i < 2 ? 2 * i - 8 : 2 * i + 4) + 4 * g - lx;
+    uint32_t hi, mid, lo;
+    split3(tap(dy), tap(dy + 1), hi, mid, lo);
+    tv[0][i] = hi;
+    tv[1][i] = mid;
+    tv[2][i] = lo;
+    split3(tap(dx), tap(dx + 1), hi, mid, lo);
+    th[0][i] = hi;
+    th[1][i] = mid;
+    th[2][i] = lo;
+  }
+
+  // noise rank of the patch of tile (tile0 + lane), and the mean luma after the brightness step
+  const int l0 = (y0 >> psh) * a.G;
+  const int my_tile = min(tile0 + lane, tile1 - 1);
+  const int my_rank =
+      kReduce ? 0 : a.ids_restore[(int64_t)b * a.L + l0 + ((16 * my_tile) >> psh)];
+  float mean = 0.0f;
+  if (!kReduce && a.mode == 2) {
+    const int slots = (S / kBandRows) * a.band_parts;
+    double sum = 0.0;
+    for (int i = lane; i < slots; i += kWave) sum += a.partials[(int64_t)b * slots + i];
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+    mean = (float)(sum / ((double)S * (double)S));
+  }
+
+  float* target_image = a.target ? a.target + (int64_t)b * a.L * D : nullptr;
+  const int64_t visible_base = (int64_t)b * a.K * D;
+  const uint32_t in_patch_row = (uint32_t)((y0 & (p - 1)) + g) * (uint32_t)(3 * p) + 3u * (uint32_t)lx;
+  float lsum = 0.0f;
+  // parts of V, the two tiles of the horizontal pass: [channel][part], registers 0, 1 the left tile's
+  u32x4 v[3][3];
+  for (int j = tile0; j <= tile1; ++j) {
+    f32x4 cur[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      u32x4 x;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)  // (whole numbers below 256: the upper halves of the floats)
+        x[i] = __builtin_amdgcn_perm(__float_as_uint(channel_of(px[2 * i + 1], c)),
+                                     __float_as_uint(channel_of(px[2 * i], c)), 0x07060302u);
+      cur[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+      cur[c] = mfma_bf16(x, tv[2], cur[c]);
+      cur[c] = mfma_bf16(x, tv[1], cur[c]);
+      cur[c] = mfma_bf16(x, tv[0], cur[c]);
+    }
+    if (j < tile1) rows.load(j + 1, px);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+#pragma unroll
+      for (int part = 0; part < 3; ++part) {
+        v[c][part][0] = v[c][part][2];
+        v[c][part][1] = v[c][part][3];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        uint32_t hi, mid, lo;
+        split3(cur[c][2 * i], cur[c][2 * i + 1], hi, mid, lo);
+        v[c][0][2 + i] = hi;
+        v[c][1][2 + i] = mid;
+        v[c][2][2 + i] = lo;
+      }
+    }
+    if (j == tile0) continue;
+    f32x4 out[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      out[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+      out[c] = mfma_bf16(v[c][2], th[0], out[c]);
+      out[c] = mfma_bf16(v[c][0], th[2], out[c]);
+      out[c] = mfma_bf16(v[c][1], th[1], out[c]);
+      out[c] = mfma_bf16(v[c][1], th[0], out[c]);
+      out[c] = mfma_bf16(v[c][0], th[1], out[c]);
+      out[c] = mfma_bf16(v[c][0], th[0], out[c]);
+    }
+    const int tile = j - 1;
+    const int rank = __builtin_amdgcn_readlane(my_rank, tile - tile0);
+    const int l = l0 + ((16 * tile) >> psh);
+    const uint32_t at0 = in_patch_row + (uint32_t)(3 * ((16 * tile) & (p - 1)));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float v0 = out[0][e], v1 = out[1][e], v2 = out[2][e];
+      if (a.mode == 2) {
+        const float lum = jitter_pixel<kReduce>(ap, mean, v0, v1, v2);
+        lsum += lum;
+      }
+      if constexpr (!kReduce) {
+        v0 = v0 * a.nscale[0] + a.nbias[0];
+        v1 = v1 * a.nscale[1] + a.nbias[1];
+        v2 = v2 * a.nscale[2] + a.nbias[2];
+        const uint32_t at = at0 + (uint32_t)(12 * e * p);
+        if (a.target)
+          *reinterpret_cast<f32x3_a4*>(target_image + ((uint32_t)(l * D) + at)) = f32x3{v0, v1, v2};
+        if (rank < a.K) {
+          const int64_t vo = visible_base + ((uint32_t)(rank * D) + at);
+          if constexpr (kBf16) {
+            // two pixels are three dwords: two from the left one's lane, one from the right one's
+            const float next = __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp(
+                (int)__float_as_uint(v0), 0xF5 /* quad_perm 1, 1, 3, 3 */, 0xF, 0xF, true));
+            uint16_t* dst = static_cast<uint16_t*>(a.visible) + vo;
+            if (lane & 1)
+              *reinterpret_cast<uint32_t*>(dst + 1) = pack_bf16x2(v1, v2);
+            else
+              *reinterpret_cast<u32x2_a4*>(dst) = u32x2{pack_bf16x2(v0, v1), pack_bf16x2(v2, next)};
+          } else {
+            *reinterpret_cast<f32x3_a4*>(static_cast<float*>(a.visible) + vo) = f32x3{v0, v1, v2};
+          }
+        }
+      }
+    }
+  }
+  if constexpr (kReduce) store_luma_sum(a, b, slot, lsum);
+}
+
+template <bool kReduce, bool kBf16>
+__global__ __launch_bounds__(kAugThreads) void aug_blur_band_kernel(AugArgs a, int parts) {
+  const int bands = a.S / kBandRows, slots = bands * parts;
+  const uint32_t task = xcd_remap(blockIdx.x, gridDim.x) * (kAugThreads / kWave) +
+                        (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  const int b = (int)(task / (uint32_t)slots);
+  if (b >= a.B) return;
+  const int slot = (int)(task - (uint32_t)b * (uint32_t)slots);
+  const bool valid = reinterpret_cast<const CropRec*>(a.workspace + kWorkspaceHeader)[b].valid != 0;
+  if (!valid) return;
+  const AugParams ap = static_cast<const AugParams*>(a.aug_recs)[b];
+  if (ap.op != kOpBlur) return;
+  const int band = slot / parts, part = slot - band * parts;
+  const int tile0 = part * bands / parts, tile1 = (part + 1) * bands / parts;  // (as many tiles as bands)
+  if (tile0 == tile1) {
+    if (kReduce && threadIdx.x % kWave == 0) a.partials[(int64_t)b * slots + slot] = 0.0;
+    return;
+  }
+  if (kReduce && ap.brightness <= 1.0f)
+    band_luma_sum(a, ap, b, band * kBandRows, tile0, tile1, slot);
+  else
+    blur_band<kReduce, kBf16>(a, ap, b, band * kBandRows, tile0, tile1, slot);
+}
+
 // Bytes of dynamic LDS of the blur kernel for parts of n patches: the vertically blurred rows,
 // then the staged bytes (or the four wavefronts' strips, whichever is larger).
 static size_t blur_lds_bytes(int p, int n) {
@@ -384,9 +667,35 @@ AugPlan three_aug_plan(int S, int p) {
   }
 }
 
+// Luma sums per image: one per row of patches and column part, or per band and its part.
+int blur_luma_slots(int S, int p) {
+  const int slots = S / p * three_aug_plan(S, p).parts;
+  return (p & 15) == 0 ? max(slots, S / kBandRows) : slots;
+}
+// Column parts of a band of the matrix kernel: as many as there are slots for their luma sums.  (The same
+// for every batch size: an image's sum is added up in the same order in a batch and in a shard of it.)
+int blur_band_parts(int S, int p) {
+  return (p & 15) != 0 ? 1 : blur_luma_slots(S, p) / (S / kBandRows);
+}
+
 // The blur images of a batch.  reduce: only the luma sums after the brightness step ("3 Aug+").
 hipError_t launch_aug_blur(const AugArgs& a, bool reduce, hipStream_t stream) {
   dim3 block(kAugThreads);
+  if ((a.p & 15) == 0) {
+    // (outputs: whole bands where they fill the chip, as a part has one more tile of V to make)
+    const int bands = a.S / kBandRows;
+    const int parts = !reduce && (int64_t)a.B * bands >= 12288 ? 1 : a.band_parts;
+    const uint64_t tasks = (uint64_t)a.B * (uint64_t)(bands * parts);
+    constexpr int kPerBlock = kAugThreads / kWave;
+    dim3 grid((uint32_t)((tasks + kPerBlock - 1) / kPerBlock));
+    if (reduce)
+      hipLaunchKernelGGL((aug_blur_band_kernel<true, false>), grid, block, 0, stream, a, parts);
+    else if (a.visible_bf16)
+      hipLaunchKernelGGL((aug_blur_band_kernel<false, true>), grid, block, 0, stream, a, parts);
+    else
+      hipLaunchKernelGGL((aug_blur_band_kernel<false, false>), grid, block, 0, stream, a, parts);
+    return hipGetLastError();
+  }
   dim3 bgrid((uint32_t)a.B * (uint32_t)a.G * (uint32_t)a.blur_parts);
   const size_t lds = blur_lds_bytes(a.p, a.blur_part_patches);
   // four pixels per lane when they tile a patch row, else two (even patch sizes)

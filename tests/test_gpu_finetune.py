@@ -116,6 +116,37 @@ def test_patch_sizes_that_are_even_but_no_multiple_of_four(mode):
     check_prep_against_oracle(prep_to_numpy(buf), ref, bf16=True, what=f"p14 bf16 mode {mode}")
 
 
+# The blur on the matrix cores: the smallest image (one tile, both borders of a pixel within the radius of
+# each other's), patches of two tiles, one and several column parts, bf16 outputs, both luma sums
+# (brightness factors on either side of 1).
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("S,p", [(16, 16), (32, 32), (32, 16), (96, 32), (240, 16), (256, 16), (512, 32)])
+def test_blur_on_the_matrix_cores(S, p, bf16):
+    B, L = (12 if S < 512 else 6), (S // p) ** 2
+    data = synth.make_images("uniform", B, seed=61)
+    for seed in (21, 22):
+        kw = dict(out_size=S, patch=p, num_keep=max(1, L // 2), seed=seed, batch_index=1,
+                  aug_mode=mae.MAE_AUG_THREE_PLUS, jitter=0.3)
+        assert 2 in _ops(seed, 1, B)
+        ref = oracle.prep_batch(*data, **kw)
+        buf, _, _ = gpu_prep(*data, bf16=bf16, **kw)
+        check_prep_against_oracle(prep_to_numpy(buf), ref, bf16=bf16, what=f"S{S} p{p} seed {seed}")
+
+
+def test_blur_shard_equals_the_slice_of_a_large_batch():
+    # the large batch's outputs are made by whole bands, the shard's by parts of them
+    S, B, n = 64, 3200, 16
+    data = synth.make_images("uniform", 64, seed=62)
+    imgs, offs, hs, ws = data
+    many = (imgs, np.tile(offs, B // 64), np.tile(hs, B // 64), np.tile(ws, B // 64))
+    kw = dict(out_size=S, patch=16, num_keep=16, seed=14, batch_index=5,
+              aug_mode=mae.MAE_AUG_THREE_PLUS, jitter=0.3)
+    full, _, _ = gpu_prep(*many, **kw)
+    part, _, _ = gpu_prep(imgs, many[1][640:640 + n].copy(), many[2][640:640 + n].copy(),
+                          many[3][640:640 + n].copy(), sample_base=640, **kw)
+    assert torch.equal(part.target, full.target[640:640 + n])
+
+
 def test_shard_of_a_batch_and_reproducibility():
     S, B = 160, 16
     L = (S // 16) ** 2
