@@ -31,6 +31,11 @@ struct ParamArgs {
 hipError_t launch_params_mask(const ParamArgs& a, hipStream_t stream);
 
 // ---- crop + resize + flip + normalise + patchify + gather --------------------------------------
+// Rounding of the finetuning augmentation's bilinear values to bytes (round_blend3).
+struct RoundPlan {
+  int32_t shift, add, mul;
+};
+RoundPlan round_plan(int S);
 struct CropArgs {
   int32_t B, S, p, G, L, K, D;
   int32_t visible_bf16;  // 0: float, 1: bfloat16
@@ -77,6 +82,7 @@ struct CropArgs {
   // the kernels read, and crop_aug_kernel takes 2 % longer: 256 images of 500 pixels -> 128, p = 8,
   // 117.5 against 115.6 us.)
   int32_t max_side;
+  RoundPlan round;  // launch_crop_aug fills it in
 };
 struct CropPlan {
   int col_parts, part_patches, tile_pixels;

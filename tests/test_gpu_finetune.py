@@ -116,6 +116,20 @@ def test_patch_sizes_that_are_even_but_no_multiple_of_four(mode):
     check_prep_against_oracle(prep_to_numpy(buf), ref, bf16=True, what=f"p14 bf16 mode {mode}")
 
 
+# The byte rounding divides by a multiplication whose constant is rounded up or, for the sizes where that
+# is too much, down: those sizes (22, 44, 88, 90, 176, 180, 352, 360, 450) and the smallest and the largest.
+@pytest.mark.parametrize("S,p", [(2, 2), (22, 2), (44, 4), (88, 8), (90, 6), (176, 22), (180, 12), (352, 22),
+                                 (360, 24), (450, 30), (512, 32)])
+def test_byte_rounding_at_all_kinds_of_sizes(S, p):
+    B, L = 12, (S // p) ** 2
+    data = synth.make_images("uniform", B, seed=60 + S)  # noise: every fraction of the rounding
+    kw = dict(out_size=S, patch=p, num_keep=L, seed=12, batch_index=1, aug_mode=mae.MAE_AUG_THREE)
+    assert set(_ops(12, 1, B)) == {0, 1, 2}
+    ref = oracle.prep_batch(*data, **kw)
+    buf, _, _ = gpu_prep(*data, **kw)
+    check_prep_against_oracle(prep_to_numpy(buf), ref, what=f"S{S} p{p}")
+
+
 # The blur on the matrix cores: the smallest image (one tile, both borders of a pixel within the radius of
 # each other's), patches of two tiles, one and several column parts, bf16 outputs, both luma sums
 # (brightness factors on either side of 1).
