@@ -160,8 +160,16 @@ int crop_side_of(const mae_prep_desc* d, int slot_side) {
   if (d->input_format == MAE_INPUT_JPEG) return slot_side;
   return d->max_image_side > 0 ? d->max_image_side : 256;
 }
-mae::CropPlan crop_plan_of(const mae_prep_desc* d, int slot_side) {
-  return mae::crop_plan(d->out_size, d->patch, crop_side_of(d, slot_side), 0);
+mae::CropPlan crop_plan_of(const mae_prep_desc* d, int slot_side, mae::CropUse use) {
+  const int parts = use == mae::CropUse::kLoss
+                        ? mae::crop_loss_min_parts(d->B, d->out_size, d->patch)
+                        : 1;
+  const int side = crop_side_of(d, slot_side);
+  return mae::crop_plan(d->out_size, d->patch, side, parts,
+                        mae::crop_whole_rows(d->out_size, d->patch, side, use));
+}
+mae::CropUse prep_use(const mae_prep_desc* d) {
+  return d->aug_mode == MAE_AUG_SIMPLE ? mae::CropUse::kOutputs : mae::CropUse::kAugment;
 }
 PrepWorkspace prep_workspace(const mae_prep_desc* d) {
   auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
@@ -190,7 +198,7 @@ PrepWorkspace prep_workspace(const mae_prep_desc* d) {
       w.crop_partials_offset =
           w.total + (size_t)d->B * mae::blur_luma_slots(d->out_size, d->patch) * sizeof(double);
       w.total = w.crop_partials_offset +
-                rows * (size_t)crop_plan_of(d, w.slot_side).col_parts * sizeof(double);
+                rows * (size_t)crop_plan_of(d, w.slot_side, prep_use(d)).col_parts * sizeof(double);
     }
   }
   if (d->input_format == MAE_INPUT_JPEG) {
@@ -239,7 +247,7 @@ mae::JpegArgs make_jpeg_args(const mae_prep_desc* d, const PrepWorkspace& wsl, u
 // What the resampling kernel needs to know about the source, for both input formats: with JPEG
 // input its "images" are the decoded regions in the workspace.
 mae::CropArgs make_crop_args(const mae_prep_desc* d, const PrepShape& sh, const PrepWorkspace& wsl,
-                             const uint8_t* ws) {
+                             const uint8_t* ws, mae::CropUse use) {
   mae::CropArgs ca;
   memset(&ca, 0, sizeof(ca));
   ca.B = d->B;
@@ -250,11 +258,12 @@ mae::CropArgs make_crop_args(const mae_prep_desc* d, const PrepShape& sh, const 
   ca.K = d->num_keep;
   ca.D = sh.D;
   ca.visible_bf16 = d->out_dtype == MAE_BF16;
-  const mae::CropPlan plan = crop_plan_of(d, wsl.slot_side);
+  const mae::CropPlan plan = crop_plan_of(d, wsl.slot_side, use);
   ca.tile_pixels = plan.tile_pixels;
   ca.col_parts = plan.col_parts;
   ca.part_patches = plan.part_patches;
   ca.max_side = crop_side_of(d, wsl.slot_side);
+  ca.whole_rows = mae::crop_whole_rows(d->out_size, d->patch, ca.max_side, use);
   for (int c = 0; c < 3; ++c) {
     ca.nscale[c] = (float)(1.0 / (255.0 * (double)d->std[c]));
     ca.nbias[c] = (float)(-(double)d->mean[c] / (double)d->std[c]);
@@ -340,7 +349,7 @@ int mae_prep_batch(const mae_prep_desc* d, void* visible, uint8_t* mask, int32_t
   if (d->input_format == MAE_INPUT_JPEG && mae::launch_jpeg_decode(ja, stream) != hipSuccess)
     return MAE_ERR_HIP;
 
-  mae::CropArgs ca = make_crop_args(d, sh, wsl, ws);
+  mae::CropArgs ca = make_crop_args(d, sh, wsl, ws, prep_use(d));
   ca.ids_restore = ids_restore;
   ca.visible = visible;
   ca.target = target;
@@ -580,7 +589,8 @@ int validate_loss_from_images(const mae_prep_desc* p, const mae_loss_desc* d, Pr
 size_t mae_loss_from_images_workspace_bytes(const mae_prep_desc* p, const mae_loss_desc* d) {
   PrepShape sh;
   if (validate_loss_from_images(p, d, &sh) != MAE_OK) return 0;
-  const mae::CropArgs ca = make_crop_args(p, sh, prep_workspace(p), nullptr);
+  const mae::CropArgs ca =
+      make_crop_args(p, sh, prep_workspace(p), nullptr, mae::CropUse::kLoss);
   return (size_t)mae::crop_loss_partials(ca) * sizeof(double) +
          (size_t)mae::kMaxCounts * sizeof(int32_t);
 }
@@ -604,7 +614,8 @@ int mae_normpix_loss_from_images(const mae_prep_desc* p, const void* prep_worksp
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
 
   mae::CropArgs ca = make_crop_args(p, sh, prep_workspace(p),
-                                    static_cast<const uint8_t*>(prep_workspace_ptr));
+                                    static_cast<const uint8_t*>(prep_workspace_ptr),
+                                    mae::CropUse::kLoss);
   const double count = (double)d->D * (double)(d->num_masked > 0 ? d->num_masked : 1);
   ca.pred = d->pred;
   ca.grad = grad;

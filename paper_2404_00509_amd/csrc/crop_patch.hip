@@ -24,7 +24,7 @@
 //    that drew the blur, and all of them when the colour jitter follows, leave as bytes for the
 //    kernels of three_aug.hip); the kept
 //    patches only (no target wanted); and the loss itself
-//    (produce_loss_wave, produce_loss): the masked patches' values stay in registers, are
+//    (produce_loss_wave, produce_loss_group): the masked patches' values stay in registers, are
 //    normalised per patch and compared with the prediction, so that no float target is ever
 //    stored or read back.
 #include "aug_device.hpp"
@@ -37,6 +37,7 @@ constexpr int kCropThreads = 256;      // crop_patch_scalar_kernel
 constexpr int kCropMaxThreads = 1024;  // resampling kernel: 64 threads per 64 groups of a patch
 constexpr int kStageRows = 7;  // rows per wavefront whose loads are issued together
 constexpr int kCropMaxLds = 64 * 1024;      // dynamic LDS available without opting in to more
+constexpr int kCropFill = 1024;             // workgroups that a launch should have
 constexpr int kCropTileTarget = 40 * 1024;  // LDS per workgroup that still leaves 4 per compute unit
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -276,14 +277,30 @@ __device__ static void produce_pixels(const CropArgs& a, const uint32_t* tile, c
 }
 
 // ---- the loss without a stored target ---------------------------------------------------------------
-// Same decomposition as produce_patches (a thread owns one 16-byte group position of every patch
-// of the part), but the values stay in registers: per patch the workgroup adds them up for the
-// mean, then the squared deviations for the variance (two block reductions for all patches of a
-// chunk at once), and the masked patches' normalised values meet the prediction: squared error
-// into the workgroup's partial sum, gradient written with the same contiguous 16-byte stores.
+// The values of a patch stay in registers: they are added up for the mean, then the squared deviations
+// for the variance, and the masked patches' normalised values meet the prediction: squared error
+// into the workgroup's partial sum, gradient written with contiguous 16-byte stores.
 // Visible patches get a zero gradient and are not resampled.  `masked` holds, in lane i, whether
 // patch i of this part is masked.
-constexpr int kLossChunk = 8;  // patches whose values a thread holds at once
+// Patches of up to 768 values (p up to 16) are a wavefront's work each (produce_loss_wave), larger ones
+// a workgroup's of three wavefronts (produce_loss_group).
+
+// Sum over the wavefront, in all lanes: pairs of lanes whose numbers differ in one bit after each other,
+// all of it in vector instructions.
+__device__ static inline float wave_sum(float x) {
+#define MAE_ADD_DPP(CTRL)                                                                         \
+  x += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xF, \
+                                                             0xF, true))
+  MAE_ADD_DPP(0xB1);   // quad 1, 0, 3, 2
+  MAE_ADD_DPP(0x4E);   // quad 2, 3, 0, 1
+  MAE_ADD_DPP(0x124);  // row of 16 rotated by 4: quads are equal lanes by now
+  MAE_ADD_DPP(0x128);  // ... by 8
+#undef MAE_ADD_DPP
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+}
 
 // (read once, written once: the non-temporal hint keeps them from displacing the source rows)
 __device__ static inline f32x4 crop_load_pred4(const void* pred, int64_t elem, bool bf16) {
@@ -310,164 +327,185 @@ __device__ static inline float loss_gscale(const CropArgs& a) {
   return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(g)));
 }
 
-// Sums of v[0 .. kLossChunk) over the workgroup, lanes by butterfly and wavefronts in index
-// order; every thread gets all of them.  red: kLossChunk floats per wavefront.
-__device__ static inline void block_sums(float* v, float* red, int lane, int wave, int nwaves) {
-#pragma unroll
-  for (int j = 0; j < kLossChunk; ++j) {
-    float t = v[j];
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) t += __shfl_xor(t, off, kWave);
-    v[j] = t;
-  }
-  __syncthreads();  // the previous round's sums have been read
-  if (lane == 0) {
-#pragma unroll
-    for (int j = 0; j < kLossChunk; ++j) red[wave * kLossChunk + j] = v[j];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kLossChunk; ++j) {
-    float t = 0.f;
-    for (int w = 0; w < nwaves; ++w) t += red[w * kLossChunk + j];
-    v[j] = t;
-  }
-}
-
-template <bool kLds>
-__device__ static void produce_loss(const CropArgs& a, const uint32_t* tile, const u32x2* xtab,
-                                    const u32x4* ytab, const uint8_t* base, int b, int gy, int gx0,
-                                    int npatch, int cw, int masked, float* red, double* red64,
-                                    uint32_t tile_id) {
+// Patches of more than 768 values.  A thread owns the groups tid, tid + 192, .. of every patch of the
+// part: with three wavefronts all of them start with the same channel, so that what depends on the
+// channel is kept once.  CH patches at a time share the two reductions (wavefronts' sums exchanged through
+// LDS; two buffers in turn, so that one barrier each will do).  Small workgroups, several of which share a
+// compute unit, are what matters here: with one of up to 12 wavefronts per compute unit (a group per
+// thread, eight patches at a time) nothing ran while the tile was on its way.  1024 images with their input
+// pipeline, 256 -> 224, p = 32: 1093 -> 381 us (bf16: 1177 -> 430); 256 -> 100, p = 20: 396 -> 183.
+constexpr int kGroupThreads = 3 * kWave;
+template <bool kLds, int NV>
+__device__ static void produce_loss_group(const CropArgs& a, const uint32_t* tile, const u32x2* xtab,
+                                          const u32x4* ytab, const uint8_t* base, int b, int gy,
+                                          int gx0, int npatch, int cw, int masked, float* red,
+                                          double* red64, uint32_t tile_id) {
+  constexpr int CH = NV <= 2 ? 2 : 1;
+  constexpr int kWaves = kGroupThreads / kWave;
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int nwaves = (int)blockDim.x / kWave;
-  const int p = a.p, D = a.D;
-  const int D4 = D >> 2;
-  const int pp = p * p;
+  const int p = a.p, D = a.D, D4 = D >> 2, pp = p * p;
   const float inv_p = 1.0f / (float)p;
-  const float ns0 = a.nscale[0], ns1 = a.nscale[1], ns2 = a.nscale[2];
-  const float nb0 = a.nbias[0], nb1 = a.nbias[1], nb2 = a.nbias[2];
   const bool bf16 = a.pred_bf16 != 0;
 
-  // position inside the patch: as in produce_patches
-  const int e4 = wave * kWave + lane;
-  const bool active = e4 < D4;
-  const int e = active ? 4 * e4 : 0;
-  const int qA = e / 3;
-  const int cA = e - 3 * qA;
-  const int qB = min(qA + 1, pp - 1);
-  const int pyA = (int)(((float)qA + 0.5f) * inv_p);
-  const int pxA = qA - pyA * p;
-  const int pyB = (int)(((float)qB + 0.5f) * inv_p);
-  const int pxB = qB - pyB * p;
-  const u32x4 ya = ytab[pyA], yb = ytab[pyB];
-  const uint32_t rowA0 = ya.x, rowA1 = ya.y, rowB0 = yb.x, rowB1 = yb.y;
-  const float fyA = __uint_as_float(ya.z), fyB = __uint_as_float(yb.z);
+  // what depends on the position inside the patch only, as in produce_patches
+  const int cA = (int)(threadIdx.x % 3u);  // (4 e4 mod 3 with e4 = tid + 192 v)
   const uint32_t sel = cA == 0 ? 0x04020100u : (cA == 1 ? 0x05040201u : 0x06050402u);
   const int nA = 3 - cA;
-  float sc[4], bi[4], fy[4];
+  float sc[4], bi[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     int c = cA + j;
     c = c >= 3 ? c - 3 : c;
     c = c >= 3 ? c - 3 : c;
-    sc[j] = c == 0 ? ns0 : (c == 1 ? ns1 : ns2);
-    bi[j] = c == 0 ? nb0 : (c == 1 ? nb1 : nb2);
-    fy[j] = j == 0 ? fyA : (j == 3 ? fyB : (j < nA ? fyA : fyB));
+    sc[j] = a.nscale[c];
+    bi[j] = a.nbias[c];
+  }
+  bool active[NV];
+  int pxA[NV], pxB[NV];
+  uint32_t rowA0[NV], rowA1[NV], rowB0[NV], rowB1[NV];
+  float fyA[NV], fyB[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int e4 = (int)threadIdx.x + v * kGroupThreads;
+    active[v] = e4 < D4;
+    const int qA = (active[v] ? 4 * e4 : 4 * (int)threadIdx.x) / 3;
+    const int qB = min(qA + 1, pp - 1);
+    const int pyA = (int)(((float)qA + 0.5f) * inv_p), pyB = (int)(((float)qB + 0.5f) * inv_p);
+    pxA[v] = qA - pyA * p;
+    pxB[v] = qB - pyB * p;
+    const u32x4 ya = ytab[pyA], yb = ytab[pyB];
+    rowA0[v] = ya.x;
+    rowA1[v] = ya.y;
+    rowB0[v] = yb.x;
+    rowB1[v] = yb.y;
+    fyA[v] = __uint_as_float(ya.z);
+    fyB[v] = __uint_as_float(yb.z);
   }
   const float inv_d = 1.0f / (float)D, inv_dm1 = 1.0f / (float)(D - 1);
   const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
   const float gscale = loss_gscale(a);
   double acc = 0.0;
+  int turn = 0;
+  // s[j] summed over the workgroup, wavefronts in index order
+  const auto group_sums = [&](float* s) {
+    float* mine = red + turn * (kWaves * CH);
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      s[j] = wave_sum(s[j]);
+      if (lane == 0) mine[wave * CH + j] = s[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+      s[j] = mine[j];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) s[j] += mine[w * CH + j];
+    }
+    turn ^= 1;
+  };
 
-  for (int g0 = 0; g0 < npatch; g0 += kLossChunk) {
-    f32x4 val[kLossChunk], q[kLossChunk];
-    float s[kLossChunk];
-    bool m[kLossChunk];
+  for (int g0 = 0; g0 < npatch; g0 += CH) {
+    const int64_t first = ((int64_t)b * a.L + gy * a.G + gx0 + g0) * D + 4 * (int)threadIdx.x;
+    f32x4 val[CH][NV], q[CH][NV];
+    float s[CH];
+    bool m[CH];
     // the predictions first: they are on their way while the pixels are resampled
 #pragma unroll
-    for (int j = 0; j < kLossChunk; ++j) {
+    for (int j = 0; j < CH; ++j) {
       m[j] = g0 + j < npatch && __builtin_amdgcn_readlane(masked, (g0 + j) & (kWave - 1)) != 0;
-      q[j] = zero;
-      if (m[j] && active)
-        q[j] = crop_load_pred4(a.pred, ((int64_t)b * a.L + gy * a.G + gx0 + g0 + j) * D + e, bf16);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        q[j][v] = zero;
+        if (m[j] && active[v])
+          q[j][v] = crop_load_pred4(a.pred, first + (int64_t)j * D + 4 * v * kGroupThreads, bf16);
+      }
     }
 #pragma unroll
-    for (int j = 0; j < kLossChunk; ++j) {
-      val[j] = zero;
+    for (int j = 0; j < CH; ++j) {
       s[j] = 0.f;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) val[j][v] = zero;
       if (!m[j]) continue;
       const int gx = g0 + j;
-      const u32x2 xa = xtab[gx * p + pxA], xb = xtab[gx * p + pxB];
-      const float fxA = __uint_as_float(xa.y), fxB = __uint_as_float(xb.y);
-      uint32_t A00, A01, A10, A11, B00, B01, B10, B11;
-      fetch2<kLds>(tile, base, rowA0, (int)xa.x, cw, A00, A01);
-      fetch2<kLds>(tile, base, rowA1, (int)xa.x, cw, A10, A11);
-      fetch2<kLds>(tile, base, rowB0, (int)xb.x, cw, B00, B01);
-      fetch2<kLds>(tile, base, rowB1, (int)xb.x, cw, B10, B11);
-      const uint32_t P00 = __builtin_amdgcn_perm(B00, A00, sel);
-      const uint32_t P01 = __builtin_amdgcn_perm(B01, A01, sel);
-      const uint32_t P10 = __builtin_amdgcn_perm(B10, A10, sel);
-      const uint32_t P11 = __builtin_amdgcn_perm(B11, A11, sel);
-      float out[4];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        const u32x2 xa = xtab[gx * p + pxA[v]], xb = xtab[gx * p + pxB[v]];
+        const float fxA = __uint_as_float(xa.y), fxB = __uint_as_float(xb.y);
+        uint32_t A00, A01, A10, A11, B00, B01, B10, B11;
+        fetch2<kLds>(tile, base, rowA0[v], (int)xa.x, cw, A00, A01);
+        fetch2<kLds>(tile, base, rowA1[v], (int)xa.x, cw, A10, A11);
+        fetch2<kLds>(tile, base, rowB0[v], (int)xb.x, cw, B00, B01);
+        fetch2<kLds>(tile, base, rowB1[v], (int)xb.x, cw, B10, B11);
+        const uint32_t P00 = __builtin_amdgcn_perm(B00, A00, sel);
+        const uint32_t P01 = __builtin_amdgcn_perm(B01, A01, sel);
+        const uint32_t P10 = __builtin_amdgcn_perm(B10, A10, sel);
+        const uint32_t P11 = __builtin_amdgcn_perm(B11, A11, sel);
+        float out[4];
 #define MAE_BLEND(J)                                                                 \
 {                                                                                  \
   const float fx = (J) == 0 ? fxA : ((J) == 3 ? fxB : ((J) < nA ? fxA : fxB));     \
+  const float fy = (J) == 0 ? fyA[v] : ((J) == 3 ? fyB[v] : ((J) < nA ? fyA[v] : fyB[v])); \
   const float a00 = byte_to_float<J>(P00), a01 = byte_to_float<J>(P01);            \
   const float a10 = byte_to_float<J>(P10), a11 = byte_to_float<J>(P11);            \
   const float rt = a00 + fx * (a01 - a00);                                         \
   const float rb = a10 + fx * (a11 - a10);                                         \
-  const float v = rt + fy[J] * (rb - rt);                                          \
-  out[J] = v * sc[J] + bi[J];                                                      \
+  const float t = rt + fy * (rb - rt);                                             \
+  out[J] = t * sc[J] + bi[J];                                                      \
 }
-      MAE_BLEND(0) MAE_BLEND(1) MAE_BLEND(2) MAE_BLEND(3)
+        MAE_BLEND(0) MAE_BLEND(1) MAE_BLEND(2) MAE_BLEND(3)
 #undef MAE_BLEND
-      if (active) {
-        val[j] = f32x4{out[0], out[1], out[2], out[3]};
-        s[j] = (out[0] + out[1]) + (out[2] + out[3]);
+        if (active[v]) val[j][v] = f32x4{out[0], out[1], out[2], out[3]};
+        s[j] += (val[j][v].x + val[j][v].y) + (val[j][v].z + val[j][v].w);
       }
     }
-    float rstd[kLossChunk];
+    float rstd[CH];
 #pragma unroll
-    for (int j = 0; j < kLossChunk; ++j) rstd[j] = 1.0f;
+    for (int j = 0; j < CH; ++j) rstd[j] = 1.0f;
     if (a.norm_pix) {
-      block_sums(s, red, lane, wave, nwaves);
+      group_sums(s);
 #pragma unroll
-      for (int j = 0; j < kLossChunk; ++j) {
+      for (int j = 0; j < CH; ++j) {
         const float mu = s[j] * inv_d;
-        val[j] = val[j] - mu;
-        s[j] = active ? (val[j].x * val[j].x + val[j].y * val[j].y) +
-                            (val[j].z * val[j].z + val[j].w * val[j].w)
-                      : 0.f;
-      }
-      block_sums(s, red, lane, wave, nwaves);
+        s[j] = 0.f;
 #pragma unroll
-      for (int j = 0; j < kLossChunk; ++j) rstd[j] = 1.0f / sqrtf(s[j] * inv_dm1 + a.eps);
+        for (int v = 0; v < NV; ++v) {
+          val[j][v] = val[j][v] - mu;
+          if (active[v])
+            s[j] += (val[j][v].x * val[j][v].x + val[j][v].y * val[j][v].y) +
+                    (val[j][v].z * val[j][v].z + val[j][v].w * val[j][v].w);
+        }
+      }
+      group_sums(s);
+#pragma unroll
+      for (int j = 0; j < CH; ++j) rstd[j] = 1.0f / sqrtf(s[j] * inv_dm1 + a.eps);
     }
     float sq = 0.f;
 #pragma unroll
-    for (int j = 0; j < kLossChunk; ++j) {
-      if (g0 + j >= npatch || !active) continue;
-      const int64_t elem = ((int64_t)b * a.L + gy * a.G + gx0 + g0 + j) * D + e;
-      f32x4 diff = zero;
-      if (m[j]) {
-        diff = q[j] - val[j] * rstd[j];
-        sq += (diff.x * diff.x + diff.y * diff.y) + (diff.z * diff.z + diff.w * diff.w);
+    for (int j = 0; j < CH; ++j) {
+      if (g0 + j >= npatch) continue;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        if (!active[v]) continue;
+        f32x4 diff = zero;
+        if (m[j]) {
+          diff = q[j][v] - val[j][v] * rstd[j];
+          sq += (diff.x * diff.x + diff.y * diff.y) + (diff.z * diff.z + diff.w * diff.w);
+        }
+        if (a.grad)
+          crop_store_grad4(a.grad, first + (int64_t)j * D + 4 * v * kGroupThreads, diff * gscale, bf16);
       }
-      if (a.grad) crop_store_grad4(a.grad, elem, diff * gscale, bf16);
     }
     acc += (double)sq;
   }
   // the workgroup's share of the loss: lanes by butterfly, wavefronts in index order
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
-  __syncthreads();
   if (lane == 0) red64[wave] = acc;
   __syncthreads();
   if (threadIdx.x == 0) {
     double t = 0.0;
-    for (int w = 0; w < nwaves; ++w) t += red64[w];
+    for (int w = 0; w < kWaves; ++w) t += red64[w];
     a.partials[tile_id] = t;
   }
 }
@@ -475,7 +513,7 @@ __device__ static void produce_loss(const CropArgs& a, const uint32_t* tile, con
 // (The per-group setup and the blend are written out again in each of these functions: behind a
 // shared helper the compiler keeps 40 more registers alive, which costs a wavefront per SIMD.)
 //
-// The same for patches of up to 768 values (NV = groups per lane, D / 4 <= 64 NV): a wavefront
+// Patches of up to 768 values (NV = groups per lane, D / 4 <= 64 NV): a wavefront
 // holds a whole patch, lane i its groups i, i + 64, ..., so the two reductions are wavefront
 // butterflies and the wavefronts of the workgroup work through the part's patches independently.
 template <bool kLds, int NV>
@@ -578,9 +616,7 @@ __device__ static void produce_loss_wave(const CropArgs& a, const uint32_t* tile
     }
     float rstd = 1.0f;
     if (a.norm_pix) {
-#pragma unroll
-      for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
-      const float mu = s * inv_d;
+      const float mu = wave_sum(s) * inv_d;
       float ss = 0.f;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
@@ -589,9 +625,7 @@ __device__ static void produce_loss_wave(const CropArgs& a, const uint32_t* tile
           ss += (val[v].x * val[v].x + val[v].y * val[v].y) +
                 (val[v].z * val[v].z + val[v].w * val[v].w);
       }
-#pragma unroll
-      for (int off = kWave / 2; off > 0; off >>= 1) ss += __shfl_xor(ss, off, kWave);
-      rstd = 1.0f / sqrtf(ss * inv_dm1 + a.eps);
+      rstd = 1.0f / sqrtf(wave_sum(ss) * inv_dm1 + a.eps);
     }
     float sq = 0.f;
 #pragma unroll
@@ -960,12 +994,14 @@ __device__ static void neutral_outputs(const CropArgs& a, int b, int gy, int gx0
 
 // Dynamic LDS: [ tile: a.tile_pixels + 4 words | ytab: p x 16 bytes | xtab: a.part_patches p x 8 ].
 // kLossMode 1, 2: instead of writing the patches, the loss and its gradient against a.pred
-// (1: produce_loss, any patch size; 2: produce_loss_wave, patches of up to 768 values).
+// (1: produce_loss_group, patches of more than 768 values; 2: produce_loss_wave, smaller ones).
 // kLossMode -1: the visible tokens only (no target).  -2: a pixel per lane (odd patch sizes).
 // kAug: the finetuning augmentation as the epilogue (produce_aug): 1 = "3 Aug", 2 = "3 Aug+" up to
 // the colour jitter.
 // kAugPx: pixels per lane of that epilogue (4 when p is a multiple of 4, else 2).
-template <bool kBf16, int kLossMode, int kAug = 0, int kAugPx = 4>
+// kPairs: crops may be so much larger than the output that only the two rows that every output row
+// taps are staged (crop_whole_rows).
+template <bool kPairs, bool kBf16, int kLossMode, int kAug = 0, int kAugPx = 4>
 __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
   constexpr bool kLoss = kLossMode > 0;
   constexpr bool kKeptOnly = kLossMode == -1;
@@ -1021,11 +1057,14 @@ __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
   const int ox_first = gx0 * p, ox_last = gx1 * p - 1;
   resize_taps(rec.flip ? S - 1 - ox_last : ox_first, rec.cw, S, inv_den, xlo, t1, tf);
   resize_taps(rec.flip ? S - 1 - ox_first : ox_last, rec.cw, S, inv_den, t0, xhi, tf);
-  const int nrows = yhi - ylo + 1;
+  // Staged rows: all from the first to the last that is tapped, or pairs (rows 2 py and 2 py + 1 for
+  // output row py)
+  const bool pairs = kPairs && yhi - ylo + 1 > a.whole_rows;
+  const int nrows = pairs ? 2 * p : yhi - ylo + 1;
   const int ng = (xhi - xlo + 4) >> 2;  // groups of four pixels per staged row
   const int pitch = 4 * ng;             // pixel words per staged row
   const bool use_lds = nrows * pitch <= a.tile_pixels;
-  const bool batched = use_lds && ng <= kWave;
+  const bool batched = use_lds && !pairs && ng <= kWave;
 
   // first tapped pixel of the first tapped row
   const uint8_t* base =
@@ -1074,6 +1113,8 @@ __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
     float f;
     resize_taps(gy * p + py, rec.ch, S, inv_den, y0, y1, f, rem);
     const uint32_t stride = use_lds ? (uint32_t)pitch : (uint32_t)row_bytes;
+    y0 = use_lds && pairs ? 2 * py + ylo : y0;  // (staged rows count from ylo)
+    y1 = use_lds && pairs ? 2 * py + 1 + ylo : y1;
     if constexpr (kAug != 0)  // integer weights of the two rows: 2 S - rem, rem (round_plan's scale)
       ytab[py] = u32x4{(uint32_t)(y0 - ylo) * stride, (uint32_t)(y1 - ylo) * stride,
                        (uint32_t)(2 * S - rem) << a.round.shift, (uint32_t)rem << a.round.shift};
@@ -1092,7 +1133,7 @@ __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
       }
     }
   }
-  if (use_lds) {  // rows beyond the first batch, and parts wider than 256 source pixels
+  if (use_lds && !pairs) {  // rows beyond the first batch, and parts wider than 256 source pixels
     for (int r = batched ? wave + kStageRows * nwaves : wave; r < nrows; r += nwaves) {
       const uint8_t* row = base + (int64_t)r * row_bytes;
       const uint32_t s = (uint32_t)reinterpret_cast<uintptr_t>(row) & 3u;
@@ -1100,6 +1141,36 @@ __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
       const bool safe = arow >= a.images && arow + 12 * ng + 4 <= img_end;
       for (int g = lane; g < ng; g += kWave)
         tile4[r * ng + g] = to_pixels(load16(arow + 12 * g, safe, a.images, img_end), s);
+    }
+  }
+  if (use_lds && pairs) {
+    // lane r of every wavefront works out what staged row r holds (2 p is at most 64); the loads of four
+    // rows in flight
+    int y0, y1;
+    float f;
+    resize_taps(gy * p + (lane >> 1), rec.ch, S, inv_den, y0, y1, f);
+    const int src_row = ((lane & 1) ? y1 : y0) - ylo;
+    constexpr int kPairRows = 4;
+    for (int r0 = __builtin_amdgcn_readfirstlane(wave); r0 < nrows; r0 += kPairRows * nwaves) {
+      for (int g0 = 0; g0 < ng; g0 += kWave) {
+        const int g = g0 + lane;
+        u32x4 part[kPairRows];
+        uint32_t skew[kPairRows];
+#pragma unroll
+        for (int u = 0; u < kPairRows; ++u) {
+          const int r = min(r0 + u * nwaves, nrows - 1);
+          const uint8_t* row = base + (int64_t)__builtin_amdgcn_readlane(src_row, r) * row_bytes;
+          skew[u] = (uint32_t)reinterpret_cast<uintptr_t>(row) & 3u;
+          const uint8_t* arow = row - skew[u];
+          const bool safe = arow >= a.images && arow + 12 * ng + 4 <= img_end;
+          part[u] = load16(arow + 12 * min(g, ng - 1), safe, a.images, img_end);
+        }
+#pragma unroll
+        for (int u = 0; u < kPairRows; ++u) {
+          const int r = r0 + u * nwaves;
+          if (r < nrows && g < ng) tile4[r * ng + g] = to_pixels(part[u], skew[u]);
+        }
+      }
     }
   }
   __syncthreads();
@@ -1117,7 +1188,7 @@ __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
     else MAE_PRODUCE_AUG(false);
 #undef MAE_PRODUCE_AUG
   } else if constexpr (kLoss) {
-    __shared__ float red[(kCropMaxThreads / kWave) * kLossChunk];
+    __shared__ float red[2 * kGroupThreads / kWave * 4];
     __shared__ double red64[kCropMaxThreads / kWave];
     if constexpr (kLossMode == 2) {
       const int nv = ((a.D >> 2) + kWave - 1) / kWave;
@@ -1131,12 +1202,18 @@ __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
       else if (use_lds) MAE_LOSS_WAVE(true, 1);
       else MAE_LOSS_WAVE(false, 1);
 #undef MAE_LOSS_WAVE
-    } else if (use_lds) {
-      produce_loss<true>(a, tile, xtab, ytab, base, b, gy, gx0, npatch, rec.cw - xlo, my_rank, red,
-                         red64, tile_id);
     } else {
-      produce_loss<false>(a, tile, xtab, ytab, base, b, gy, gx0, npatch, rec.cw - xlo, my_rank,
-                          red, red64, tile_id);
+      const int nv = ((a.D >> 2) + kGroupThreads - 1) / kGroupThreads;
+#define MAE_LOSS_GROUP(LDS, NV)                                                                  \
+  produce_loss_group<LDS, NV>(a, tile, xtab, ytab, base, b, gy, gx0, npatch, rec.cw - xlo, my_rank, \
+                              red, red64, tile_id)
+      if (nv == 4 && use_lds) MAE_LOSS_GROUP(true, 4);
+      else if (nv == 4) MAE_LOSS_GROUP(false, 4);
+      else if (nv == 3 && use_lds) MAE_LOSS_GROUP(true, 3);
+      else if (nv == 3) MAE_LOSS_GROUP(false, 3);
+      else if (use_lds) MAE_LOSS_GROUP(true, 2);
+      else MAE_LOSS_GROUP(false, 2);
+#undef MAE_LOSS_GROUP
     }
   } else if constexpr (kLossMode == -2) {
     if (use_lds)
@@ -1152,35 +1229,37 @@ __device__ static inline void crop_band(const CropArgs& a, uint32_t* lds) {
   }
 }
 
-template <bool kBf16>
+template <bool kPairs, bool kBf16>
 __global__ __launch_bounds__(kCropMaxThreads) void crop_patch_kernel(CropArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  crop_band<kBf16, 0>(a, lds);
+  crop_band<kPairs, kBf16, 0>(a, lds);
 }
 // ... when no target is wanted: only the patches that are kept
-template <bool kBf16>
+template <bool kPairs, bool kBf16>
 __global__ __launch_bounds__(kCropMaxThreads) void crop_kept_kernel(CropArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  crop_band<kBf16, -1>(a, lds);
+  crop_band<kPairs, kBf16, -1>(a, lds);
 }
 
 // ... with the finetuning augmentation's pointwise operations as the epilogue
-template <bool kBf16, int kAug, int kPx>
+template <bool kPairs, bool kBf16, int kAug, int kPx>
 __global__ __launch_bounds__(kCropMaxThreads) void crop_aug_kernel(CropArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  crop_band<kBf16, 0, kAug, kPx>(a, lds);
+  crop_band<kPairs, kBf16, 0, kAug, kPx>(a, lds);
 }
 
 // The resampling kernel with the loss as its epilogue: what mae_normpix_loss computes, with the
 // masked patches' pixels taken from the images again instead of from a stored target.
-__global__ __launch_bounds__(kCropMaxThreads) void crop_loss_kernel(CropArgs a) {
+template <bool kPairs>
+__global__ __launch_bounds__(kGroupThreads, 4) void crop_loss_group_kernel(CropArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  crop_band<false, 1>(a, lds);
+  crop_band<kPairs, false, 1>(a, lds);
 }
 // ... with a wavefront per patch (D <= 768): four wavefronts per workgroup
+template <bool kPairs>
 __global__ __launch_bounds__(4 * kWave) void crop_loss_wave_kernel(CropArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  crop_band<false, 2>(a, lds);
+  crop_band<kPairs, false, 2>(a, lds);
 }
 
 // ... for odd patch sizes (most of them: crop_pixels_staged), with or without a target: 64 threads
@@ -1188,7 +1267,7 @@ __global__ __launch_bounds__(4 * kWave) void crop_loss_wave_kernel(CropArgs a) {
 template <bool kBf16>
 __global__ __launch_bounds__(kCropMaxThreads) void crop_pixel_kernel(CropArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  crop_band<kBf16, -2>(a, lds);
+  crop_band<false, kBf16, -2>(a, lds);
 }
 
 // Odd patch sizes where staging does not pay (crop_pixels_staged below): one output pixel per thread,
@@ -1255,14 +1334,38 @@ __global__ __launch_bounds__(kCropThreads) void crop_patch_scalar_kernel(CropArg
   }
 }
 
+// Source rows that a row of patches may tap.
+static int64_t tapped_rows(int S, int p, int max_side) {
+  return ((int64_t)(p - 1) * max_side + S - 1) / S + 2;
+}
+// Source rows of a row of patches that are staged as they follow each other; where a crop has more, the
+// 2 p that are tapped.  Fewer rows make the tile smaller, so that more workgroups share a compute unit, and
+// leave out what is not tapped; but the requests no longer run beside the tap tables, which the outputs of
+// large patches, whose workgroups are large, feel up to four times the output's size.
+// 1024 images, all rows / pairs, us.  Outputs: 256 -> 96, p = 16: 70 / 63, 500 -> 96, p = 16: 354 / 113, 500 ->
+// 160, p = 16: 290 / 194; 500 -> 220, p = 20: 327 / 374, 500 -> 128, p = 32: 213 / 250, 500 -> 100, p = 20 with
+// its loss: 395 / 252.  Loss from the images, with its input pipeline: 500 -> 96, p = 16: 814 / 203, 500 -> 224,
+// p = 28: 938 / 760.  Augmentation, "3 Aug+": 500 -> 160, p = 32: 535 / 368, 500 -> 224, p = 32: 583 / 484.
+int crop_whole_rows(int S, int p, int max_side, CropUse use) {
+  if (p & 1) return INT32_MAX;  // (crop_pixels_staged has the rule for them)
+  if (use == CropUse::kOutputs && p > 16 && tapped_rows(S, p, max_side) <= 4 * p) return INT32_MAX;
+  return 2 * p;
+}
+// Whether crops of images of up to max_side pixels may have more.
+static bool crop_pairs(const CropArgs& a) {
+  return tapped_rows(a.S, a.p, a.max_side) > a.whole_rows;
+}
+
 // Launch plan of the resampling kernel when no image side exceeds max_side.  A row of patches
-// taps at most ceil((p - 1) max_side / S) + 2 source rows; a column part of n patches taps at most
-// min(max_side, ceil((n p - 1) max_side / S) + 2) source columns, rounded up to groups of four.  The row is split
-// into the fewest parts (whole patches, a power of two) whose tile stays within kCropTileTarget
-// bytes, so that several workgroups share a compute unit's LDS.
-CropPlan crop_plan(int S, int p, int max_side, int force_parts) {
+// taps at most ceil((p - 1) max_side / S) + 2 source rows, of which no more than whole_rows are staged; a column
+// part of n patches taps at most min(max_side, ceil((n p - 1) max_side / S) + 2) source columns, rounded
+// up to groups of four.  The row is split into the fewest parts (whole patches, a power of two) whose tile
+// stays within kCropTileTarget bytes, so that several workgroups share a compute unit's LDS, and no fewer
+// than min_parts.
+CropPlan crop_plan(int S, int p, int max_side, int min_parts, int whole_rows) {
   const int G = S / p;
-  const int64_t rows = ((int64_t)(p - 1) * max_side + S - 1) / S + 2;
+  int64_t rows = tapped_rows(S, p, max_side);
+  if (rows > whole_rows) rows = whole_rows;
   CropPlan plan;
   int parts = 1;
   for (;;) {
@@ -1272,9 +1375,8 @@ CropPlan crop_plan(int S, int p, int max_side, int force_parts) {
     cols = (cols + 3) & ~(int64_t)3;
     const int64_t px = rows * cols;
     const int64_t fixed = 16 + 16 * (int64_t)p + 8 * (int64_t)n * p;
-    const bool forced = force_parts > 0;
     const bool fits = px * 4 + fixed <= kCropTileTarget;
-    if ((forced && parts >= force_parts) || (!forced && fits) || parts * 2 > G) {
+    if ((fits && parts >= min_parts) || parts * 2 > G) {
       int64_t cap = (kCropMaxLds - fixed) / 4;
       plan.col_parts = parts;
       plan.part_patches = n;
@@ -1286,6 +1388,16 @@ CropPlan crop_plan(int S, int p, int max_side, int force_parts) {
   }
 }
 
+// Column parts that a small batch's rows of patches are split into at least for the loss over large
+// patches, whose workgroups take one patch after the other: so many that there are four of them per
+// compute unit (64 images of 256 pixels -> 192, p = 24, with their input pipeline: 44.4 -> 41.5 us).  Where a part's patches are
+// dealt to the wavefronts, or a thread takes a position of all of them, fewer patches per part only
+// repeat the set-up.
+int crop_loss_min_parts(int B, int S, int p) {
+  const int64_t bands = (int64_t)B * (S / p);
+  return 3 * p * p <= 768 || bands >= kCropFill ? 1 : (int)((kCropFill + bands - 1) / bands);
+}
+
 size_t crop_lds_bytes(const CropArgs& a) {
   return (size_t)(a.tile_pixels + 4) * 4 + (size_t)a.p * 16 + (size_t)a.part_patches * a.p * 8;
 }
@@ -1294,6 +1406,7 @@ size_t crop_lds_bytes(const CropArgs& a) {
 // adds its contiguous share in a fixed order and leaves one double; the second stage is the
 // single-workgroup kernel that finishes the other loss, too.
 constexpr int kLossGroups = 128;
+constexpr int kLossOneStage = 4096;
 __global__ __launch_bounds__(256) void crop_loss_reduce_kernel(const double* partials, int64_t n,
                                                                double* out) {
   __shared__ double red[256];
@@ -1318,14 +1431,23 @@ int64_t crop_loss_partials(const CropArgs& a) {
 hipError_t launch_crop_loss(const CropArgs& a, hipStream_t stream) {
   dim3 grid((uint32_t)a.B * (uint32_t)a.G * (uint32_t)a.col_parts);
   const int nv = ((a.D >> 2) + kWave - 1) / kWave;
-  // patches of up to 768 values are a wavefront's work each: four wavefronts share a part
-  if (nv <= 3)
-    hipLaunchKernelGGL(crop_loss_wave_kernel, grid, dim3(4 * kWave), crop_lds_bytes(a), stream, a);
+  // patches of up to 768 values are a wavefront's work each: four wavefronts share a part; larger ones
+  // that of three wavefronts together
+  const size_t lds = crop_lds_bytes(a);
+  if (nv <= 3 && crop_pairs(a))
+    hipLaunchKernelGGL(crop_loss_wave_kernel<true>, grid, dim3(4 * kWave), lds, stream, a);
+  else if (nv <= 3)
+    hipLaunchKernelGGL(crop_loss_wave_kernel<false>, grid, dim3(4 * kWave), lds, stream, a);
+  else if (crop_pairs(a))
+    hipLaunchKernelGGL(crop_loss_group_kernel<true>, grid, dim3(kGroupThreads), lds, stream, a);
   else
-    hipLaunchKernelGGL(crop_loss_kernel, grid, dim3(kWave * nv), crop_lds_bytes(a), stream, a);
+    hipLaunchKernelGGL(crop_loss_group_kernel<false>, grid, dim3(kGroupThreads), lds, stream, a);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   const int64_t n = (int64_t)grid.x;
+  if (n <= kLossOneStage)  // few enough for the last stage alone
+    return launch_loss_finish(a.partials, (int)n, a.inv_count, a.loss_out, a.counts, a.ncounts, a.D,
+                              stream);
   hipLaunchKernelGGL(crop_loss_reduce_kernel, dim3(kLossGroups), dim3(256), 0, stream, a.partials,
                      n, a.partials + n);
   err = hipGetLastError();
@@ -1345,12 +1467,16 @@ hipError_t launch_crop_aug(const CropArgs& args, hipStream_t stream) {
   const size_t tables = (crop_lds_bytes(a) + 15) & ~(size_t)15;
   const size_t strips = (size_t)(block.x / kWave) * kStripFloats * sizeof(float);
   // four pixels per lane when they tile a patch row, else two (even patch sizes)
-#define MAE_AUG_LAUNCH(BF, AUG, LDS)                                                     \
-  do {                                                                                   \
-    if ((a.p & 3) == 0)                                                                  \
-      hipLaunchKernelGGL((crop_aug_kernel<BF, AUG, 4>), grid, block, LDS, stream, a);    \
-    else                                                                                 \
-      hipLaunchKernelGGL((crop_aug_kernel<BF, AUG, 2>), grid, block, LDS, stream, a);    \
+#define MAE_AUG_LAUNCH(BF, AUG, LDS)                                                           \
+  do {                                                                                         \
+    if ((a.p & 3) == 0 && crop_pairs(a))                                                       \
+      hipLaunchKernelGGL((crop_aug_kernel<true, BF, AUG, 4>), grid, block, LDS, stream, a);    \
+    else if ((a.p & 3) == 0)                                                                   \
+      hipLaunchKernelGGL((crop_aug_kernel<false, BF, AUG, 4>), grid, block, LDS, stream, a);   \
+    else if (crop_pairs(a))                                                                    \
+      hipLaunchKernelGGL((crop_aug_kernel<true, BF, AUG, 2>), grid, block, LDS, stream, a);    \
+    else                                                                                       \
+      hipLaunchKernelGGL((crop_aug_kernel<false, BF, AUG, 2>), grid, block, LDS, stream, a);   \
   } while (0)
   // ("3 Aug+" writes bytes only, whatever the type of `visible`)
   if (a.aug_mode != 1) MAE_AUG_LAUNCH(false, 2, tables);
@@ -1383,15 +1509,18 @@ hipError_t launch_crop_patch(const CropArgs& a, hipStream_t stream) {
     dim3 grid((uint32_t)a.B * (uint32_t)a.G * (uint32_t)a.col_parts);
     dim3 block(kWave * (((a.D >> 2) + kWave - 1) / kWave));
     const size_t lds = crop_lds_bytes(a);
-    if (!a.target && a.visible_bf16) {
-      hipLaunchKernelGGL(crop_kept_kernel<true>, grid, block, lds, stream, a);
-    } else if (!a.target) {
-      hipLaunchKernelGGL(crop_kept_kernel<false>, grid, block, lds, stream, a);
-    } else if (a.visible_bf16) {
-      hipLaunchKernelGGL(crop_patch_kernel<true>, grid, block, lds, stream, a);
-    } else {
-      hipLaunchKernelGGL(crop_patch_kernel<false>, grid, block, lds, stream, a);
-    }
+#define MAE_CROP_LAUNCH(KERNEL, BF)                                                       \
+  do {                                                                                    \
+    if (crop_pairs(a))                                                                    \
+      hipLaunchKernelGGL((KERNEL<true, BF>), grid, block, lds, stream, a);                \
+    else                                                                                  \
+      hipLaunchKernelGGL((KERNEL<false, BF>), grid, block, lds, stream, a);               \
+  } while (0)
+    if (!a.target && a.visible_bf16) MAE_CROP_LAUNCH(crop_kept_kernel, true);
+    else if (!a.target) MAE_CROP_LAUNCH(crop_kept_kernel, false);
+    else if (a.visible_bf16) MAE_CROP_LAUNCH(crop_patch_kernel, true);
+    else MAE_CROP_LAUNCH(crop_patch_kernel, false);
+#undef MAE_CROP_LAUNCH
   } else if (!crop_pixels_staged(a)) {
     const int64_t total = (int64_t)a.B * a.L * a.p * a.p;  // output pixels
     int64_t blocks = (total + kCropThreads - 1) / kCropThreads;

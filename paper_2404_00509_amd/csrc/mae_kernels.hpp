@@ -82,12 +82,17 @@ struct CropArgs {
   // the kernels read, and crop_aug_kernel takes 2 % longer: 256 images of 500 pixels -> 128, p = 8,
   // 117.5 against 115.6 us.)
   int32_t max_side;
+  int32_t whole_rows;  // crops that tap more source rows per row of patches have only those staged
   RoundPlan round;  // launch_crop_aug fills it in
 };
 struct CropPlan {
   int col_parts, part_patches, tile_pixels;
 };
-CropPlan crop_plan(int S, int p, int max_side, int force_parts);
+// What a plan is for: outputs of the input pipeline, the loss from the images, the augmentation.
+enum class CropUse { kOutputs, kLoss, kAugment };
+int crop_whole_rows(int S, int p, int max_side, CropUse use);
+CropPlan crop_plan(int S, int p, int max_side, int min_parts, int whole_rows);
+int crop_loss_min_parts(int B, int S, int p);
 size_t crop_lds_bytes(const CropArgs& a);
 hipError_t launch_crop_patch(const CropArgs& a, hipStream_t stream);
 // The same with the finetuning augmentation's pointwise operations as the epilogue: "3 Aug" writes

@@ -89,6 +89,32 @@ def test_patch_sizes_ratios_and_bf16(S, p, ratio, bf16):
     _check(data, kw, synth.make_pred(2, B, L, D), bf16=bf16, what=f"S{S} p{p}")
 
 
+# Patches of more than 768 values: a workgroup's work, in two to four groups per thread (the last one whole,
+# partly there or, at p = 26, nearly so), parts of one patch and of several.
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("S,p,B", [(18, 18, 1), (36, 18, 5), (220, 22, 3), (120, 24, 40), (208, 26, 4), (84, 28, 7),
+                                   (210, 30, 5), (224, 32, 3), (512, 32, 2)])
+def test_patches_of_more_than_768_values(S, p, B, bf16):
+    data = synth.make_images("gradient", B, seed=30 + p)
+    L, D = (S // p) ** 2, 3 * p * p
+    for norm_pix in (True, False):
+        kw = dict(out_size=S, patch=p, num_keep=max(1, L // 3), seed=4, batch_index=2)
+        if L > kw["num_keep"]:
+            _check(data, kw, synth.make_pred(2, B, L, D), bf16=bf16, norm_pix=norm_pix, what=f"S{S} p{p}")
+
+
+# Crops several times as large as the output, where only the rows that are tapped are staged: all sizes of
+# crops in one batch, on either side of the line, one and several parts, patches of all kernels.
+@pytest.mark.parametrize("S,p", [(96, 16), (64, 32), (48, 4), (80, 20), (100, 10), (24, 2), (126, 14)])
+def test_crops_of_which_only_the_tapped_rows_are_staged(S, p):
+    B = 10
+    data = synth.make_images("gradient500", B, seed=40 + p)
+    L, D = (S // p) ** 2, 3 * p * p
+    kw = dict(out_size=S, patch=p, num_keep=max(1, L // 4), scale=(0.02, 1.0), seed=5, batch_index=2)
+    for side in (500, 600):
+        _check(data, kw, synth.make_pred(3, B, L, D), max_image_side=side, what=f"S{S} p{p}")
+
+
 def test_unnormalised_variant_scale_and_loss_only():
     B, S, p = 8, 112, 16
     data = synth.make_images("uniform", B, seed=5)

@@ -483,6 +483,25 @@ def test_loss_zero_for_exact_prediction_and_reproducible():
 # ------------------------------------------------------------------------------------------------
 # buffer-edge and stream behaviour
 # ------------------------------------------------------------------------------------------------
+# Crops several times as large as the output: only the rows that are tapped are staged, in an unaligned
+# buffer without slack, with outputs of both types and with the augmentations.
+@pytest.mark.parametrize("S,p,aug", [(96, 16, 0), (96, 32, 0), (100, 20, 0), (32, 2, 0), (60, 12, 0), (96, 16, 1),
+                                     (64, 32, 1), (60, 6, 2), (96, 16, 2)])
+def test_prep_of_crops_of_which_only_the_tapped_rows_are_staged(S, p, aug):
+    flat, offsets, h, w = synth.make_images("gradient500", 8, seed=70 + S + p)
+    L = (S // p) ** 2
+    for shift in (0, 3):
+        store = torch.zeros(flat.size + shift, dtype=torch.uint8, device="cuda")
+        store[shift:] = torch.from_numpy(flat).cuda()
+        dimg = (store[shift:], torch.from_numpy(offsets).cuda(), torch.from_numpy(h).cuda(),
+                torch.from_numpy(w).cuda())
+        kw = dict(out_size=S, patch=p, num_keep=max(1, L // 2), scale=(0.02, 1.0), seed=7 + shift, aug_mode=aug)
+        ref = oracle.prep_batch(flat, offsets, h, w, **kw)
+        for bf16 in (False, True):
+            buf, _, _ = gpu_prep(flat, offsets, h, w, bf16=bf16, device_inputs=dimg, max_image_side=500, **kw)
+            check_prep_against_oracle(prep_to_numpy(buf), ref, bf16=bf16, what=f"S{S} p{p} aug {aug}")
+
+
 @pytest.mark.parametrize("shift", [1, 2, 3])
 def test_prep_image_buffer_with_unaligned_base_and_tight_end(shift):
     # the staging loads are 4-byte aligned 16-byte reads; with an unaligned base pointer and no
