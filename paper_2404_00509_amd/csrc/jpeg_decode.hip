@@ -1125,7 +1125,11 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_scan_kernel(JpegArgs a) {
 // A step is one AC symbol, one look-up and no branch; what only some lanes need comes every kSteps
 // steps: a block's end, the next one's DC coefficient, a code that is not in the table.  A lane that
 // ends its block in between waits for that point, three steps on average; without the waiting every
-// step would carry the instructions for all of it (about 100 instead of 33, 20 without the value).
+// step would carry the instructions for all of it (about 100 instead of 31, 20 without the value).
+// A lane that waits goes through the steps with an entry that moves nothing, and not around them: a
+// branch per step, even one that is never taken, costs more than it can save, since a wavefront has its
+// SIMD to itself (the walk below 650 -> 576 us, entropy decoding 762 -> 718 us with the value of a
+// symbol made while the next one is looked up; with a way out where all lanes wait 733 us).
 constexpr int kLongCodes = 512;  // entries for codes beyond the direct part of a table
 constexpr int kDirect = 1 << kFastBits;
 constexpr int kSteps = 6;    // AC symbols of at most 31 bits between two points that all lanes pass
@@ -1139,6 +1143,7 @@ constexpr int kCoefTable = 2 * kCoefAc + (2 << kDcBits);
 // index ends the block) | 32 - bits of code and value (bits 10-15).  kMiss, for a code that is not in
 // the table, uses no bits and parks the lane at the end of a block, where the code is looked up.
 constexpr uint32_t kMiss = (32u << 10) | (63u << 4);
+constexpr uint32_t kNoStep = 32u << 10;  // no bits, no coefficient
 constexpr uint32_t kNoCode = (31u << 10) | (63u << 4);  // one bit, the end of the block
 __device__ static inline uint32_t coef_entry(int len, int rs) {
   const int size = rs & 15, run = rs >> 4;
@@ -1170,11 +1175,19 @@ __device__ static __forceinline__ uint32_t sym_ahead(const Reader& r) {
   return r.ring[(r.taken & (kRingBytes / 4 - 1)) * kJpegThreads];
 }
 // `size` value bits that end `off` bits above the lowest, as the signed value they stand for (T.81
-// F.2.2.1: the lower half of the range is the negative numbers); 0 for none.
+// F.2.2.1: the lower half of the range is the negative numbers); 0 for none.  With t the bits as a two's
+// complement number: t + 2^size where t is negative, else t + 1 - 2^size.
 __device__ static __forceinline__ int symbol_value(uint32_t top, int off, int size) {
-  const int v = (int)__builtin_amdgcn_ubfe(top, (uint32_t)off, (uint32_t)size);
-  const int most = (1 << size) - 1;
-  return 2 * v <= most ? v - most : v;
+  const int t = __builtin_amdgcn_sbfe((int)top, (uint32_t)off, (uint32_t)size);
+  const int below = (int)(0xFFFFFFFFu << (size & 31));
+  return t + ((below ^ (t >> 31)) + 1);
+}
+// The value of the symbol with entry e, found in the bits `top`, which leaves a block at its coefficient
+// k - 1 (at the last one if that is behind it); `block`: 2 bytes in front of it.
+__device__ static __forceinline__ void store_symbol(uint8_t* coefs, uint32_t block, int k, uint32_t top,
+                                                    uint32_t e) {
+  *reinterpret_cast<int16_t*>(coefs + (block + 2u * (uint32_t)min(k, 64))) =
+      (int16_t)symbol_value(top, (int)(e >> 10), (int)(e & 15u));
 }
 
 // The tables of an image: AC luma, AC chroma, DC luma, DC chroma (whole wavefront).
@@ -1227,7 +1240,7 @@ __device__ static void coef_tables(const JpegImage& im, uint16_t* tables) {
 // the mark before it.
 //
 // The bits come from the data without byte stuffing, so topping up is a select.  1024 files of 256
-// pixels: 0.65 ms, on one wavefront per SIMD, bound by the steps' issue and latency (with DC and AC
+// pixels: 0.58 ms, on one wavefront per SIMD, bound by the steps' issue and latency (with DC and AC
 // symbols and the blocks' ends all in one step of 100 instructions 1.05 ms, by one lane per file
 // 12.7 ms).
 constexpr int kMarks = 3;         // block boundaries remembered inside a part (at each quarter)
@@ -1542,14 +1555,15 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
         round = round + 1 == kRounds ? 0 : round + 1;
 #pragma unroll
         for (int i = 0; i < kSteps; ++i) {
-          if (k < 64) {
-            const uint32_t ahead = sym_ahead(r), top = sym_top(r);
-            const uint32_t beyond = __builtin_elementwise_sub_sat(top >> 16, ac_limit);
-            e = s.table[(uint32_t)ac + min(top >> (32 - kFastBits), ac_limit >> (16 - kFastBits)) +
-                        beyond];
-            k += (int)((e >> 4) & 63u);
-            sym_skip(r, (int)(e >> 10), ahead);
-          }
+          const bool on = k < 64;
+          const uint32_t ahead = sym_ahead(r), top = sym_top(r);
+          const uint32_t beyond = __builtin_elementwise_sub_sat(top >> 16, ac_limit);
+          const uint32_t found =
+              s.table[(uint32_t)ac + min(top >> (32 - kFastBits), ac_limit >> (16 - kFastBits)) + beyond];
+          e = on ? found : e;
+          const uint32_t step = on ? found : kNoStep;
+          k += (int)((step >> 4) & 63u);
+          sym_skip(r, (int)(step >> 10), ahead);
         }
       }
       bit = clean_bit(r);
@@ -1772,10 +1786,10 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_decode_kernel(JpegArgs a) {
 // last of the coefficients that it skips), and the blocks to the left of the crop go where the
 // row's first block will be, which is cleared once they are behind. The file's bytes lose their
 // stuffing on the way into the ring (SymbolReader): topping up the bit buffer is then a select.
-// 4096 files of 256 pixels with a restart interval per row: 0.80 to 0.84 ms and 0.25 ms for the
+// 4096 files of 256 pixels with a restart interval per row: 0.72 ms and 0.22 ms for the
 // inverse transform and colours (entropy decoding and transform by the same lanes, block after
 // block, as in jpeg_decode_kernel: 1.42 ms and 0.20 ms for the colours); 1024 files without
-// markers, rows in pieces: 0.22 + 0.07 ms (1.34 + 0.04 ms).
+// markers, rows in pieces: 0.18 + 0.06 ms (1.34 + 0.04 ms).
 struct SymbolReader {
   const uint8_t* chunks;  // as in BitReader
   int64_t chunks_bytes;
@@ -1795,19 +1809,35 @@ __device__ static __forceinline__ void sym_request(SymbolReader& r) {
   if (!r.ended) r.next = load_chunk(r.chunks, r.chunks_bytes, r.at);
   r.pending = true;
 }
+// Byte stuffing leaves four bytes at a time: of the bytes that are not there to stay (a zero behind a 0xFF;
+// a 0xFF in the last place, which waits for its follower and then takes that one's place) there is one at
+// most, as a rule, and it is taken out without looking at single bytes.  (A third of a wavefront's dwords has
+// a 0xFF in one of its lanes: entropy decoding of 4096 files 805 -> 762 us against single bytes for all
+// of them.)  What is more than that goes byte by byte: two such bytes, a marker, the ends of the row's
+// data.
 __device__ static __forceinline__ void sym_accept(SymbolReader& r) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const uint32_t x = r.next[j], inv = ~x;
+    const uint32_t x = r.ended ? 0u : r.next[j];
     const int p = r.at + 4 * j - r.skew;  // file position
-    const bool ff = ((inv - 0x01010101u) & ~inv & 0x80808080u) != 0u;
-    const bool plain = (int)!ff & (int)!r.pend_ff & (int)(p >= r.start) & (int)(p + 4 <= r.n);
-    if ((int)r.ended | (int)plain) {
-      const uint32_t be = r.ended ? 0u : __builtin_bswap32(x);
+    const uint32_t ff = ((x & 0x7F7F7F7Fu) + 0x01010101u) & x & 0x80808080u;  // bit 7 of bytes 0xFF
+    const uint32_t pend = r.pend_ff ? 0xFFu : 0u;
+    const uint32_t behind = (ff << 8) | (pend & 0x80u);    // of bytes behind one
+    const uint32_t drop = (ff << 8) | (ff & 0x80000000u);  // of bytes that go, or wait
+    const bool odd = ((drop & (drop - 1u)) | (x & ((behind << 1) - (behind >> 7)))) != 0u;
+    const bool inside = (int)r.ended | ((int)(p >= r.start) & (int)(p + 4 <= r.n));
+    if ((int)!odd & (int)inside) {
+      const uint32_t low = (drop >> 7) - 1u;  // the bytes in front of it (all of them if there is none)
+      const uint32_t y = x | pend;
+      const uint32_t be = __builtin_bswap32((y & low) | ((y >> 8) & ~low));
+      const int out = drop ? 1 : 0;
       r.ring[(r.have & (kRingBytes / 4 - 1)) * kJpegThreads] =
-          __builtin_amdgcn_alignbit(r.part, be, 8u * (uint32_t)r.nb);
-      r.part = be;
-      ++r.have;
+          __builtin_amdgcn_alignbit(r.part, be, 8u * (uint32_t)r.nb);  // (to be written again if too short)
+      r.part = be >> (8 * out);
+      const int bytes = r.nb + 4 - out;
+      r.have += bytes >> 2;
+      r.nb = bytes & 3;
+      r.pend_ff = (ff >> 31) != 0u;
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -1985,11 +2015,9 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_entropy_kernel(JpegArgs a) 
         k -= 63;
         if (len < 16) {
           e = coef_entry(len + 1, h.symbols[index & 255]);
-          const int size = (int)(e & 15u), off = (int)(e >> 10);
           k += (int)((e >> 4) & 63u);
-          *reinterpret_cast<int16_t*>(coefs + (out + 2u * (uint32_t)min(k, 64))) =
-              (int16_t)symbol_value(top, off, size);
-          sym_skip(r, off, ahead);
+          store_symbol(coefs, out, k, top, e);
+          sym_skip(r, (int)(e >> 10), ahead);
         } else {  // no such code
           bad = true;
           break;
@@ -2040,19 +2068,25 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_entropy_kernel(JpegArgs a) 
       round = round + 1 == kRounds ? 0 : round + 1;
       if (opens) *reinterpret_cast<int16_t*>(coefs + (out + 2u)) = (int16_t)dc;
       // ---- AC symbols; a lane whose block ends waits for the next round ----
+      // No branch: a waiting lane keeps its last symbol and stores that value again.  A symbol's value is
+      // made and stored while the next one's entry comes out of LDS.
+      uint32_t bits = 0;  // those that `e` was found in
 #pragma unroll
       for (int i = 0; i < kSteps; ++i) {
-        if (k < 64) {
-          const uint32_t ahead = sym_ahead(r), top = sym_top(r);
-          const uint32_t beyond = __builtin_elementwise_sub_sat(top >> 16, limit);
-          e = s.table[(uint32_t)ac + min(top >> (32 - kFastBits), limit >> (16 - kFastBits)) + beyond];
-          const int size = (int)(e & 15u), off = (int)(e >> 10);
-          k += (int)((e >> 4) & 63u);
-          *reinterpret_cast<int16_t*>(coefs + (out + 2u * (uint32_t)min(k, 64))) =
-              (int16_t)symbol_value(top, off, size);
-          sym_skip(r, off, ahead);
-        }
+        const bool on = k < 64;
+        const uint32_t ahead = sym_ahead(r), top = sym_top(r);
+        const uint32_t beyond = __builtin_elementwise_sub_sat(top >> 16, limit);
+        const uint32_t found =
+            s.table[(uint32_t)ac + min(top >> (32 - kFastBits), limit >> (16 - kFastBits)) + beyond];
+        if (i > 0) store_symbol(coefs, out, k, bits, e);
+        __builtin_amdgcn_sched_barrier(0);
+        e = on ? found : e;
+        bits = on ? top : bits;
+        const uint32_t step = on ? found : kNoStep;
+        k += (int)((step >> 4) & 63u);
+        sym_skip(r, (int)(step >> 10), ahead);
       }
+      store_symbol(coefs, out, k, bits, e);
     }
     if (bad) {
       reinterpret_cast<CropRec*>(a.workspace + kWorkspaceHeader)[b].valid = 0;

@@ -740,3 +740,68 @@ def test_files_cut_short_with_and_without_an_end_marker(sub, indexed):
     check_prep_against_oracle(prep_to_numpy(buf, rows=keep), sel, what="cut files")
     for b in range(len(cuts), len(chunks)):
         check_neutral_outputs(buf, b)
+
+
+def _rewrite_scan(file, rng, restart_rows):
+    """The file (4:4:4, sides multiples of 8) with entropy-coded data that is mostly ones: every block a
+    random DC difference, up to three coefficients 1023 behind runs of 15 zeros (26 bits, 25 of them
+    ones, next to each other), end of block."""
+    d = file.tobytes()
+    codes, pos = {}, 2
+    while True:
+        m, n = d[pos + 1], int.from_bytes(d[pos + 2:pos + 4], "big")
+        if m == 0xC0:
+            rows, cols = (int.from_bytes(d[pos + 5 + 2 * i:pos + 7 + 2 * i], "big") // 8 for i in (0, 1))
+        o = pos + 4
+        while m == 0xC4 and o < pos + 2 + n:
+            code, sym = 0, o + 17
+            for length in range(1, 17):
+                for _ in range(d[o + length]):
+                    codes[d[o], d[sym]] = format(code, f"0{length}b")
+                    code, sym = code + 1, sym + 1
+                code <<= 1
+            o = sym
+        pos += 2 + n
+        if m == 0xDA:
+            break
+    out, bits = bytearray(d[:pos]), ""
+
+    def flush():
+        nonlocal bits
+        bits += "1" * (-len(bits) % 8)
+        out.extend(bytes(int(bits[i:i + 8], 2) for i in range(0, len(bits), 8)).replace(b"\xff", b"\xff\0"))
+        bits = ""
+    for row in range(rows):
+        for _ in range(cols):
+            for t in (0, 1, 1):
+                size = int(rng.integers(0, 5))
+                bits += codes[t, size] + "".join(rng.choice(["0", "1"], size))
+                bits += (codes[16 + t, 0xFA] + "1" * 10) * int(rng.integers(0, 4)) + codes[16 + t, 0]
+        if restart_rows and row + 1 < rows:
+            flush()
+            out.extend((0xFF, 0xD0 + row % 8))
+    flush()
+    return np.frombuffer(bytes(out) + b"\xff\xd9", np.uint8)
+
+
+@pytest.mark.parametrize("restart_rows", [0, 1])
+def test_stuffed_bytes_at_all_places_of_a_dword(restart_rows):
+    """Byte stuffing is taken out four bytes at a time, byte by byte where more than one of them goes:
+    0xFF at every place of a dword, next to each other too, and in front of the restart markers.  The
+    rows' states come from the markers or the walk, and from an index."""
+    rng = np.random.default_rng(90)
+    kw = {"restart_marker_rows": 1} if restart_rows else {}
+    files, offsets, sizes = _join([_rewrite_scan(_flat(64 + 8 * i, 72, 100, "4:4:4", **kw), rng, restart_rows)
+                                   for i in range(11)])
+    stuffed = np.flatnonzero((files[:-1] == 0xFF) & (files[1:] == 0))
+    pairs = np.intersect1d(stuffed, stuffed + 2)     # FF 00 FF 00
+    for at in (stuffed, pairs):
+        assert np.bincount(at % 4, minlength=4).min() > 500
+    kw = dict(out_size=64, patch=16, num_keep=4, seed=27, batch_index=4)
+    ref = oracle.prep_batch(*_decode_all(files, offsets, sizes), **kw)
+    buf, _ = _gpu_jpeg_prep(files, offsets, sizes, **kw)
+    assert mae.mae_prep_status(buf.workspace) == 0
+    check_prep_against_oracle(prep_to_numpy(buf), ref, what=f"stuffed bytes, restart {restart_rows}")
+    index, dev = _row_index(files, offsets, sizes)
+    got = _prep_with_index(dev, index, **kw)
+    assert torch.equal(got.target, buf.target) and torch.equal(got.visible, buf.visible)
