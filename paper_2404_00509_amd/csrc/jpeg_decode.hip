@@ -1190,7 +1190,8 @@ __device__ static __forceinline__ void store_symbol(uint8_t* coefs, uint32_t blo
       (int16_t)symbol_value(top, (int)(e >> 10), (int)(e & 15u));
 }
 
-// The tables of an image: AC luma, AC chroma, DC luma, DC chroma (whole wavefront).
+// The tables of an image: AC luma, AC chroma, DC luma, DC chroma (kThreads threads).
+template <int kThreads>
 __device__ static void coef_tables(const JpegImage& im, uint16_t* tables) {
   const int lane = threadIdx.x;
   for (int t = 0; t < 2; ++t) {
@@ -1200,11 +1201,11 @@ __device__ static void coef_tables(const JpegImage& im, uint16_t* tables) {
     uint16_t* table = tables + t * kCoefAc;
     const int direct = (int)(limit >> (16 - kFastBits));
 #pragma unroll 4
-    for (int j = lane; j < kDirect; j += kJpegThreads) {
+    for (int j = lane; j < kDirect; j += kThreads) {
       const int e = h.fast[j];
       if (j < direct) table[j] = (uint16_t)(e ? coef_entry(e >> 8, e & 255) : kMiss);
     }
-    for (int j = lane; j < kLongCodes; j += kJpegThreads) {
+    for (int j = lane; j < kLongCodes; j += kThreads) {
       const uint32_t x = limit + (uint32_t)j;
       uint32_t e = kMiss;
       if (x <= 0xFFFFu) {
@@ -1215,7 +1216,7 @@ __device__ static void coef_tables(const JpegImage& im, uint16_t* tables) {
       table[direct + j] = (uint16_t)e;
     }
     table = tables + 2 * kCoefAc + (t << kDcBits);
-    for (int j = lane; j < (1 << kDcBits); j += kJpegThreads) {
+    for (int j = lane; j < (1 << kDcBits); j += kThreads) {
       int index;
       const int len = find_code<0>(g.range, (uint32_t)j << (16 - kDcBits), index);
       const int sym = len < kDcBits ? g.symbols[index & 15] : 16;
@@ -1229,13 +1230,14 @@ __device__ static void coef_tables(const JpegImage& im, uint16_t* tables) {
 // used to decode JPEG files in parallel by Klein and Wiseman, 2003): a decoder set down anywhere in
 // the data soon reads the same blocks as one that came from the start (measured over the synthetic
 // files: after 700 bits at the median, 4000 at the 99th percentile; white noise 2000 / 15000).  The
-// wavefront cuts the data into 64 equal parts, a lane each.  Every lane walks its part from a
+// workgroup, of one wavefront or, for few and long files, of two or four (launch_sync), cuts the data
+// into equal parts, 64 or, with kPartBits and more bits in each, up to a lane each.  Every lane walks its part from a
 // guessed block boundary and notes the one (bit position and block of the MCU) at which it leaves
 // the part, which is where the next lane should have entered.  A lane whose entry turns out to be
 // another walks again, but only until it meets its earlier walk at one of the marks in its part.
 // The first lane's entry is known, so after i rounds the first i lanes are right, whatever the
-// guesses were: when no entry changes any more the result is that of the walk from the start (64
-// rounds at most, three or four in practice).  Prefix sums over the parts' block counts and DC
+// guesses were: when no entry changes any more the result is that of the walk from the start (a round
+// per part at most, three or four in practice).  Prefix sums over the parts' block counts and DC
 // differences then say in which part each row of MCUs starts, and a lane per row walks there from
 // the mark before it.
 //
@@ -1244,6 +1246,7 @@ __device__ static void coef_tables(const JpegImage& im, uint16_t* tables) {
 // symbols and the blocks' ends all in one step of 100 instructions 1.05 ms, by one lane per file
 // 12.7 ms).
 constexpr int kMarks = 3;         // block boundaries remembered inside a part (at each quarter)
+constexpr int kPartBits = 2304;   // of a part, where the file makes more than 64 of them
 
 // A block boundary of a walk and what came before it in the part.
 struct alignas(16) WalkMark {
@@ -1251,11 +1254,16 @@ struct alignas(16) WalkMark {
   uint16_t dc[3];         // sums of DC differences per component, modulo 2^16 like the predictors
   uint16_t pad;
 };
+template <int kWaves>
 struct JpegSyncLds {
   uint16_t table[kCoefTable];
-  uint32_t ring[kRingBytes / 4][kJpegThreads];  // big-endian dwords of the data
-  WalkMark mark[kMarks + 1][kJpegThreads];      // [0]: the entry; bit -1 = none
-  int first_block[kJpegThreads], dc[3][kJpegThreads];
+  uint32_t ring[kWaves][kRingBytes / 4][kJpegThreads];  // big-endian dwords of the data
+  WalkMark mark[kMarks + 1][kWaves * kJpegThreads];     // [0]: the entry; bit -1 = none
+  // per part: what came before it; until that is known where the part is left, bit and block
+  int first_block[kWaves * kJpegThreads], dc[3][kWaves * kJpegThreads];
+  int sums[kWaves][4];     // per wavefront: blocks, DC differences
+  int asked[2][kWaves];    // has a lane to walk again? (in turn)
+  int tail[4];             // last part: block it is left at; DC differences of an MCU of zero bits
 };
 // Reads the data of one image, a bit position at a time.  (hi:lo) >> left are the next 32 bits.
 struct CleanReader {
@@ -1320,28 +1328,33 @@ __device__ static inline int clean_bit(const CleanReader& r) { return 32 * r.tak
 // ends early are looked at, the rows' starts are walked to, then their pieces'.
 enum class SyncStage { kParts, kTail, kRows, kPieces };
 
-__global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
-  __shared__ JpegSyncLds s;
-  const int lane = threadIdx.x;
+template <int kWaves>
+__global__ __launch_bounds__(kWaves * kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
+  constexpr int kParts = kWaves * kJpegThreads;
+  __shared__ JpegSyncLds<kWaves> s;
+  const int lane = threadIdx.x;  // of the workgroup: the part
+  const int wave = __builtin_amdgcn_readfirstlane(lane / kJpegThreads);
   const int b = (int)blockIdx.x;
   const JpegImage* im = &reinterpret_cast<const JpegPrepared*>(a.prepared)[b].im;
-  if (!im->live || im->clean_bytes < 0) return;
+  const int live = im->live;
+  if (!live || im->clean_bytes < 0) return;
   const int nblk = im->hs * im->hs, last_phase = nblk + 1, per_mcu = nblk + 2;
   const int my0 = im->my0, nrows = min(im->nrows, a.max_rows);
   const int row_blocks = im->mcux * per_mcu;
   const int ncols = im->mx1 - im->mx0 + 1, sub = pieces_per_row(nrows, ncols);
   const uint32_t limit_y = long_from(im->ac[0]), limit_c = long_from(im->ac[1]);
-  coef_tables(*im, s.table);
+  coef_tables<kParts>(*im, s.table);
   for (int i = 0; i <= kMarks; ++i) s.mark[i][lane].bit = -1;
   __syncthreads();
 
   CleanReader r;
   r.clean = a.regions + im->region_off;
   r.bytes = im->clean_bytes & (kCutShort - 1);
-  r.ring = &s.ring[0][lane];
+  r.ring = &s.ring[wave][0][lane % kJpegThreads];
   const int bits = 8 * r.bytes;  // below 2^30 (clean_fits)
-  const int quarter =
-      (int)((((int64_t)bits + kJpegThreads - 1) / kJpegThreads + 31) & ~(int64_t)31) / 4;
+  // (the lanes behind the last part have nothing to do until the rows)
+  const int parts = max(kJpegThreads, min(kParts, bits / kPartBits));
+  const int quarter = (int)((((int64_t)bits + parts - 1) / parts + 31) & ~(int64_t)31) / 4;
   constexpr int kPartQuarters = kMarks + 1;
   const int begin = min(bits, lane * kPartQuarters * quarter);
   const int part_end = min(bits, begin + kPartQuarters * quarter);
@@ -1365,32 +1378,71 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
     int bit, phase, limit, end, base0 = 0, base1 = 0, base2 = 0;
     if (stage == SyncStage::kParts) {
       if (round) {
-        int e = __shfl_up(leave, 1), ph = __shfl_up(leave_phase, 1);
+        int e, ph;
+        if constexpr (kWaves == 1) {
+          e = __shfl_up(leave, 1);
+          ph = __shfl_up(leave_phase, 1);
+        } else {
+          s.first_block[lane] = leave;
+          s.dc[0][lane] = leave_phase;
+          __syncthreads();
+          e = s.first_block[max(lane - 1, 0)];
+          ph = s.dc[0][max(lane - 1, 0)];
+        }
         if (lane == 0) {
           e = 0;
           ph = 0;
+        }
+        if (lane >= parts) {
+          e = enter;
+          ph = enter_phase;
         }
         go = e != enter || ph != enter_phase;
         enter = e;
         enter_phase = ph;
       } else {
-        go = true;
+        go = lane < parts;
       }
-      if (round > kJpegThreads || __builtin_amdgcn_ballot_w64(go) == 0) {
+      bool more = __builtin_amdgcn_ballot_w64(go) != 0;
+      if constexpr (kWaves > 1) {  // (the barrier also ends the exchange above)
+        if (lane % kJpegThreads == 0) s.asked[round & 1][wave] = more ? 1 : 0;
+        __syncthreads();
+        int any = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) any |= s.asked[round & 1][w];
+        more = any != 0;
+      }
+      if (round > parts || !more) {
         // blocks and DC differences before each part
         first_block = blocks;
         int d0 = dc0, d1 = dc1, d2 = dc2;
         for (int off = 1; off < kWave; off <<= 1) {
           const int t = __shfl_up(first_block, off), t0 = __shfl_up(d0, off),
                     t1 = __shfl_up(d1, off), t2 = __shfl_up(d2, off);
-          if (lane >= off) {
+          if (lane % kWave >= off) {
             first_block += t;
             d0 += t0;
             d1 += t1;
             d2 += t2;
           }
         }
-        total = __shfl(first_block, kWave - 1);
+        if (lane % kWave == kWave - 1) {
+          s.sums[wave][0] = first_block;
+          s.sums[wave][1] = d0;
+          s.sums[wave][2] = d1;
+          s.sums[wave][3] = d2;
+        }
+        __syncthreads();
+        total = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+          total += s.sums[w][0];
+          if (w >= wave) continue;
+          first_block += s.sums[w][0];
+          d0 += s.sums[w][1];
+          d1 += s.sums[w][2];
+          d2 += s.sums[w][3];
+        }
         first_block -= blocks;
         s.first_block[lane] = first_block;
         s.dc[0][lane] = d0 - dc0;
@@ -1410,15 +1462,15 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
     } else if (stage == SyncStage::kTail) {
       // where the data ends early zero bits follow, block after block of a component the same: one
       // MCU tells
-      go = lane == kWave - 1 && total < (my0 + nrows) * row_blocks;
+      go = lane == parts - 1 && total < (my0 + nrows) * row_blocks;
       bit = leave;
       phase = leave_phase;
       limit = per_mcu;
       end = kNever;
     } else {
-      if (stage == SyncStage::kRows && __builtin_amdgcn_ballot_w64(row < nrows) == 0) {
+      if (stage == SyncStage::kRows && row - lane >= nrows) {  // (the same for all lanes)
         // (files whose data ends early are decoded row by row)
-        if (im->live != kLiveCoefs || total < (my0 + nrows) * row_blocks || nrows != im->nrows ||
+        if (live != kLiveCoefs || total < (my0 + nrows) * row_blocks || nrows != im->nrows ||
             !pieces_fit(a, im->size, im->scan_off, nrows))
           break;
         stage = SyncStage::kPieces;
@@ -1429,7 +1481,7 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
         target += (im->mx0 + (lane - row * sub) * ncols / sub) * per_mcu;
       go = row < nrows && (target < total || target == 0);
       from = 0;  // the last part that starts at or before the row's first block
-      for (int step = kJpegThreads / 2; step > 0; step >>= 1)
+      for (int step = kParts / 2; step > 0; step >>= 1)
         if (s.first_block[from + step] <= target) from += step;
       const int inside = target - s.first_block[from];
       WalkMark m = s.mark[0][from];
@@ -1590,13 +1642,22 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
       if (__builtin_expect((im->clean_bytes & kCutShort) != 0, 0)) {
         // Behind a file that merely stops a row is zero bits, and so are the blocks between the last
         // that the data began and the row's first (the rest of an MCU, then whole ones).
-        const int ph = __shfl(leave_phase, kWave - 1), rest = ph ? per_mcu - ph : 0;
-        const int mcu0 = __shfl(sum0, kWave - 1), mcu1 = __shfl(sum1, kWave - 1),
-                  mcu2 = __shfl(sum2, kWave - 1);
-        const int end0 = s.dc[0][kWave - 1] + __shfl(dc0, kWave - 1),
-                  end1 = s.dc[1][kWave - 1] + __shfl(dc1, kWave - 1),
-                  end2 = s.dc[2][kWave - 1] + __shfl(dc2, kWave - 1);
-        for (int i = lane; i < nrows; i += kJpegThreads) {
+        if (lane == parts - 1) {
+          s.tail[0] = leave_phase;
+          s.tail[1] = sum0;
+          s.tail[2] = sum1;
+          s.tail[3] = sum2;
+        }
+        __syncthreads();
+        const int ph = s.tail[0], rest = ph ? per_mcu - ph : 0;
+        const int mcu0 = s.tail[1], mcu1 = s.tail[2], mcu2 = s.tail[3];
+        int end0 = 0, end1 = 0, end2 = 0;
+        for (int w = 0; w < kWaves; ++w) {
+          end0 += s.sums[w][1];
+          end1 += s.sums[w][2];
+          end2 += s.sums[w][3];
+        }
+        for (int i = lane; i < nrows; i += kParts) {
           const int target = (my0 + i) * row_blocks;
           if (target < total || target == 0) continue;
           const int whole = (target - total - rest) / per_mcu;
@@ -1640,7 +1701,7 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_sync_kernel(JpegArgs a) {
         if (lane == 0) reinterpret_cast<JpegPrepared*>(a.prepared)[b].im.live = kLivePieces;
         break;
       }
-      row += kJpegThreads;
+      row += kParts;
     }
   }
   if (bad) {
@@ -1937,7 +1998,7 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_entropy_kernel(JpegArgs a) 
     }
     first_task[i + 1] = first_task[i] + rows;
     if (rows == 0) continue;
-    coef_tables(prepared[i].im, s.table + i * kCoefTable);
+    coef_tables<kJpegThreads>(prepared[i].im, s.table + i * kCoefTable);
   }
   __syncthreads();
   const int ntasks = first_task[kGroup];
@@ -2376,14 +2437,30 @@ __global__ __launch_bounds__(kIdctThreads) void jpeg_idct_kernel(JpegArgs a, int
   }
 }
 
+// Wavefronts per file.  Long files fill more than one with parts of kPartBits bits, which shortens the
+// walks until the SIMDs have other files to switch to; on files of 256 pixels (2200 to 3200 bits in each of
+// 64 parts) shorter parts only take more rounds.  Whole calls with 1 / 2 / 4 of them in us, files without
+// markers of 500 pixels: 16 files 1740 / 1404 / 1298, 128 1863 / 1527 / 1491, 512 2137 / 1853 / 1675, 1024
+// 2455 / 2284 / 2631; with 2200 bits or less in a part, 256 pixels: 16 files 674 / 642 / 686, 256 809 / 820 /
+// 833, 1024 1058 / 1110 / 1486, 2048 1783 / 1886 / 2627.
+static hipError_t launch_sync(const JpegArgs& a, hipStream_t stream) {
+  const int waves = a.slot_side < 320 || a.B > 1024 ? 1 : (a.B > 512 ? 2 : 4);
+  if (waves == 4)
+    hipLaunchKernelGGL(jpeg_sync_kernel<4>, dim3((uint32_t)a.B), dim3(4 * kJpegThreads), 0, stream, a);
+  else if (waves == 2)
+    hipLaunchKernelGGL(jpeg_sync_kernel<2>, dim3((uint32_t)a.B), dim3(2 * kJpegThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL(jpeg_sync_kernel<1>, dim3((uint32_t)a.B), dim3(kJpegThreads), 0, stream, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_jpeg_index(const JpegArgs& a, hipStream_t stream) {
   dim3 block(kJpegThreads);
   hipLaunchKernelGGL(jpeg_tables_kernel, dim3((uint32_t)a.B), block, 0, stream, a);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   if (!a.row_index) {
-    hipLaunchKernelGGL(jpeg_sync_kernel, dim3((uint32_t)a.B), block, 0, stream, a);
-    err = hipGetLastError();
+    err = launch_sync(a, stream);
     if (err != hipSuccess) return err;
   }
   hipLaunchKernelGGL(jpeg_scan_kernel, dim3((uint32_t)((a.B + kScanImages - 1) / kScanImages)),
@@ -2397,8 +2474,7 @@ hipError_t launch_jpeg_decode(const JpegArgs& a, hipStream_t stream) {
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   if (!a.row_index) {
-    hipLaunchKernelGGL(jpeg_sync_kernel, dim3((uint32_t)a.B), block, 0, stream, a);
-    err = hipGetLastError();
+    err = launch_sync(a, stream);
     if (err != hipSuccess) return err;
   }
   // files whose rows are not independent (its wavefronts leave at once where there are none)

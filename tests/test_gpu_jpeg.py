@@ -805,3 +805,51 @@ def test_stuffed_bytes_at_all_places_of_a_dword(restart_rows):
     index, dev = _row_index(files, offsets, sizes)
     got = _prep_with_index(dev, index, **kw)
     assert torch.equal(got.target, buf.target) and torch.equal(got.visible, buf.visible)
+
+
+@pytest.mark.parametrize("B,side", [(23, 512), (513, 512), (1025, 512)])
+def test_the_parallel_walk_by_several_wavefronts(B, side):
+    """Files without markers are walked by four wavefronts in batches of up to 512, by two up to 1024
+    and by one beyond, with 64 to 256 parts by the length of the data: just over a wavefront's parts,
+    parts that end in the last wavefront, all of them taken; flat images and single MCUs next to them,
+    noise, data that simply stops and data that a marker ends too early."""
+    import io
+
+    from PIL import Image
+    rng = np.random.default_rng(side)
+    jobs = [("noise", 0.26, 100), ("noise", 0.31, 90), ("ramp", 1.0, 95), ("noise", 0.5, 100), ("flat", 1.0, 90),
+            ("noise", 0.9, 75), ("noise", 0.05, 90), ("noise", 1.0, 60), ("noise", 0.5, 75)]
+    chunks = []
+    for kind, part, quality in jobs:
+        h = w = max(8, int(part * side) - 3)
+        img = np.full((h, w, 3), 77, np.uint8)
+        if kind == "noise":
+            img = rng.integers(0, 256, (h, w, 3), dtype=np.uint8)
+        elif kind == "ramp":
+            img = (np.add.outer(np.arange(h) * 3, np.arange(w) * 2)[..., None]
+                   + np.array([0, 40, 90])).astype(np.uint8)
+        buf = io.BytesIO()
+        Image.fromarray(img).save(buf, format="JPEG", quality=quality, subsampling="4:2:0")
+        chunks.append(np.frombuffer(buf.getvalue(), np.uint8))
+    bits = np.array([8 * c.size for c in chunks])
+    assert bits.min() < 64 * 2304 and bits.max() > 256 * 2304
+    assert ((bits > 66 * 2304) & (bits < 128 * 2304)).any() and ((bits > 130 * 2304) & (bits < 250 * 2304)).any()
+    n = len(chunks)
+    for i in (3, 7):  # stops; ends with a marker
+        chunks.append(chunks[i][:chunks[i].size * 2 // 3])
+    chunks.append(np.concatenate([chunks[7][:chunks[7].size // 2], np.array([0xFF, 0xD9], np.uint8)]))
+    files, first, lens = _join(chunks)
+    pick = np.arange(B) % len(chunks)
+    images, offs, hs, ws = _decode_all(files, first, lens)
+    kw = dict(out_size=32, patch=16, num_keep=2, scale=(1.0, 1.0), ratio=(1.0, 1.0), seed=35, batch_index=1)
+    buf, _ = _gpu_jpeg_prep(files, first[pick], lens[pick], max_image_side=side, **kw)
+    ref = oracle.prep_batch(images, offs[pick], hs[pick], ws[pick], **kw)
+    keep = np.flatnonzero(pick != n + 2)
+    np.testing.assert_array_equal(buf.crop[:, 5].cpu().numpy(), pick != n + 2)
+    sel = {k: (v[keep] if v is not None else None) for k, v in ref.items()}
+    check_prep_against_oracle(prep_to_numpy(buf, rows=keep), sel, what=f"{B} files, side {side}")
+    if B < 64:  # the index comes from the same walk, over whole images
+        index, dev = _row_index(files, first[pick], lens[pick], max_image_side=side)
+        got = _prep_with_index(dev, index, max_image_side=side, **kw)
+        keep = torch.from_numpy(keep).cuda()
+        assert torch.equal(got.target[keep], buf.target[keep])
