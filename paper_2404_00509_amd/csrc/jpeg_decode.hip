@@ -585,69 +585,124 @@ __device__ static inline bool pieces_fit(const JpegArgs& a, int size, int scan_o
                                       (int64_t)a.slot_side * a.slot_side * 3;
 }
 
+// The two passes over a file's bytes below take 16 of them per lane and step, four at a time: bit 7 of
+// every byte of x that is 0xFF, or zero, and bit i of a mask for byte i of a lane's 16.
+__device__ static inline uint32_t ff_bytes(uint32_t x) {
+  return ((x & 0x7F7F7F7Fu) + 0x01010101u) & x & 0x80808080u;
+}
+__device__ static inline uint32_t zero_bytes(uint32_t x) {
+  return ~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu);
+}
+__device__ static inline uint32_t byte_mask(uint32_t m0, uint32_t m1, uint32_t m2, uint32_t m3) {
+  const uint32_t lo = __builtin_amdgcn_udot4(m1 >> 7, 0x80402010u,
+                                             __builtin_amdgcn_udot4(m0 >> 7, 0x08040201u, 0u, false), false);
+  const uint32_t hi = __builtin_amdgcn_udot4(m3 >> 7, 0x80402010u,
+                                             __builtin_amdgcn_udot4(m2 >> 7, 0x08040201u, 0u, false), false);
+  return lo | (hi << 8);
+}
+// Bits n and up / below n, of 16 (any n).
+__device__ static inline uint32_t mask_from(int n) { return (0xFFFFu << min(max(n, 0), 16)) & 0xFFFFu; }
+__device__ static inline uint32_t mask_below(int n) { return ~mask_from(n) & 0xFFFFu; }
+// Sum of the lanes' x (below 32) over the lanes in front of this one, and over all of them.
+__device__ static inline int lanes_before(int x, int& total) {
+  int before = 0;
+  total = 0;
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    const uint64_t has = __builtin_amdgcn_ballot_w64((x >> k) & 1);
+    before += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u)) << k;
+    total += __popcll(has) << k;
+  }
+  return before;
+}
+
 // Entropy-coded data from scan_off to the first marker, byte stuffing removed, into `clean`, with
 // the file position of every 16th byte in `map`; returns how many bytes, + kCutShort when the file
 // ends before a marker does it (whole wavefront).  The file is read in aligned 16-byte pieces, one
-// per lane, the next step's in flight; a prefix sum gives each piece its place in the LDS buffer,
-// which leaves in 1-KiB stores.
+// per lane, the next two steps' on their way (a step looks at the first byte of the next one); a prefix
+// sum gives each piece its place in the LDS buffer, which leaves in 1-KiB stores.  What bounds it is
+// a wavefront's chain of latencies per step, 1.2 us: with single bytes looked at and stored, prefix sums through
+// LDS and one step's pieces on their way, which the look at the next one waited for, it was 2.9 us.  The
+// whole kernel, 1024 files of 256 pixels 92 -> 56 us, 512 files of 500 pixels 254 -> 115 us; 4096 files whose
+// restart markers it looks for 158 -> 131 us.
 __device__ static int jpeg_unstuff(const JpegArgs& a, int64_t origin, int scan_off, int n,
                                    uint8_t* stage, uint8_t* clean, int32_t* map) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  typedef u32x4 u32x4_a1 __attribute__((aligned(1)));
+  typedef uint64_t u64_a1 __attribute__((aligned(1)));
+  typedef uint32_t u32_a1 __attribute__((aligned(1)));
+  typedef uint16_t u16_a1 __attribute__((aligned(1)));
   const int lane = threadIdx.x;
   const int64_t first = (origin + scan_off) & ~(int64_t)15;
   const int64_t end = origin + n;
   int done = 0, fill = 0;  // bytes stored / bytes waiting in `stage`
-  uint32_t carry = 0;      // last byte of the step before
+  uint32_t carry = 0;      // the last byte of the step before was 0xFF
   int cut = kCutShort;
   u32x4_a8 cur = load_chunk(a.files, a.files_bytes, first + lane * 16);
+  u32x4_a8 next = load_chunk(a.files, a.files_bytes, first + lane * 16 + kCleanStep);
   for (int64_t base = first; base < end; base += kCleanStep) {
     const int64_t at = base + lane * 16;
-    const u32x4_a8 next = load_chunk(a.files, a.files_bytes, at + kCleanStep);
-    uint32_t follow = (uint32_t)__shfl_down((int)(cur.x & 0xFFu), 1);
-    const uint32_t wrap = (uint32_t)__shfl((int)(next.x & 0xFFu), 0);
-    if (lane == kJpegThreads - 1) follow = wrap;
-    uint32_t prev = (uint32_t)__shfl_up((int)(cur.w >> 24), 1);
-    if (lane == 0) prev = carry;
+    const u32x4_a8 later = load_chunk(a.files, a.files_bytes, at + 2 * kCleanStep);
     const int p0 = (int)(at - origin);
-    uint32_t keep = 0;
-    int stop = 16;  // first byte of the piece that belongs to a marker
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint32_t b = (cur[i >> 2] >> (8 * (i & 3))) & 0xFFu;
-      const uint32_t before = i ? (cur[(i - 1) >> 2] >> (8 * ((i - 1) & 3))) & 0xFFu : prev;
-      const uint32_t after = i < 15 ? (cur[(i + 1) >> 2] >> (8 * ((i + 1) & 3))) & 0xFFu : follow;
-      const int pp = p0 + i;
-      const bool inside = pp >= scan_off && pp < n;
-      const bool stuffing = b == 0u && before == 0xFFu && pp > scan_off;
-      const bool marker = b == 0xFFu && !(after == 0u && pp + 1 < n);
-      if (inside && !stuffing) keep |= 1u << i;
-      if (inside && marker && stop == 16) stop = i;
-    }
-    const uint64_t stops = __builtin_amdgcn_ballot_w64(stop < 16);
-    if (stops) {
+    const uint32_t ff = byte_mask(ff_bytes(cur.x), ff_bytes(cur.y), ff_bytes(cur.z), ff_bytes(cur.w));
+    const uint32_t zero =
+        byte_mask(zero_bytes(cur.x), zero_bytes(cur.y), zero_bytes(cur.z), zero_bytes(cur.w));
+    // the byte in front of the piece is 0xFF; the one behind it is zero
+    const uint64_t last_ff = __builtin_amdgcn_ballot_w64(ff >> 15 != 0u);
+    const uint64_t first_zero = __builtin_amdgcn_ballot_w64((zero & 1u) != 0u);
+    const uint64_t wrap = (uint64_t)((__builtin_amdgcn_readfirstlane((int)next.x) & 0xFF) == 0);
+    const uint32_t prev = (uint32_t)(((last_ff << 1) | carry) >> lane) & 1u;
+    const uint32_t follow = (uint32_t)(((first_zero >> 1) | (wrap << 63)) >> lane) & 1u;
+    const uint32_t inside = mask_from(scan_off - p0) & mask_below(n - p0);
+    const uint32_t stuffing = zero & ((ff << 1) | prev) & mask_from(scan_off + 1 - p0);
+    const uint32_t marker = ff & inside & ~(((zero >> 1) | (follow << 15)) & mask_below(n - 1 - p0));
+    uint32_t keep = inside & ~stuffing;
+    const uint64_t stops = __builtin_amdgcn_ballot_w64(marker != 0u);
+    if (stops) {  // (of the first piece with a marker, what comes before it)
       const int who = __builtin_ctzll(stops);
-      keep &= lane < who ? 0xFFFFu : (lane == who ? (1u << stop) - 1u : 0u);
+      keep &= lane < who ? 0xFFFFu : (lane == who ? (marker & (0u - marker)) - 1u : 0u);
     }
     const int cnt = __popc(keep);
-    int place = cnt;
-    for (int off = 1; off < kWave; off <<= 1) {
-      const int t = __shfl_up(place, off);
-      if (lane >= off) place += t;
+    int total;
+    const int place = fill + lanes_before(cnt, total);
+    // the kept bytes next to each other, and where the one was that is the 16th of the data
+    uint64_t lo = (uint64_t)cur.x | ((uint64_t)cur.y << 32), hi = (uint64_t)cur.z | ((uint64_t)cur.w << 32);
+    const int mapped = -(done + place) & 15;
+    int from = mapped;
+    uint32_t drop = keep ? ~keep & ((1u << (31 - __clz((int)keep))) - 1u) : 0u;
+    for (int gone = 0; drop; ++gone) {
+      const int q = __builtin_ctz(drop);
+      from += q + gone <= from ? 1 : 0;
+      const uint64_t low = q < 8 ? ~(uint64_t)0 << (8 * q) : 0u;         // bytes q .. 7
+      const uint64_t high = q < 8 ? ~(uint64_t)0 : ~(uint64_t)0 << (8 * (q - 8));
+      lo = (lo & ~low) | (((lo >> 8) | (hi << 56)) & low);
+      hi = (hi & ~high) | ((hi >> 8) & high);
+      drop = (drop & (drop - 1u)) >> 1;
     }
-    const int total = __shfl(place, kWave - 1);
-    place += fill - cnt;
-    int mapped = -1, mapped_pos = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      if (!((keep >> i) & 1u)) continue;
-      stage[place] = (uint8_t)(cur[i >> 2] >> (8 * (i & 3)));
-      if (((done + place) & 15) == 0) {  // at most one of a piece's 16
-        mapped = (done + place) >> 4;
-        mapped_pos = p0 + i;
+    uint8_t* dst = stage + place;
+    if (cnt == 16) {
+      *reinterpret_cast<u32x4_a1*>(dst) =
+          u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+    } else {
+      if (cnt & 8) {
+        *reinterpret_cast<u64_a1*>(dst) = lo;
+        lo = hi;
+        dst += 8;
       }
-      ++place;
+      if (cnt & 4) {
+        *reinterpret_cast<u32_a1*>(dst) = (uint32_t)lo;
+        lo >>= 32;
+        dst += 4;
+      }
+      if (cnt & 2) {
+        *reinterpret_cast<u16_a1*>(dst) = (uint16_t)lo;
+        lo >>= 16;
+        dst += 2;
+      }
+      if (cnt & 1) *dst = (uint8_t)lo;
     }
-    if (mapped >= 0) map[mapped] = mapped_pos;
+    if (mapped < cnt) map[(done + place + mapped) >> 4] = p0 + from;
     fill += total;
     __syncthreads();
     if (fill >= kCleanStep) {
@@ -664,8 +719,9 @@ __device__ static int jpeg_unstuff(const JpegArgs& a, int64_t origin, int scan_o
       cut = 0;
       break;
     }
-    carry = (uint32_t)__shfl((int)(cur.w >> 24), kJpegThreads - 1);
+    carry = (uint32_t)(last_ff >> 63);
     cur = next;
+    next = later;
   }
   if (lane * 16 < fill)
     reinterpret_cast<u32x4*>(clean + done)[lane] = reinterpret_cast<u32x4*>(stage)[lane];
@@ -859,8 +915,8 @@ __device__ static void jpeg_prepare_image(const JpegArgs& a, int b, JpegImage& i
   if (rec.restart != rec.mcux) return;  // rows not independent: the scan kernel finds the states
 
   // restart markers: marker m (0-based) ends MCU row m; row r starts after marker r - 1.  The
-  // file is scanned in aligned 16-byte pieces of the buffer, one per lane and step, the next
-  // step's pieces loaded while this step's are examined.
+  // file is scanned in aligned 16-byte pieces of the buffer, one per lane and step, the next two
+  // steps' pieces on their way while this step's are examined.
   RowState start;
   start.nbits = 0;
   start.acc = 0;
@@ -872,43 +928,35 @@ __device__ static void jpeg_prepare_image(const JpegArgs& a, int b, JpegImage& i
   const int64_t last = origin + n - 1;  // a marker starts before this byte
   int seen = 0;                         // markers before the current step
   u32x4_a8 cur = load_chunk(a.files, a.files_bytes, first + lane * 16);
+  u32x4_a8 next = load_chunk(a.files, a.files_bytes, first + lane * 16 + kJpegThreads * 16);
   for (int64_t base = first; base < last && seen <= my1; base += kJpegThreads * 16) {
     const int64_t at = base + lane * 16;
-    const u32x4_a8 next = load_chunk(a.files, a.files_bytes, at + kJpegThreads * 16);
-    // the byte after this piece: the first of the next lane's, or of the next step's
-    uint32_t follow = (uint32_t)__shfl_down((int)(cur.x & 0xFFu), 1);
-    const uint32_t wrap = (uint32_t)__shfl((int)(next.x & 0xFFu), 0);
-    if (lane == kJpegThreads - 1) follow = wrap;
+    const u32x4_a8 later = load_chunk(a.files, a.files_bytes, at + 2 * kJpegThreads * 16);
     const int p0 = (int)(at - origin);  // file position of the piece (negative before the file)
-    uint32_t mask = 0;                  // bit i: a restart marker starts at byte p0 + i
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint32_t b0 = (cur[i >> 2] >> (8 * (i & 3))) & 0xFFu;
-      const uint32_t b1 = i < 15 ? (cur[(i + 1) >> 2] >> (8 * ((i + 1) & 3))) & 0xFFu : follow;
-      const int pp = p0 + i;
-      if (pp >= rec.scan_off && pp + 1 < n && b0 == 0xFFu && (b1 & 0xF8u) == 0xD0u)
-        mask |= 1u << i;
-    }
-    const int cnt = __popc(mask);
-    // rank of this lane's first marker among the wavefront's: counts of the lanes before it
-    int before = cnt;
-    for (int off = 1; off < kWave; off <<= 1) {
-      const int t = __shfl_up(before, off);
-      if (lane >= off) before += t;
-    }
-    const int total = __shfl(before, kWave - 1);
-    before -= cnt;
-    for (int i = 0; i < 16; ++i) {
-      if (!((mask >> i) & 1u)) continue;
-      // the row that starts after this marker
-      const int row = seen + before + __popc(mask & ((1u << i) - 1u)) + 1;
-      if (row >= my0 && row <= my1 && row - my0 < a.max_rows) {
-        start.pos = p0 + i + 2;
-        states[row - my0] = start;
+    const uint32_t ff = byte_mask(ff_bytes(cur.x), ff_bytes(cur.y), ff_bytes(cur.z), ff_bytes(cur.w));
+    const auto rst = [](uint32_t x) { return zero_bytes((x & 0xF8F8F8F8u) ^ 0xD0D0D0D0u); };  // 0xD0 .. 0xD7
+    const uint32_t second = byte_mask(rst(cur.x), rst(cur.y), rst(cur.z), rst(cur.w));
+    // the byte after this piece: the first of the next lane's, or of the next step's
+    const uint64_t first_second = __builtin_amdgcn_ballot_w64((second & 1u) != 0u);
+    const uint64_t wrap = (uint64_t)((__builtin_amdgcn_readfirstlane((int)next.x) & 0xF8) == 0xD0);
+    const uint32_t follow = (uint32_t)(((first_second >> 1) | (wrap << 63)) >> lane) & 1u;
+    // bit i: a restart marker starts at byte p0 + i
+    uint32_t mask = ff & ((second >> 1) | (follow << 15)) & mask_from(rec.scan_off - p0) &
+                    mask_below(n - 1 - p0);
+    if (__builtin_amdgcn_ballot_w64(mask != 0u)) {
+      int total;
+      // the row that starts after the lane's first marker
+      int row = seen + lanes_before(__popc(mask), total) + 1;
+      for (; mask; mask &= mask - 1u, ++row) {
+        if (row >= my0 && row <= my1 && row - my0 < a.max_rows) {
+          start.pos = p0 + __builtin_ctz(mask) + 2;
+          states[row - my0] = start;
+        }
       }
+      seen += total;
     }
-    seen += total;
     cur = next;
+    next = later;
   }
   if (my0 == 0 && lane == 0) {
     start.pos = rec.scan_off;
