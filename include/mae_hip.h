@@ -295,7 +295,8 @@ int mae_normpix_loss_static(const mae_loss_desc* d, float* loss, void* grad, voi
  *                 match p (MAE_ERR_SHAPE otherwise)
  * Outputs as for mae_normpix_loss.  Samples flagged invalid by mae_prep_batch add nothing to the
  * loss and get a zero gradient.  workspace: mae_loss_from_images_workspace_bytes(p, d) bytes,
- * 256-byte aligned.
+ * 256-byte aligned; the size never falls as B grows, so one made for an epoch's batches serves its
+ * smaller last one.
  * ---------------------------------------------------------------------------------------------- */
 int mae_normpix_loss_from_images(const mae_prep_desc* p, const void* prep_workspace,
                                  size_t prep_workspace_bytes, const mae_loss_desc* d, float* loss,

@@ -160,12 +160,10 @@ int crop_side_of(const mae_prep_desc* d, int slot_side) {
   if (d->input_format == MAE_INPUT_JPEG) return slot_side;
   return d->max_image_side > 0 ? d->max_image_side : 256;
 }
-mae::CropPlan crop_plan_of(const mae_prep_desc* d, int slot_side, mae::CropUse use) {
-  const int parts = use == mae::CropUse::kLoss
-                        ? mae::crop_loss_min_parts(d->B, d->out_size, d->patch)
-                        : 1;
+mae::CropPlan crop_plan_of(const mae_prep_desc* d, int slot_side, mae::CropUse use,
+                           int min_parts = 1) {
   const int side = crop_side_of(d, slot_side);
-  return mae::crop_plan(d->out_size, d->patch, side, parts,
+  return mae::crop_plan(d->out_size, d->patch, side, min_parts,
                         mae::crop_whole_rows(d->out_size, d->patch, side, use));
 }
 mae::CropUse prep_use(const mae_prep_desc* d) {
@@ -247,7 +245,7 @@ mae::JpegArgs make_jpeg_args(const mae_prep_desc* d, const PrepWorkspace& wsl, u
 // What the resampling kernel needs to know about the source, for both input formats: with JPEG
 // input its "images" are the decoded regions in the workspace.
 mae::CropArgs make_crop_args(const mae_prep_desc* d, const PrepShape& sh, const PrepWorkspace& wsl,
-                             const uint8_t* ws, mae::CropUse use) {
+                             const uint8_t* ws, mae::CropUse use, int min_parts = 1) {
   mae::CropArgs ca;
   memset(&ca, 0, sizeof(ca));
   ca.B = d->B;
@@ -258,7 +256,7 @@ mae::CropArgs make_crop_args(const mae_prep_desc* d, const PrepShape& sh, const 
   ca.K = d->num_keep;
   ca.D = sh.D;
   ca.visible_bf16 = d->out_dtype == MAE_BF16;
-  const mae::CropPlan plan = crop_plan_of(d, wsl.slot_side, use);
+  const mae::CropPlan plan = crop_plan_of(d, wsl.slot_side, use, min_parts);
   ca.tile_pixels = plan.tile_pixels;
   ca.col_parts = plan.col_parts;
   ca.part_patches = plan.part_patches;
@@ -586,13 +584,17 @@ int validate_loss_from_images(const mae_prep_desc* p, const mae_loss_desc* d, Pr
 }
 }  // namespace
 
+namespace {
+size_t loss_from_images_bytes(int64_t partials) {
+  return (size_t)partials * sizeof(double) + (size_t)mae::kMaxCounts * sizeof(int32_t);
+}
+}  // namespace
+
 size_t mae_loss_from_images_workspace_bytes(const mae_prep_desc* p, const mae_loss_desc* d) {
   PrepShape sh;
   if (validate_loss_from_images(p, d, &sh) != MAE_OK) return 0;
-  const mae::CropArgs ca =
-      make_crop_args(p, sh, prep_workspace(p), nullptr, mae::CropUse::kLoss);
-  return (size_t)mae::crop_loss_partials(ca) * sizeof(double) +
-         (size_t)mae::kMaxCounts * sizeof(int32_t);
+  const int side = crop_side_of(p, prep_workspace(p).slot_side);
+  return loss_from_images_bytes(mae::crop_loss_most_partials(p->B, p->out_size, p->patch, side));
 }
 
 int mae_normpix_loss_from_images(const mae_prep_desc* p, const void* prep_workspace_ptr,
@@ -606,16 +608,19 @@ int mae_normpix_loss_from_images(const mae_prep_desc* p, const void* prep_worksp
   if (!aligned(d->pred, 16) || (grad && !aligned(grad, 16))) return MAE_ERR_RANGE;
   if (!aligned(prep_workspace_ptr, 256) || prep_workspace_bytes < mae_prep_workspace_bytes(p))
     return MAE_ERR_WORKSPACE;
-  if (!workspace || !aligned(workspace, 256) ||
-      workspace_bytes < mae_loss_from_images_workspace_bytes(p, d))
+  const PrepWorkspace wsl = prep_workspace(p);
+  const int64_t least = mae::crop_loss_least_partials(p->B, p->out_size, p->patch,
+                                                      crop_side_of(p, wsl.slot_side));
+  if (!workspace || !aligned(workspace, 256) || workspace_bytes < loss_from_images_bytes(least))
     return MAE_ERR_WORKSPACE;
   rc = have_device();
   if (rc != MAE_OK) return rc;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
 
-  mae::CropArgs ca = make_crop_args(p, sh, prep_workspace(p),
-                                    static_cast<const uint8_t*>(prep_workspace_ptr),
-                                    mae::CropUse::kLoss);
+  const size_t room = (workspace_bytes - loss_from_images_bytes(0)) / sizeof(double);
+  mae::CropArgs ca =
+      make_crop_args(p, sh, wsl, static_cast<const uint8_t*>(prep_workspace_ptr), mae::CropUse::kLoss,
+                     mae::crop_loss_min_parts(p->B, p->out_size, p->patch, (int64_t)room));
   const double count = (double)d->D * (double)(d->num_masked > 0 ? d->num_masked : 1);
   ca.pred = d->pred;
   ca.grad = grad;

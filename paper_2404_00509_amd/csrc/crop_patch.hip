@@ -1388,16 +1388,6 @@ CropPlan crop_plan(int S, int p, int max_side, int min_parts, int whole_rows) {
   }
 }
 
-// Column parts that a small batch's rows of patches are split into at least for the loss over large
-// patches, whose workgroups take one patch after the other: so many that there are four of them per
-// compute unit (64 images of 256 pixels -> 192, p = 24, with their input pipeline: 44.4 -> 41.5 us).  Where a part's patches are
-// dealt to the wavefronts, or a thread takes a position of all of them, fewer patches per part only
-// repeat the set-up.
-int crop_loss_min_parts(int B, int S, int p) {
-  const int64_t bands = (int64_t)B * (S / p);
-  return 3 * p * p <= 768 || bands >= kCropFill ? 1 : (int)((kCropFill + bands - 1) / bands);
-}
-
 size_t crop_lds_bytes(const CropArgs& a) {
   return (size_t)(a.tile_pixels + 4) * 4 + (size_t)a.p * 16 + (size_t)a.part_patches * a.p * 8;
 }
@@ -1421,6 +1411,32 @@ __global__ __launch_bounds__(256) void crop_loss_reduce_kernel(const double* par
     __syncthreads();
   }
   if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+}
+
+// Doubles of workspace that a call asks for at least: as many as its rows of patches leave when they are
+// staged whole and split into no more column parts than the tile needs, a number that grows with the batch.
+int64_t crop_loss_least_partials(int B, int S, int p, int max_side) {
+  return (int64_t)B * (S / p) * crop_plan(S, p, max_side, 1, INT32_MAX).col_parts + kLossGroups;
+}
+// ... and that a caller is told to bring: with room for the column parts of crop_loss_min_parts, which are
+// fewer than 2 kCropFill in all whatever the batch, so that this grows with the batch as well and an epoch's
+// workspace serves its smaller last batch.
+int64_t crop_loss_most_partials(int B, int S, int p, int max_side) {
+  const int64_t least = crop_loss_least_partials(B, S, p, max_side);
+  const int64_t split = 2 * kCropFill + kLossGroups;
+  return 3 * p * p <= 768 || least > split ? least : split;
+}
+// Column parts that a small batch's rows of patches are split into at least for the loss over large
+// patches, whose workgroups take one patch after the other: so many that there are four of them per
+// compute unit (64 images of 256 pixels -> 192, p = 24, with their input pipeline: 44.4 -> 41.5 us), as far
+// as the workspace has room for their sums.  Where a part's patches are dealt to the wavefronts, or a
+// thread takes a position of all of them, fewer patches per part only repeat the set-up.
+int crop_loss_min_parts(int B, int S, int p, int64_t partials) {
+  const int64_t bands = (int64_t)B * (S / p);
+  int parts = 1;
+  if (3 * p * p <= 768) return parts;
+  while (bands * parts < kCropFill && 2 * bands * parts + kLossGroups <= partials) parts *= 2;
+  return parts;
 }
 
 // Doubles of workspace: one per workgroup, then kLossGroups for the first stage of their sum.

@@ -92,7 +92,9 @@ struct CropPlan {
 enum class CropUse { kOutputs, kLoss, kAugment };
 int crop_whole_rows(int S, int p, int max_side, CropUse use);
 CropPlan crop_plan(int S, int p, int max_side, int min_parts, int whole_rows);
-int crop_loss_min_parts(int B, int S, int p);
+int64_t crop_loss_least_partials(int B, int S, int p, int max_side);
+int64_t crop_loss_most_partials(int B, int S, int p, int max_side);
+int crop_loss_min_parts(int B, int S, int p, int64_t partials);
 size_t crop_lds_bytes(const CropArgs& a);
 hipError_t launch_crop_patch(const CropArgs& a, hipStream_t stream);
 // The same with the finetuning augmentation's pointwise operations as the epilogue: "3 Aug" writes

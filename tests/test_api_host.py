@@ -299,6 +299,40 @@ def test_loss_from_images_validates_both_descriptors(lib):
         binding.MAE_ERR_SHAPE
 
 
+def _images_loss_bytes(lib, B, S, p, side):
+    L = (S // p) ** 2
+    prep = _prep_desc(B=B, out_size=S, patch=p, num_keep=1, max_image_side=side)
+    loss = _loss_desc(B=B, L=L, D=3 * p * p, num_masked=B * max(L - 1, 1))
+    return prep, loss, lib.mae_loss_from_images_workspace_bytes(C.byref(prep), C.byref(loss))
+
+
+# Small batches of large patches are split into more parts, each of which leaves a partial sum: the size
+# that is asked for must not fall as the batch grows, or an epoch's workspace would refuse its last batch.
+@pytest.mark.parametrize("S,p", [(224, 28), (192, 24), (224, 32), (36, 18), (72, 18), (200, 20), (512, 32),
+                                 (224, 16), (224, 14)])
+@pytest.mark.parametrize("side", [0, 128, 500])
+def test_loss_from_images_takes_the_workspace_of_a_larger_batch(lib, S, p, side):
+    before = 0
+    for B in list(range(1, 300)) + [511, 512, 513, 1023, 1024, 1025, 4096]:
+        prep, loss, need = _images_loss_bytes(lib, B, S, p, side)
+        assert need >= before, B
+        assert _call_loss_from_images(lib, prep, loss, ws_bytes=need, prep_bytes=1 << 40) == \
+            binding.MAE_ERR_NO_DEVICE
+        before = need
+
+
+# Rows of patches staged whole and split as far as the tile needs it, a double per part: such a workspace
+# has always been accepted, so it stays enough (with fewer parts for a small batch).
+@pytest.mark.parametrize("B,S,p,parts", [(64, 192, 24, 1), (128, 224, 28, 1), (3, 224, 32, 2), (1, 18, 18, 1)])
+def test_loss_from_images_takes_a_workspace_without_room_for_more_parts(lib, B, S, p, parts):
+    prep, loss, need = _images_loss_bytes(lib, B, S, p, 256)
+    least = (B * (S // p) * parts + 128) * 8 + 256 * 4
+    assert need >= least
+    kw = dict(prep_bytes=1 << 40)
+    assert _call_loss_from_images(lib, prep, loss, ws_bytes=least, **kw) == binding.MAE_ERR_NO_DEVICE
+    assert _call_loss_from_images(lib, prep, loss, ws_bytes=least - 1, **kw) == binding.MAE_ERR_WORKSPACE
+
+
 def _embed_desc(**over):
     d = binding.MaeEmbedDesc()
     d.M, d.D, d.E, d.L = 196, 768, 768, 196

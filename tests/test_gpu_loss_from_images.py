@@ -103,6 +103,42 @@ def test_patches_of_more_than_768_values(S, p, B, bf16):
             _check(data, kw, synth.make_pred(2, B, L, D), bf16=bf16, norm_pix=norm_pix, what=f"S{S} p{p}")
 
 
+# An epoch's workspace serves its smaller last batch, and one without room for more column parts than the tile
+# needs gives the same loss with fewer of them; nothing behind either is written.
+@pytest.mark.parametrize("S,p,B,parts", [(192, 24, 100, 1), (224, 28, 3, 1), (224, 32, 74, 2), (36, 18, 1, 2),
+                                         (192, 16, 5, 1)])
+def test_workspaces_of_other_sizes(S, p, B, parts):
+    data = synth.make_images("gradient", B, seed=50 + p)
+    L, D = (S // p) ** 2, 3 * p * p
+    kw = dict(out_size=S, patch=p, num_keep=max(1, L // 4), seed=6, batch_index=2)
+    pred_host = synth.make_pred(4, B, L, D)
+    ref = oracle.prep_batch(*data, **kw)
+    M = B * (L - kw["num_keep"])
+    want, want_grad, _ = oracle.normpix_loss(pred_host, ref["target"], ref["mask"], num_masked=M)
+    pred = torch.from_numpy(pred_host).cuda()
+    dimg = to_device(*data)
+    buf, _, _, _ = _run(dimg, kw, pred)
+    desc = mae.make_prep_desc(*dimg, **kw)
+    least = (B * (S // p) * parts + 128) * 8 + 256 * 4  # rows of patches split as far as the tile needs it
+    twice = (dimg[0], *(x.repeat(2) for x in dimg[1:]))
+    pred2, mask2 = pred.repeat(2, 1, 1), buf.mask.repeat(2, 1)
+    room = mae.mae_loss_from_images_workspace_bytes(
+        mae.make_prep_desc(*twice, **kw), mae.make_loss_desc(pred2, None, mask2, num_masked=2 * M))
+    ldesc = mae.make_loss_desc(pred, None, buf.mask, num_masked=M)
+    for size in {least, mae.mae_loss_from_images_workspace_bytes(desc, ldesc), room}:
+        store = torch.full((size + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        loss = torch.full((1,), float("nan"), device="cuda")
+        grad = torch.full_like(pred, float("nan"))
+        mae.mae_normpix_loss_from_images(desc, buf.workspace, ldesc, loss, grad, store[:size])
+        torch.cuda.synchronize()
+        what = f"S{S} p{p} B{B} workspace {size}"
+        assert abs(float(loss.item()) - want) <= ATOL + RTOL * abs(want), what
+        check_grad(grad.cpu().numpy(), want_grad, D, M, what=what)
+        assert bool((store[size:] == 0xA5).all()), what
+    with pytest.raises(mae.MaeError):
+        mae.mae_normpix_loss_from_images(desc, buf.workspace, ldesc, loss, grad, store[:least - 8])
+
+
 # Crops several times as large as the output, where only the rows that are tapped are staged: all sizes of
 # crops in one batch, on either side of the line, one and several parts, patches of all kernels.
 @pytest.mark.parametrize("S,p", [(96, 16), (64, 32), (48, 4), (80, 20), (100, 10), (24, 2), (126, 14)])
