@@ -233,6 +233,7 @@ struct EmbedArgs {
   const float* pos;         // [L, E], nullable
   void* tokens;             // [M, E] bf16 or float
 };
+int embed_tile(int64_t M, int D, int E);
 hipError_t launch_patch_embed(const EmbedArgs& a, hipStream_t stream);
 
 }  // namespace mae

@@ -7,7 +7,7 @@
 // consecutive k of one row.
 //
 // A workgroup makes a tile of 256 x 256 results (eight wavefronts, 2 x 4, 128 x 64 each), or of 128 x 128
-// or 64 x 64 where larger ones would leave compute units idle (launch_patch_embed).  D is
+// or 64 x 64 where larger ones would leave compute units idle or take longer (embed_tile).  D is
 // walked in slices of 64 values, so that every row contributes one full 128-byte line per slice:
 // half-line requests cost the vector memory pipeline as much as whole lines.  The two operand
 // slices (of the large tile 512 rows of 128 bytes = 64 KiB) go from global memory straight into LDS
@@ -404,17 +404,34 @@ static hipError_t launch_cfg(const EmbedArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// The largest tile that gives the 256 compute units work: 256 x 256 from two rounds of tiles on,
-// 128 x 128 (eight wavefronts of 64 x 32) from a tile for every second unit on, else 64 x 64 with three
-// stages.  Times of 256 / 128 / 64 (inputs in the caches), 768 -> 768 in bf16: 784 rows 25 / 9.7 / 7.5 us, 3136 25 / 10.3 / 11.7, 12544
-// (147 tiles of 256) 27.0 / 27.6 / 33, 25088 (294) 53 / 43 / 61, 50176 (588) 83 / 82 / 118, 100352 153 /
-// 181 / 262; 32768 rows, 588 -> 1024 (512) 56 / 68 / 99; 4800 rows, 1200 -> 192 (76 tiles of 128) 34 / 13 / 10.
+// The side of the tiles.  Tiles of 64 x 64, with three stages, where 128 x 128 (eight wavefronts of 64 x 32)
+// would leave every second compute unit without one; 256 x 256 beyond two rounds of them, a compute unit
+// holding one at a time; in between what takes less time by the numbers of tiles that the busiest unit gets.
+// A tile of 256 takes 11 us and 1.3 us per slice, one of 128 (two of which share a unit) 1.5 us and 0.5, a
+// seventh more where rows do not begin on a line, and 2 us once.  That is within 5 % of the better one
+// of both wherever it was measured up to two rounds.  Times of 256 / 128 in us, inputs in the caches, bf16:
+//   large tiles     147          180          216          255          300          384          468          510
+//   768 -> 768   27.3 / 27.4  27.4 / 28.0  28.4 / 33.0  30.8 / 35.1  52.1 / 43.8  52.5 / 51.7  56.4 / 64.1  60.0 / 67.3
+//   588 -> 1024  24.1 / 26.1  24.4 / 26.7  25.9 / 31.8  28.2 / 33.5  46.8 / 41.1  47.4 / 50.0  51.1 / 62.5  53.4 / 65.4
+//   1200 -> 1024 36.7 / 43.2  38.6 / 45.2  40.2 / 51.5  44.0 / 56.4  75.5 / 71.1  76.3 / 82.9  81.8 / 105   86.1 / 110
+//   192 -> 384   14.2 / 9.0   14.3 / 12.0  14.5 / 12.6  15.3 / 13.3  25.6 / 16.0  26.2 / 19.7  27.8 / 22.9  29.5 / 23.3
+// Beyond: 516 of 768 -> 768 81.7 / 74.9, 600 82.4 / 80.4, 660 83.8 / 90.5, 1023 119 / 137; in fp32, whose outputs
+// leave the caches earlier, 660 92.0 / 97.8, 768 104 / 140.  64 / 128: 784 rows, 768 -> 768 (28 tiles of 128) 7.5 /
+// 9.7, 3136 (150) 11.7 / 10.3, 4800 rows, 1200 -> 192 (76) 10 / 13.
+int embed_tile(int64_t M, int D, int E) {
+  const auto tiles = [&](int side) { return ((M + side - 1) / side) * ((E + side - 1) / side); };
+  if (tiles(128) < 128) return 64;
+  const int64_t large = (tiles(256) + 255) / 256, small = (tiles(128) + 255) / 256;  // per compute unit
+  if (large > 2) return 256;
+  const int64_t nk = (D + kBK - 1) / kBK;
+  const int64_t small_time = 2000 + small * (150 + 50 * nk) * (D % kBK ? 115 : 100) / 10;  // in units of 1 ns
+  return small_time < large * (11000 + 1300 * nk) ? 128 : 256;
+}
+
 hipError_t launch_patch_embed(const EmbedArgs& a, hipStream_t stream) {
-  const auto tiles = [&](int side) {
-    return ((a.M + side - 1) / side) * ((a.E + side - 1) / side);
-  };
-  if (tiles(256) >= 512) return launch_cfg<4, 2, 2, 4, 2>(a, stream);
-  if (tiles(128) >= 128) return launch_cfg<2, 1, 2, 4, 2>(a, stream);
+  const int side = embed_tile(a.M, a.D, a.E);
+  if (side == 256) return launch_cfg<4, 2, 2, 4, 2>(a, stream);
+  if (side == 128) return launch_cfg<2, 1, 2, 4, 2>(a, stream);
   return launch_cfg<1, 1, 2, 2, 3>(a, stream);
 }
 

@@ -15,6 +15,7 @@ import paper_2404_00509_amd as mae
 from paper_2404_00509_amd import synth
 
 from helpers import gpu_prep
+from test_dispatch_rules import embed_tile
 
 pytestmark = pytest.mark.gpu
 
@@ -101,10 +102,10 @@ def test_embed_matches_the_oracle(M, D, E, L, bf16_out):
     _check(tokens, ref, S, D, bf16_out, f"M{M} D{D} E{E} L{L}")
 
 
-# The launch takes 256 x 256 tiles from 512 of them on, 128 x 128 from 128 of those on, else 64 x 64:
-# the sizes on either side of both lines, ragged in both directions, rows of every kind of last slice
-# (whole, half a chunk alone, one to four sub-steps with and without a half chunk) and fewer slices
-# than stages.
+# The launch takes 64 x 64 tiles where there are fewer than 128 of 128 x 128, then these or 256 x 256 by the
+# time that either needs (the large ones for the largest D here): the sizes on either side, ragged
+# in both directions, rows of every kind of last slice (whole, half a chunk alone, one to four sub-steps
+# with and without a half chunk) and fewer slices than stages.
 @pytest.mark.parametrize("D", [4, 16, 20, 40, 52, 64, 128, 140, 192, 200])
 @pytest.mark.parametrize("M,E", [(4090, 8190), (4093, 8188), (3838, 8190), (1020, 2041), (1020, 1916)])
 def test_embed_tile_sizes_and_last_slices(M, E, D):
@@ -121,6 +122,14 @@ def test_embed_tile_sizes_and_last_slices(M, E, D):
         mae.mae_patch_embed(mae.make_embed_desc(dv, di, dw, padded[1:], dp, out_dtype=mae.MAE_BF16
                                                 if bf16_out else mae.MAE_F32), again)
         assert torch.equal(again, tokens)
+
+
+# ... and more than two rounds of 256 x 256 tiles, which are taken for every D.
+@pytest.mark.parametrize("D", [4, 16, 20, 40, 52, 64, 128, 140, 192, 200])
+@pytest.mark.parametrize("M,E", [(4100, 8190), (4099, 8188)])
+def test_embed_large_tiles_and_last_slices(M, E, D):
+    assert embed_tile(M, D, E) == 256
+    test_embed_tile_sizes_and_last_slices(M, E, D)
 
 
 @pytest.mark.parametrize("with_bias,with_pos", [(False, False), (True, False), (False, True)])
