@@ -164,7 +164,7 @@ mae::CropPlan crop_plan_of(const mae_prep_desc* d, int slot_side, mae::CropUse u
                            int min_parts = 1) {
   const int side = crop_side_of(d, slot_side);
   return mae::crop_plan(d->out_size, d->patch, side, min_parts,
-                        mae::crop_whole_rows(d->out_size, d->patch, side, use));
+                        mae::crop_whole_rows(d->B, d->out_size, d->patch, side, use));
 }
 mae::CropUse prep_use(const mae_prep_desc* d) {
   return d->aug_mode == MAE_AUG_SIMPLE ? mae::CropUse::kOutputs : mae::CropUse::kAugment;
@@ -261,7 +261,7 @@ mae::CropArgs make_crop_args(const mae_prep_desc* d, const PrepShape& sh, const 
   ca.col_parts = plan.col_parts;
   ca.part_patches = plan.part_patches;
   ca.max_side = crop_side_of(d, wsl.slot_side);
-  ca.whole_rows = mae::crop_whole_rows(d->out_size, d->patch, ca.max_side, use);
+  ca.whole_rows = mae::crop_whole_rows(d->B, d->out_size, d->patch, ca.max_side, use);
   for (int c = 0; c < 3; ++c) {
     ca.nscale[c] = (float)(1.0 / (255.0 * (double)d->std[c]));
     ca.nbias[c] = (float)(-(double)d->mean[c] / (double)d->std[c]);

@@ -38,6 +38,7 @@ constexpr int kCropMaxThreads = 1024;  // resampling kernel: 64 threads per 64 g
 constexpr int kStageRows = 7;  // rows per wavefront whose loads are issued together
 constexpr int kCropMaxLds = 64 * 1024;      // dynamic LDS available without opting in to more
 constexpr int kCropFill = 1024;             // workgroups that a launch should have
+constexpr int kComputeUnitLds = 160 * 1024;
 constexpr int kCropTileTarget = 40 * 1024;  // LDS per workgroup that still leaves 4 per compute unit
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -1338,6 +1339,10 @@ __global__ __launch_bounds__(kCropThreads) void crop_patch_scalar_kernel(CropArg
 static int64_t tapped_rows(int S, int p, int max_side) {
   return ((int64_t)(p - 1) * max_side + S - 1) / S + 2;
 }
+// Bytes of dynamic LDS of a workgroup.
+static int crop_plan_lds(const CropPlan& plan, int p) {
+  return (plan.tile_pixels + 4) * 4 + p * 16 + plan.part_patches * p * 8;
+}
 // Source rows of a row of patches that are staged as they follow each other; where a crop has more, the
 // 2 p that are tapped.  Fewer rows make the tile smaller, so that more workgroups share a compute unit, and
 // leave out what is not tapped; but the requests no longer run beside the tap tables, which the outputs of
@@ -1346,9 +1351,27 @@ static int64_t tapped_rows(int S, int p, int max_side) {
 // 160, p = 16: 290 / 194; 500 -> 220, p = 20: 327 / 374, 500 -> 128, p = 32: 213 / 250, 500 -> 100, p = 20 with
 // its loss: 395 / 252.  Loss from the images, with its input pipeline: 500 -> 96, p = 16: 814 / 203, 500 -> 224,
 // p = 28: 938 / 760.  Augmentation, "3 Aug+": 500 -> 160, p = 32: 535 / 368, 500 -> 224, p = 32: 583 / 484.
-int crop_whole_rows(int S, int p, int max_side, CropUse use) {
+// Where hardly more rows than the tapped ones lie between them (up to a quarter), this is worth it only if it
+// saves a column part or lets another workgroup onto a compute unit.  Rows 2 p / all, times all / pairs:
+// 512 images 500 -> 224, p = 16, 32 / 36, four workgroups either way: outputs 139.3 / 140.1, kept patches 87.9 / 89.2,
+// "3 Aug" 254.3 / 256.5; p = 14, 28 / 32, four against five: 146.9 / 132.9, 91.7 / 83.1, 308 / 283; 1024 images 256 ->
+// 120, p = 20, 40 / 43, seven either way, "3 Aug+" 219.3 / 223.3.  And, for outputs, only if there are more than two
+// rounds of workgroups: 64 images 256 -> 112, p = 14, 12.8 / 13.2, 500 -> 224, p = 14, 25.7 / 25.9.  A workgroup of one
+// wavefront (p up to 8) has few rows on their way at once, so that every row counts: 1024 images 256 -> 112, p = 8,
+// 16 / 18: 108.7 / 100.6.
+int crop_whole_rows(int B, int S, int p, int max_side, CropUse use) {
   if (p & 1) return INT32_MAX;  // (crop_pixels_staged has the rule for them)
-  if (use == CropUse::kOutputs && p > 16 && tapped_rows(S, p, max_side) <= 4 * p) return INT32_MAX;
+  const int64_t rows = tapped_rows(S, p, max_side);
+  if (use == CropUse::kOutputs && p > 16 && rows <= 4 * p) return INT32_MAX;
+  if (p > 8 && 4 * rows <= 10 * p) {
+    const CropPlan whole = crop_plan(S, p, max_side, 1, INT32_MAX), pairs = crop_plan(S, p, max_side, 1, 2 * p);
+    const int at_once = kComputeUnitLds / crop_plan_lds(whole, p);
+    if (whole.col_parts == pairs.col_parts &&
+        (at_once == kComputeUnitLds / crop_plan_lds(pairs, p) ||
+         // (the others' plans, of which partial sums are kept, don't depend on the batch)
+         (use == CropUse::kOutputs && (int64_t)B * (S / p) * whole.col_parts <= 2 * 256 * at_once)))
+      return INT32_MAX;
+  }
   return 2 * p;
 }
 // Whether crops of images of up to max_side pixels may have more.
@@ -1389,7 +1412,7 @@ CropPlan crop_plan(int S, int p, int max_side, int min_parts, int whole_rows) {
 }
 
 size_t crop_lds_bytes(const CropArgs& a) {
-  return (size_t)(a.tile_pixels + 4) * 4 + (size_t)a.p * 16 + (size_t)a.part_patches * a.p * 8;
+  return (size_t)crop_plan_lds(CropPlan{a.col_parts, a.part_patches, a.tile_pixels}, a.p);
 }
 
 // First stage of adding the workgroups' partial sums (there are tens of thousands): workgroup w

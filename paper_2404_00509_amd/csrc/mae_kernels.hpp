@@ -90,7 +90,7 @@ struct CropPlan {
 };
 // What a plan is for: outputs of the input pipeline, the loss from the images, the augmentation.
 enum class CropUse { kOutputs, kLoss, kAugment };
-int crop_whole_rows(int S, int p, int max_side, CropUse use);
+int crop_whole_rows(int B, int S, int p, int max_side, CropUse use);
 CropPlan crop_plan(int S, int p, int max_side, int min_parts, int whole_rows);
 int64_t crop_loss_least_partials(int B, int S, int p, int max_side);
 int64_t crop_loss_most_partials(int B, int S, int p, int max_side);

@@ -44,3 +44,46 @@ def test_tiles_of_the_embedding_at_the_ends_of_its_range():
     assert embed_tile(1 << 28, 4, 1) == 256
     for D in (4, 64, 588, 3072):  # beyond two rounds
         assert embed_tile(256 * 513, D, 256) == 256
+
+
+OUTPUTS, LOSS, AUGMENT = 0, 1, 2
+ALL_ROWS = 0x7FFFFFFF
+
+
+def staged_rows(B, S, p, side, use):
+    rule = mae.load()._ZN3mae15crop_whole_rowsEiiiiNS_7CropUseE
+    rule.argtypes, rule.restype = (C.c_int,) * 5, C.c_int
+    return rule(B, S, p, side, use)
+
+
+# images, their side, output, patch: all rows between the first and the last that is tapped, or pairs of rows
+@pytest.mark.parametrize("use,B,side,S,p,whole,pairs", [
+    (OUTPUTS, 512, 500, 224, 16, 87.9, 89.2), (OUTPUTS, 64, 500, 224, 16, 20.0, 20.7),
+    (OUTPUTS, 512, 500, 240, 16, 94.0, 95.6), (OUTPUTS, 1024, 256, 112, 16, 43.9, 44.7),
+    (OUTPUTS, 512, 500, 224, 14, 91.7, 83.1), (OUTPUTS, 64, 500, 224, 14, 20.5, 20.9),
+    (OUTPUTS, 1024, 256, 112, 14, 46.2, 42.8), (OUTPUTS, 64, 256, 112, 14, 12.8, 13.2),
+    (OUTPUTS, 1024, 256, 112, 8, 63.8, 59.1), (OUTPUTS, 64, 256, 112, 8, 15.7, 15.4),
+    (OUTPUTS, 512, 500, 192, 16, 134.0, 122.4), (OUTPUTS, 64, 500, 192, 16, 25.3, 23.6),
+    (OUTPUTS, 512, 500, 192, 12, 170.5, 126.8), (OUTPUTS, 64, 500, 192, 12, 27.4, 25.6),
+    (OUTPUTS, 512, 500, 160, 16, 150.8, 101.5), (OUTPUTS, 512, 500, 128, 8, 191.8, 140.6),
+    (OUTPUTS, 1024, 256, 64, 4, 53.6, 39.5), (OUTPUTS, 512, 500, 224, 28, 215.0, 247.0),
+    (OUTPUTS, 512, 500, 192, 24, 144.3, 170.4), (OUTPUTS, 512, 500, 224, 32, 188.9, 203.5),
+    (OUTPUTS, 512, 500, 200, 20, 152.1, 174.1), (OUTPUTS, 1024, 256, 120, 20, 94.9, 108.0),
+    (LOSS, 512, 500, 224, 16, 224.7, 227.5), (LOSS, 64, 500, 224, 16, 47.2, 48.1),
+    (LOSS, 512, 500, 192, 16, 273.3, 198.7), (LOSS, 512, 500, 224, 14, 244.8, 239.8),
+    (AUGMENT, 512, 500, 224, 16, 254.3, 256.5), (AUGMENT, 64, 500, 224, 16, 43.6, 44.4),
+    (AUGMENT, 512, 500, 224, 14, 308.1, 283.2), (AUGMENT, 512, 500, 240, 16, 280.1, 283.2),
+    (AUGMENT, 512, 500, 224, 32, 388.8, 324.9), (AUGMENT, 512, 500, 200, 20, 286.7, 254.9),
+    (AUGMENT, 1024, 256, 120, 20, 219.3, 223.3), (AUGMENT, 512, 500, 224, 28, 463.3, 443.9)])
+def test_staged_rows_of_large_crops(use, B, side, S, p, whole, pairs):
+    rows = staged_rows(B, S, p, side, use)
+    assert rows in (2 * p, ALL_ROWS)
+    assert (whole if rows == ALL_ROWS else pairs) <= 1.001 * min(whole, pairs)
+
+
+def test_staged_rows_of_the_loss_and_the_augmentation_do_not_depend_on_the_batch():
+    # (partial sums are kept per column part, of which a shard has as many as the whole batch)
+    for use in (LOSS, AUGMENT):
+        for S, p in ((112, 14), (224, 14), (224, 16), (224, 32), (120, 20), (112, 8)):
+            for side in (256, 500):
+                assert len({staged_rows(B, S, p, side, use) for B in (1, 64, 512, 4096)}) == 1
