@@ -1177,7 +1177,12 @@ __global__ __launch_bounds__(kJpegThreads) void jpeg_scan_kernel(JpegArgs a) {
 // A lane that waits goes through the steps with an entry that moves nothing, and not around them: a
 // branch per step, even one that is never taken, costs more than it can save, since a wavefront has its
 // SIMD to itself (the walk below 650 -> 576 us, entropy decoding 762 -> 718 us with the value of a
-// symbol made while the next one is looked up; with a way out where all lanes wait 733 us).
+// symbol made while the next one is looked up; with a way out where all lanes wait 733 us).  Files whose blocks
+// are nearly all ended by their first or second symbol pay for it: whole calls with 1024 files of 256 pixels
+// without markers, gradients and discs without noise at quality 50 1122 -> 1168 us, one colour 325 -> 336 (with
+// a restart interval per row 306 -> 336).  A way out after the first step gives 317 and 303 there, but 982 instead of 936
+// for gradients with noise at quality 90; steps of which all but the first are left out while all lanes
+// waited in the round before, 1083.
 constexpr int kLongCodes = 512;  // entries for codes beyond the direct part of a table
 constexpr int kDirect = 1 << kFastBits;
 constexpr int kSteps = 6;    // AC symbols of at most 31 bits between two points that all lanes pass
@@ -1302,17 +1307,26 @@ struct alignas(16) WalkMark {
   uint16_t dc[3];         // sums of DC differences per component, modulo 2^16 like the predictors
   uint16_t pad;
 };
+// What several wavefronts tell each other.
 template <int kWaves>
-struct JpegSyncLds {
+struct SyncExchange {
+  int sums[kWaves][4];   // per wavefront: blocks, DC differences
+  int asked[2][kWaves];  // has a lane to walk again? (in turn)
+  int tail[4];           // last part: block it is left at; DC differences of an MCU of zero bits
+};
+template <>
+struct SyncExchange<1> {};  // (exchanged in registers)
+template <int kWaves>
+struct JpegSyncLds : SyncExchange<kWaves> {
   uint16_t table[kCoefTable];
   uint32_t ring[kWaves][kRingBytes / 4][kJpegThreads];  // big-endian dwords of the data
   WalkMark mark[kMarks + 1][kWaves * kJpegThreads];     // [0]: the entry; bit -1 = none
   // per part: what came before it; until that is known where the part is left, bit and block
   int first_block[kWaves * kJpegThreads], dc[3][kWaves * kJpegThreads];
-  int sums[kWaves][4];     // per wavefront: blocks, DC differences
-  int asked[2][kWaves];    // has a lane to walk again? (in turn)
-  int tail[4];             // last part: block it is left at; DC differences of an MCU of zero bits
 };
+// (48 bytes more and it is seven: whole calls with 2000 files of 256 pixels 1.69 ms instead of 1.28, 4096 2.88
+// instead of 2.54, 2000 of 500 pixels 4.34 instead of 3.51)
+static_assert(sizeof(JpegSyncLds<1>) <= 160 * 1024 / 8, "eight files at a time on a compute unit");
 // Reads the data of one image, a bit position at a time.  (hi:lo) >> left are the next 32 bits.
 struct CleanReader {
   const uint8_t* clean;
@@ -1474,22 +1488,26 @@ __global__ __launch_bounds__(kWaves * kJpegThreads) void jpeg_sync_kernel(JpegAr
             d2 += t2;
           }
         }
-        if (lane % kWave == kWave - 1) {
-          s.sums[wave][0] = first_block;
-          s.sums[wave][1] = d0;
-          s.sums[wave][2] = d1;
-          s.sums[wave][3] = d2;
-        }
-        __syncthreads();
-        total = 0;
+        if constexpr (kWaves == 1) {
+          total = __shfl(first_block, kWave - 1);
+        } else {
+          if (lane % kWave == kWave - 1) {
+            s.sums[wave][0] = first_block;
+            s.sums[wave][1] = d0;
+            s.sums[wave][2] = d1;
+            s.sums[wave][3] = d2;
+          }
+          __syncthreads();
+          total = 0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-          total += s.sums[w][0];
-          if (w >= wave) continue;
-          first_block += s.sums[w][0];
-          d0 += s.sums[w][1];
-          d1 += s.sums[w][2];
-          d2 += s.sums[w][3];
+          for (int w = 0; w < kWaves; ++w) {
+            total += s.sums[w][0];
+            if (w >= wave) continue;
+            first_block += s.sums[w][0];
+            d0 += s.sums[w][1];
+            d1 += s.sums[w][2];
+            d2 += s.sums[w][3];
+          }
         }
         first_block -= blocks;
         s.first_block[lane] = first_block;
@@ -1690,21 +1708,34 @@ __global__ __launch_bounds__(kWaves * kJpegThreads) void jpeg_sync_kernel(JpegAr
       if (__builtin_expect((im->clean_bytes & kCutShort) != 0, 0)) {
         // Behind a file that merely stops a row is zero bits, and so are the blocks between the last
         // that the data began and the row's first (the rest of an MCU, then whole ones).
-        if (lane == parts - 1) {
-          s.tail[0] = leave_phase;
-          s.tail[1] = sum0;
-          s.tail[2] = sum1;
-          s.tail[3] = sum2;
+        int ph, mcu0, mcu1, mcu2, end0 = 0, end1 = 0, end2 = 0;
+        if constexpr (kWaves == 1) {
+          ph = __shfl(leave_phase, kWave - 1);
+          mcu0 = __shfl(sum0, kWave - 1);
+          mcu1 = __shfl(sum1, kWave - 1);
+          mcu2 = __shfl(sum2, kWave - 1);
+          end0 = s.dc[0][kWave - 1] + __shfl(dc0, kWave - 1);
+          end1 = s.dc[1][kWave - 1] + __shfl(dc1, kWave - 1);
+          end2 = s.dc[2][kWave - 1] + __shfl(dc2, kWave - 1);
+        } else {
+          if (lane == parts - 1) {
+            s.tail[0] = leave_phase;
+            s.tail[1] = sum0;
+            s.tail[2] = sum1;
+            s.tail[3] = sum2;
+          }
+          __syncthreads();
+          ph = s.tail[0];
+          mcu0 = s.tail[1];
+          mcu1 = s.tail[2];
+          mcu2 = s.tail[3];
+          for (int w = 0; w < kWaves; ++w) {
+            end0 += s.sums[w][1];
+            end1 += s.sums[w][2];
+            end2 += s.sums[w][3];
+          }
         }
-        __syncthreads();
-        const int ph = s.tail[0], rest = ph ? per_mcu - ph : 0;
-        const int mcu0 = s.tail[1], mcu1 = s.tail[2], mcu2 = s.tail[3];
-        int end0 = 0, end1 = 0, end2 = 0;
-        for (int w = 0; w < kWaves; ++w) {
-          end0 += s.sums[w][1];
-          end1 += s.sums[w][2];
-          end2 += s.sums[w][3];
-        }
+        const int rest = ph ? per_mcu - ph : 0;
         for (int i = lane; i < nrows; i += kParts) {
           const int target = (my0 + i) * row_blocks;
           if (target < total || target == 0) continue;
