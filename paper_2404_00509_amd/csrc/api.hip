@@ -144,8 +144,10 @@ int32_t mae_num_keep(int32_t L, double mask_ratio) {
 
 namespace {
 // Workspace: header | CropRec[B] | (augmentation) 8-bit resized crops, S * S * 3 bytes each |
-// (jitter) one double per (image, row of patches, column part of the blur kernel); every part
-// starts on a 256-byte boundary.
+// (jitter) luma sums, a double each: B * blur_luma_slots(S, p) of the blur, which keeps one per band of
+// 16 rows and its column part for patches of 16 and 32 pixels, else one per row of patches and column part;
+// then one per image, row of patches and column part of the resampling kernel; every part
+// starts on a 256-byte boundary (the resampling kernel's sums follow the blur's directly).
 struct PrepWorkspace {
   size_t aug_offset, u8_offset, partials_offset, crop_partials_offset, total;
   // crop decode: per-file records, heights, widths, region widths, region offsets, tables, planes, regions
@@ -190,8 +192,7 @@ PrepWorkspace prep_workspace(const mae_prep_desc* d) {
     w.partials_offset = up(w.u8_offset + (size_t)d->B * d->out_size * d->out_size * 3);
     w.total = w.partials_offset;
     if (d->aug_mode == MAE_AUG_THREE_PLUS) {
-      // luma sums per (image, row of patches, column part): of the blur kernel, then of the
-      // resampling kernel
+      // luma sums of the blur, then of the resampling kernel
       const size_t rows = (size_t)d->B * (d->out_size / d->patch);
       w.crop_partials_offset =
           w.total + (size_t)d->B * mae::blur_luma_slots(d->out_size, d->patch) * sizeof(double);
@@ -380,7 +381,7 @@ int mae_prep_batch(const mae_prep_desc* d, void* visible, uint8_t* mask, int32_t
   aa.D = ca.D;
   aa.visible_bf16 = ca.visible_bf16;
   aa.mode = d->aug_mode;
-  const mae::AugPlan aplan = mae::three_aug_plan(d->out_size, d->patch);
+  const mae::AugPlan aplan = mae::three_aug_plan(d->out_size, d->patch);  // (patches of 16 and 32: not used)
   aa.blur_parts = aplan.parts;
   aa.blur_part_patches = aplan.part_patches;
   aa.band_parts = mae::blur_band_parts(d->out_size, d->patch);

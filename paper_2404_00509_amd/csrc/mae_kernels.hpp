@@ -119,7 +119,7 @@ struct AugArgs {
   const int32_t* ids_restore;
   const uint8_t* workspace;  // header + CropRec[B] (valid flags)
   const void* aug_recs;      // AugParams[B], written by the parameter kernel
-  double* partials;          // [B * G * blur_parts] luma sums of the blur images, mode 2
+  double* partials;          // [B * blur_luma_slots] luma sums of the blur images, mode 2
   const double* luma_partials;  // [B * luma_slots] of the other images, from the resampling kernel
   int32_t luma_slots;
   void* visible;
