@@ -151,6 +151,16 @@ def test_crops_of_which_only_the_tapped_rows_are_staged(S, p):
         _check(data, kw, synth.make_pred(3, B, L, D), max_image_side=side, what=f"S{S} p{p}")
 
 
+# ... and just over twice as large, where all rows are staged unless that costs a workgroup.
+@pytest.mark.parametrize("S,p,side", [(224, 16, 500), (224, 14, 500), (224, 28, 500), (112, 16, 256), (120, 20, 256)])
+def test_crops_just_over_twice_the_output(S, p, side):
+    B = 6
+    data = synth.make_images("gradient500" if side == 500 else "gradient", B, seed=45 + p)
+    L, D = (S // p) ** 2, 3 * p * p
+    kw = dict(out_size=S, patch=p, num_keep=max(1, L // 4), scale=(0.8, 1.0), seed=5, batch_index=2)
+    _check(data, kw, synth.make_pred(3, B, L, D), max_image_side=side, what=f"S{S} p{p}")
+
+
 def test_unnormalised_variant_scale_and_loss_only():
     B, S, p = 8, 112, 16
     data = synth.make_images("uniform", B, seed=5)

@@ -502,6 +502,23 @@ def test_prep_of_crops_of_which_only_the_tapped_rows_are_staged(S, p, aug):
             check_prep_against_oracle(prep_to_numpy(buf), ref, bf16=bf16, what=f"S{S} p{p} aug {aug}")
 
 
+# ... and crops that tap nearly all of the rows between the first and the last tapped one, which are staged whole
+# up to a quarter more rows than 2 p where that costs no workgroup of a compute unit (or, for the outputs of a batch
+# of two rounds of workgroups or fewer, always): on either side of these lines.
+@pytest.mark.parametrize("S,p,side,aug", [(224, 16, 500, 0), (240, 16, 500, 0), (112, 16, 256, 0), (112, 14, 256, 0),
+                                          (112, 8, 256, 0), (224, 16, 500, 1), (120, 20, 256, 1), (112, 14, 256, 1),
+                                          (224, 16, 500, 2), (120, 20, 256, 2), (224, 28, 500, 2)])
+def test_prep_of_crops_just_over_twice_the_output(S, p, side, aug):
+    data = synth.make_images("gradient500" if side == 500 else "gradient", 6, seed=90 + S + p)
+    L = (S // p) ** 2
+    kw = dict(out_size=S, patch=p, num_keep=max(1, L // 2), scale=(0.8, 1.0), seed=9, aug_mode=aug)
+    assert max(data[2].max(), data[3].max()) == side
+    ref = oracle.prep_batch(*data, **kw)
+    for bf16 in (False, True):
+        buf, _, _ = gpu_prep(*data, bf16=bf16, max_image_side=side, **kw)
+        check_prep_against_oracle(prep_to_numpy(buf), ref, bf16=bf16, what=f"S{S} p{p} side {side} aug {aug}")
+
+
 @pytest.mark.parametrize("shift", [1, 2, 3])
 def test_prep_image_buffer_with_unaligned_base_and_tight_end(shift):
     # the staging loads are 4-byte aligned 16-byte reads; with an unaligned base pointer and no
