@@ -10,7 +10,9 @@
 //    operations in registers) and writes four pixel words with one ds_write_b128.  All loads of a
 //    wavefront (up to seven rows) are issued before the first is consumed, and the tap tables
 //    (S horizontal entries, p vertical entries, integer tap positions + fp32 weights) are built
-//    while they are in flight.
+//    while they are in flight.  Of crops that are much larger than the output only the two rows that
+//    every output row taps are staged (crop_whole_rows); their loads come behind the tables, four
+//    rows of a wavefront at a time.
 //  * Compute + store.  A patch is D/4 groups of 16 bytes; wavefront w of the workgroup owns groups
 //    64w .. 64w+63 (one per lane) of EVERY patch of the row, so what depends only on the position
 //    inside the patch (rows tapped, vertical weights, channel constants, byte selectors) is set
@@ -22,8 +24,7 @@
 //  * Variants of the last phase on the same staged tile: the finetuning augmentation as the
 //    epilogue (produce_aug: values rounded to bytes in integers, grayscale / solarisation; the images
 //    that drew the blur, and all of them when the colour jitter follows, leave as bytes for the
-//    kernels of three_aug.hip); the kept
-//    patches only (no target wanted); and the loss itself
+//    kernels of three_aug.hip); the kept patches only (no target wanted); and the loss itself
 //    (produce_loss_wave, produce_loss_group): the masked patches' values stay in registers, are
 //    normalised per patch and compared with the prediction, so that no float target is ever
 //    stored or read back.

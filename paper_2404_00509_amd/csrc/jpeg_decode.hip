@@ -2518,10 +2518,14 @@ __global__ __launch_bounds__(kIdctThreads) void jpeg_idct_kernel(JpegArgs a, int
 
 // Wavefronts per file.  Long files fill more than one with parts of kPartBits bits, which shortens the
 // walks until the SIMDs have other files to switch to; on files of 256 pixels (2200 to 3200 bits in each of
-// 64 parts) shorter parts only take more rounds.  Whole calls with 1 / 2 / 4 of them in us, files without
-// markers of 500 pixels: 16 files 1740 / 1404 / 1298, 128 1863 / 1527 / 1491, 512 2137 / 1853 / 1675, 1024
-// 2455 / 2284 / 2631; with 2200 bits or less in a part, 256 pixels: 16 files 674 / 642 / 686, 256 809 / 820 /
-// 833, 1024 1058 / 1110 / 1486, 2048 1783 / 1886 / 2627.
+// 64 parts) shorter parts only take more rounds.  The line is drawn by what the call knows of its files, the
+// largest side that they may have.  Whole calls with 1 / 2 / 4 wavefronts in us, files without markers whose
+// sides reach the limit: 300 pixels, 16 files 768 / 728 / 725, 512 1068 / 1096 / 1089; 320 pixels, 16 files 862 / 771 / 779, 512
+// 1121 / 1068 / 1056, 1024 1299 / 1243 / 1741; 384 pixels, 128 files 1221 / 1039 / 1063, 512 1493 / 1328 / 1312, 1024 1743 / 1522 /
+// 2087; 500 pixels, 16 files 1622 / 1214 / 1141, 128 1761 / 1420 / 1311, 512 2045 / 1766 / 1604, 1024 2337 / 2113 / 2532.  Short
+// files under a large limit leave wavefronts without a part: 256 pixels and a limit of 500, 16 files 670 / 697 /
+// 688, 512 921 / 943 / 944, 1024 1141 / 1144 / 1583; a limit of 320, 16 files 671 / 695 / 707; 160 and 500, 512 files 796 / 789 /
+// 778.
 static hipError_t launch_sync(const JpegArgs& a, hipStream_t stream) {
   const int waves = a.slot_side < 320 || a.B > 1024 ? 1 : (a.B > 512 ? 2 : 4);
   if (waves == 4)

@@ -25,14 +25,19 @@
 // accesses, so it does not make each of them wait for every direct load in flight (which would
 // undo the pipeline); the code waits on lgkmcnt itself and reads one sub-step ahead.
 //
-// What bounds the large tile is the compute unit's vector memory pipeline, not the matrix cores: a load
-// of 1 KiB takes it about 35 cycles, a tile of D = 768 is 768 operand loads, 256 of positional rows and
-// 128 to 256 stores, and a wavefront that finds the pipeline full cannot issue its multiplies either.  Hence the
-// large tile, which needs the fewest operand bytes per result, and loads that are spread over three of
-// a slice's four sub-steps.  200704 rows, 768 -> 768, inputs from memory: 300 us in bf16, 340 in fp32 (with
-// the turn between slices where nothing is multiplied, a burst of loads behind it and lines of later
-// slices requested into L2: 311 and 357; with such requests beside the present loads 304 and 347);
-// 32768 rows, 588 -> 1024: 62 and 70 us (63 and 74).
+// What bounds the large tile.  200704 rows, 768 -> 768, bf16, by a clock read at the turns of every
+// workgroup: a tile takes 31.3 us at the 1.91 GHz that the card holds in this kernel, 3.8 until its
+// first slice is there, 20.4 for eleven slices (3540 cycles each), 1.5 for the last one, 5.7 for the epilogue; a
+// compute unit makes 9.2 of them one after the other, the tenth round a fifth full.  The matrix
+// instructions are 12.8 us of it (2048 cycles of a slice).  In a slice no unit is busy all the time: beside them the
+// LDS moves 256 KiB (2048 cycles: 192 KiB of fragments, 64 KiB coming in), and 64 loads of 1 KiB take the
+// vector memory pipeline about 35 cycles each (2240); over the kernel the counters show the data return
+// of that pipeline at work 75 % of the time and the wavefronts 34 % waiting for data or barriers, 41 % for an
+// instruction to be taken.  Hence the large tile, which needs the fewest operand bytes per result, and loads that
+// are spread over three of a slice's four sub-steps.  Calls with inputs from memory: 310 us in bf16, 343 in fp32 (324
+// and 370 with the turn between slices where nothing is multiplied, a burst of loads behind it and lines of later
+// slices requested into L2; with such requests beside the present loads 1 and 2 % slower than without); 32768 rows,
+// 588 -> 1024: 60 and 62 us (65 and 75).
 //
 // Epilogue: each wavefront turns its accumulators into rows through a private strip of LDS, 32
 // rows at a time, so that the stores to `tokens` and the loads of the positional rows are
